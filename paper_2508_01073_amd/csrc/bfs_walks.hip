@@ -20,10 +20,10 @@
 // offers). Every root starts in one tier, picked from the expected tree size; a
 // root whose tree outgrows a tier is abandoned there and queued for the next.
 // The last pass, a persistent grid of workgroups that each own a slice of the
-// workspace (per-entity stamps and offers, the tree beyond its first kTreeLds
-// positions; about 36 bytes per entity), reruns the roots no tier could hold
-// from scratch. All loops are bounded by the tree and level sizes or the table
-// size; a workgroup never waits for another.
+// workspace, reruns the roots no tier could hold from scratch: it takes the
+// pairs of a level in order, a chunk at a time, with one "reached" bit per
+// entity instead of per-entity offers. All loops are bounded by the tree and
+// level sizes or the table size; a workgroup never waits for another.
 
 #include <algorithm>
 
@@ -33,9 +33,6 @@
 namespace rdf2v {
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kLevelLds = 1024;  // levels of at most this many entities keep their prefix and row starts in LDS
-
 struct BfsArgs {
   const int32_t *row_ptr;
   const int32_t *edges;  // (predicate, object) pairs
@@ -44,10 +41,8 @@ struct BfsArgs {
   int32_t *lens;
   int32_t *counts;
   int32_t *status;
-  int32_t *queue_counts;  // [6]: lengths of the queues below, then how far each has been taken
+  int32_t *queue_counts;  // [kQueueCounters]: lengths of the queues below, then how far each has been taken
   int32_t *queue[3];      // roots (indices into roots) LDS tier i could not hold
-  char *workspace;        // slices of the workspace pass
-  size_t slice_bytes;
   int64_t num_roots;
   int64_t num_edges;
   int32_t num_entities;
@@ -56,65 +51,22 @@ struct BfsArgs {
   int32_t max_walks;
 };
 
-// Workspace slice of one workgroup: mark, offer (8 B), ent, parent, pred,
-// level, has_child, and the degree prefix of a level (V + 1 entries).
+// Slots of queue_counts: the lengths of the three tiers' queues, then how far
+// each was taken (tier t takes queue t - 1 through slot 3 + t: slots 4 and 5),
+// then the bitmap pass: queue 2 taken, and the length and taken count of the
+// queue of its second run (queue 0 again, which is used up by then).
+constexpr int kQueueCounters = 9;
+constexpr int kWideTaken = 6, kWide2Length = 7, kWide2Taken = 8;
+
+// The workspace is sized in units of 36 bytes per entity, about 4 GiB of them
+// at most and one at least.
 inline size_t slice_bytes(int64_t V) {
   return align_up(size_t(V) * 4, 256) * 6 + align_up(size_t(V) * 8, 256) + align_up(size_t(V + 1) * 4, 256);
 }
 
-// Workspace: the queue counters, three queues (one int32 per root each), the slices.
+// Workspace: the queue counters, three queues (one int32 per root each), the
+// slices of the bitmap pass.
 inline size_t queue_bytes(int64_t num_roots) { return 256 + 3 * align_up(size_t(num_roots) * 4, 256); }
-
-// Scratch arrays are shared by the whole workgroup and written by atomics or by
-// other lanes; agent-scope relaxed accesses keep every read at L2.
-__device__ __forceinline__ int32_t ld(const int32_t *p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st(int32_t *p, int32_t v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ uint64_t ld64(const uint64_t *p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// The tree of the current root: positions below kTreeLds live in LDS (parent
-// as int16, level and "has a child" as bytes), the rest in the workgroup's
-// global slice. Positions are assigned in the order entities are reached, so
-// small trees and the first levels of big ones stay in LDS.
-constexpr int kTreeLds = 1024;
-
-struct Tree {
-  int32_t *ent_s;
-  int16_t *par_s;
-  int32_t *pred_s;
-  uint8_t *lev_s;
-  uint8_t *child_s;
-  int32_t *ent, *parent, *pred, *level, *has_child;  // global tier
-  __device__ __forceinline__ int32_t get_ent(int32_t i) const { return i < kTreeLds ? ent_s[i] : ld(ent + i); }
-  __device__ __forceinline__ int32_t get_par(int32_t i) const { return i < kTreeLds ? par_s[i] : ld(parent + i); }
-  __device__ __forceinline__ int32_t get_pred(int32_t i) const { return i < kTreeLds ? pred_s[i] : ld(pred + i); }
-  __device__ __forceinline__ int32_t get_lev(int32_t i) const { return i < kTreeLds ? lev_s[i] : ld(level + i); }
-  __device__ __forceinline__ bool leaf(int32_t i) const { return (i < kTreeLds ? child_s[i] : ld(has_child + i)) == 0; }
-  __device__ __forceinline__ void add(int32_t i, int32_t x, int32_t par, int32_t p, int32_t lev) const {
-    if (i < kTreeLds) {
-      ent_s[i] = x;
-      par_s[i] = int16_t(par);  // par < i < kTreeLds
-      pred_s[i] = p;
-      lev_s[i] = uint8_t(lev);
-      child_s[i] = 0;
-    } else {
-      st(ent + i, x);
-      st(parent + i, par);
-      st(pred + i, p);
-      st(level + i, lev);
-      st(has_child + i, 0);
-    }
-  }
-  __device__ __forceinline__ void set_child(int32_t i) const {
-    if (i < kTreeLds) child_s[i] = 1;
-    else st(has_child + i, 1);
-  }
-};
 
 // ---------------------------------------------------------------------------
 // LDS tiers: one root at a time per workgroup, all state in LDS.
@@ -150,6 +102,11 @@ struct BigTier {
   static constexpr int kWavesPerSimd = 6;
   static constexpr int kPerCu = 3;
 };
+// A level of more than kGiveUp * kCap pairs leaves a tier before its offers
+// (1,000 roots of the 20M-triple power-law graph that no tier can hold: the
+// two tiers took 2.8 + 8.1 ms until their tables were full, 0.06 + 0.09 ms
+// with this and the checks while a table fills).
+constexpr int32_t kGiveUp = 2;
 constexpr int32_t kFreeSlot = -1;
 constexpr uint32_t kNoOffer = 0xFFFFFFFFu;
 
@@ -418,16 +375,34 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kWpe))) void
       total = carry;
       if (t == 0) dpre_s[nlev] = total;
       __syncthreads();
+      // A level of many more pairs than the table holds entities outgrows the
+      // tier (nearly always: only repeats could keep it in): leave at once.
+      if (V > kCap && total > kGiveUp * kCap) {  // uniform
+        overflow = true;
+        break;
+      }
       const bool one_chunk = total <= kChunk;  // uniform: records stay in registers
       const bool last = lev + 1 == a.depth;
       // Offers (tree members hold 0 and ignore them).
+      // Where the level can outgrow the tier, a wave adds what it inserted after
+      // every round and stops once the capacity is passed: the table never
+      // comes near full, where every further offer would probe most of it.
       bool full = false;
       int32_t inserted = 0;
-      for (int32_t c0 = 0; c0 < total && !full; c0 += kChunk) {
+      const int32_t cap = last ? kCap : kTreeCap;
+      const bool may_outgrow = used_s + total > cap;  // uniform: no wave adds before the barrier below otherwise
+      for (int32_t c0 = 0; c0 < total && (!may_outgrow || __ballot(full) == 0); c0 += kChunk) {
         load_chunk(c0);
 #pragma unroll
         for (int k = 0; k < R; ++k) {
           slot_k[k] = -1;
+          if (may_outgrow && (k > 0 || c0 > 0)) {
+            const int32_t sum = wave_sum(inserted);
+            inserted = 0;
+            if (lane_id() == 0 && sum > 0) atomicAdd(&used_s, sum);
+            const int32_t used = __hip_atomic_load(&used_s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            full = __ballot(full || used > cap) != 0;  // the whole wave stops, so the wave sums stay whole
+          }
           if (full || node_k[k] < 0) continue;
           const int32_t x = rec_k[k].y;
           if (uint32_t(x) >= uint32_t(V)) {
@@ -446,7 +421,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kWpe))) void
       inserted = wave_sum(inserted);
       if (lane_id() == 0 && inserted > 0) atomicAdd(&used_s, inserted);
       __syncthreads();
-      if (overflow_s || used_s > (last ? kCap : kTreeCap)) {  // uniform
+      if (overflow_s || used_s > cap) {  // uniform
         overflow = true;
         break;
       }
@@ -509,7 +484,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kWpe))) void
       __syncthreads();
     }
     if (overflow) {
-      if (t == 0) out_queue[atomicAdd(out_count, 1)] = int32_t(r);
+      if (t == 0) {
+        // a level that even the last tier would give up goes to the bitmap pass
+        const bool skip = V > BigTier::kCap && total > kGiveUp * BigTier::kCap;
+        int32_t *q = skip ? a.queue[2] : out_queue;
+        q[atomicAdd(skip ? a.queue_counts + 2 : out_count, 1)] = int32_t(r);
+      }
       continue;  // the clearing loop of the next root starts after this root's last barrier
     }
     // Walk rows: root, then the tokens of `node` and its ancestors up to level h.
@@ -577,187 +557,409 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kWpe))) void
 }
 
 __global__ void bfs_queue_reset_kernel(int32_t *queue_counts) {
-  if (threadIdx.x < 6) queue_counts[threadIdx.x] = 0;
+  if (threadIdx.x < kQueueCounters) queue_counts[threadIdx.x] = 0;
 }
 
 // ---------------------------------------------------------------------------
-// Workspace pass: the roots no tier could hold, with per-workgroup slices of
-// the workspace.
+// Bitmap pass: the roots no tier could hold (in a power-law graph nearly every
+// root that reaches a hub: levels of 10^5 to 10^7 pairs).
+//
+// One workgroup runs a root and takes a level's pairs in order, kWideChunk at
+// a time, so "reached before this chunk" is one bit per entity and an entity
+// belongs to the first pair that reaches it without any per-entity offers:
+//   * filter: every thread loads kWideRounds records and tests their bits; on a
+//     hub's row, where almost all pairs meet entities already reached, a chunk
+//     ends here;
+//   * the candidates left are numbered in pair order and settled kWideThreads
+//     at a time: equal entities meet in an LDS table that keeps the first,
+//     which becomes a node, sets its bit and marks its parent.
+// What bounds it is the latency of a chunk (records, bits, one to five
+// barriers), so the bitmap lives in LDS while it fits (V up to about 1.07M
+// entities; the random bit tests and updates then never leave the CU) and in
+// the workgroup's slice otherwise, and a chunk is as wide as registers allow.
+// Measured on the 20M-triple power-law graph (1M entities, depth 2, 1,000
+// roots of 290K pairs on average and 5M at most): 2.4 ms, the time of the root
+// with most pairs, against 165 ms with 64-bit offers per entity in the
+// workspace (two random accesses at agent scope per pair, 119 workgroups).
+// A slice holds 25 bytes per tree node: entity, parent, predicate, a
+// has-a-child byte, and for the nodes of the level being expanded that have
+// records their position, row start and degree prefix.
+// At the depth limit only the first max_walks nodes are kept (nothing else of
+// them is ever needed). A root with more nodes than a slice holds is queued
+// for a second run of the same kernel with fewer, V-sized slices.
+constexpr int kWideThreads = 1024;
+constexpr int kWideRounds = 8;
+constexpr int32_t kWideChunk = kWideThreads * kWideRounds;
+constexpr int kWideWindow = 1024;  // nodes of a level whose rows and prefix are in LDS at a time
+constexpr int kWideSlots = 2 * kWideThreads;
+constexpr int kWideStreamRow = kWideChunk / 2;  // shortest (rest of a) row that is streamed on its own
 
-__global__ __launch_bounds__(kThreads) void bfs_walks_kernel(const BfsArgs a) {
-  __shared__ int32_t scan_scratch[kThreads / kWave];
-  __shared__ int32_t dpre_s[kLevelLds + 1];  // degree prefix of the current level (small levels)
-  __shared__ int32_t rowlo_s[kLevelLds];     // row start of each of its entities
-  __shared__ int32_t t_ent[kTreeLds];
-  __shared__ int32_t t_pred[kTreeLds];
-  __shared__ int16_t t_par[kTreeLds];
-  __shared__ uint8_t t_lev[kTreeLds];
-  __shared__ uint8_t t_child[kTreeLds];
+// Static LDS of the kernel below, rounded up: what a bitmap in LDS leaves it.
+constexpr size_t kWideStaticLds = 32 << 10;
+
+struct WidePass {
+  const int32_t *in_queue;
+  const int32_t *in_count;
+  int32_t *taken;
+  int32_t *out_queue;  // roots with more than node_cap nodes (none when node_cap >= V)
+  int32_t *out_count;
+  char *slices;
+  size_t slice_bytes;
+  int32_t node_cap;
+};
+
+inline size_t wide_bitmap_bytes(int64_t V) { return align_up(size_t((V + 31) / 32) * 4, 256); }
+// Bytes of a slice of `cap` nodes, and how many nodes a slice of `bytes` holds.
+inline size_t wide_slice_bytes(int64_t cap) { return 6 * align_up(size_t(cap) * 4, 256) + align_up(size_t(cap), 256); }
+inline int64_t wide_slice_nodes(size_t bytes) { return bytes < 8192 ? 0 : int64_t((bytes - 7 * 256) / 25); }
+
+// Ranks, in pair order, the flagged pairs of a chunk whose wave w holds 64 R
+// consecutive pairs, 64 per round (as rank_chunk otherwise; 128 (wave, round)
+// counts, two per lane). One barrier; cnt_s must not be
+// written again before the next one.
+template <int NT, int R>
+__device__ __forceinline__ void rank_wide_chunk(uint32_t mask, int32_t (&rank)[R], int32_t &total, int32_t *cnt_s) {
+  constexpr int W = NT / kWave;
+  static_assert(R * W == 2 * kWave, "two counts per lane");
+  const int lane = lane_id();
+  const int32_t w = wave_index();
+  uint64_t b[R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) b[k] = __ballot((mask >> k) & 1u);
+  if (lane == 0) {
+#pragma unroll
+    for (int k = 0; k < R; ++k) cnt_s[w * R + k] = __popcll(b[k]);
+  }
+  __syncthreads();
+  const int32_t c0 = cnt_s[2 * lane], c1 = cnt_s[2 * lane + 1];
+  const int32_t inc = wave_inclusive_sum(c0 + c1);
+  const int32_t ex0 = inc - c0 - c1, ex1 = inc - c1;  // counts before entries 2*lane and 2*lane + 1
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int32_t idx = w * R + k;
+    const int32_t before = (idx & 1) ? __builtin_amdgcn_readlane(ex1, idx >> 1) : __builtin_amdgcn_readlane(ex0, idx >> 1);
+    rank[k] = before + lanes_below(b[k]);
+  }
+  total = __builtin_amdgcn_readlane(inc, kWave - 1);
+}
+
+template <bool kLdsBits>
+__global__ __launch_bounds__(kWideThreads) void bfs_wide_kernel(const BfsArgs a, const WidePass p) {
+  constexpr int NT = kWideThreads, R = kWideRounds;
+  extern __shared__ __align__(16) uint32_t lds_bits[];  // kLdsBits: one bit per entity
+  __shared__ int32_t scan_scratch[2][2 * kWave];        // alternated between block-wide scans
+  __shared__ uint32_t win_pre[kWideWindow + kWave];  // past the window's nodes: above any pair's number
+  __shared__ int32_t win_lo[kWideWindow];
+  __shared__ uint8_t win_child[kWideWindow];
+  __shared__ int32_t c_ent[NT], c_pred[NT], c_node[NT];  // the candidates being settled
+  __shared__ uint32_t table[kWideSlots];                 // 1 + the first candidate of an entity, 0 if free
+  __shared__ int32_t level_begin[RDF2V_MAX_DEPTH + 2];
+  __shared__ int32_t next_s;
   const int t = threadIdx.x;
   const int32_t V = a.num_entities;
   const uint32_t E = uint32_t(a.num_edges);
   const int64_t width = 2 * int64_t(a.depth) + 1;
   const int2 *edges = reinterpret_cast<const int2 *>(a.edges);
 
-  char *base = a.workspace + size_t(blockIdx.x) * a.slice_bytes;
-  const size_t a4 = align_up(size_t(V) * 4, 256), a8 = align_up(size_t(V) * 8, 256);
-  int32_t *mark = reinterpret_cast<int32_t *>(base);
-  uint64_t *offer = reinterpret_cast<uint64_t *>(base + a4);
-  int32_t *dpre = reinterpret_cast<int32_t *>(base + 6 * a4 + a8);
-  const Tree tree{t_ent,
-                  t_par,
-                  t_pred,
-                  t_lev,
-                  t_child,
-                  reinterpret_cast<int32_t *>(base + a4 + a8),
-                  reinterpret_cast<int32_t *>(base + 2 * a4 + a8),
-                  reinterpret_cast<int32_t *>(base + 3 * a4 + a8),
-                  reinterpret_cast<int32_t *>(base + 4 * a4 + a8),
-                  reinterpret_cast<int32_t *>(base + 5 * a4 + a8)};
-
-  const int32_t queued = a.queue_counts[2];
-  if (int32_t(blockIdx.x) >= queued) return;  // uniform, before any barrier
-  // Each workgroup initialises its own slice once per call.
-  for (int32_t v = t; v < V; v += kThreads) {
-    st(mark + v, -1);
-    __hip_atomic_store(offer + v, ~uint64_t(0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int32_t n_in = *p.in_count;
+  if (int32_t(blockIdx.x) >= n_in) return;  // uniform; an empty queue costs one load per workgroup
+  char *slice = p.slices + size_t(blockIdx.x) * p.slice_bytes;
+  const int64_t bit_words = (int64_t(V) + 31) / 32;
+  uint32_t *bits = lds_bits;
+  if (!kLdsBits) {
+    bits = reinterpret_cast<uint32_t *>(slice);
+    slice += align_up(size_t(bit_words) * 4, 256);
   }
-  __syncthreads();
+  const size_t a4 = align_up(size_t(p.node_cap) * 4, 256);
+  int32_t *ent = reinterpret_cast<int32_t *>(slice);
+  int32_t *parent = reinterpret_cast<int32_t *>(slice + a4);
+  int32_t *pred = reinterpret_cast<int32_t *>(slice + 2 * a4);
+  // of the level being expanded, for its nodes with records: position, row start, degree prefix
+  int32_t *x_node = reinterpret_cast<int32_t *>(slice + 3 * a4);
+  int32_t *x_lo = reinterpret_cast<int32_t *>(slice + 4 * a4);
+  int32_t *x_pre = reinterpret_cast<int32_t *>(slice + 5 * a4);
+  uint8_t *has_child = reinterpret_cast<uint8_t *>(slice + 6 * a4);
 
-  uint32_t stamp = 0xFFFFFFFEu;  // falls by one per (root, level) of this workgroup
+  auto visited = [&](int32_t x) -> bool {
+    const uint32_t w = kLdsBits ? bits[uint32_t(x) >> 5]
+                                : __hip_atomic_load(bits + (uint32_t(x) >> 5), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return (w >> (x & 31)) & 1u;
+  };
+  auto visit = [&](int32_t x) { atomicOr(bits + (uint32_t(x) >> 5), 1u << (x & 31)); };
+
   int flags = 0;
-  for (int32_t k = blockIdx.x; k < queued; k += gridDim.x) {
-    const int64_t r = a.queue[2][k];
-    const int32_t root = a.roots[r];
-    const int32_t mark_id = int32_t(r);
-    if (uint32_t(root) >= uint32_t(V)) {
-      if (t == 0) a.counts[r] = 0;
-      flags |= RDF2V_STATUS_ID_OUT_OF_RANGE;
-      continue;  // uniform: every lane skips the same root
-    }
-    if (t == 0) {
-      tree.add(0, root, -1, -1, 0);
-      st(mark + root, mark_id);
-    }
-    int32_t lb = 0, le = 1;
+  int32_t phase = 0;
+  auto scratch = [&]() -> int32_t * { return scan_scratch[phase ^= 1]; };
+  for (;;) {
+    if (t == 0) next_s = atomicAdd(p.taken, 1);
     __syncthreads();
-    for (int32_t lev = 0; lev < a.depth && lb < le; ++lev) {
-      // Degree prefix of the level's entities (their (entity, record) pairs are
-      // numbered in order), with the row starts, in LDS for small levels.
+    const int32_t k_in = next_s;
+    __syncthreads();
+    if (k_in >= n_in) break;
+    const int64_t r = p.in_queue[k_in];
+    const int32_t root = a.roots[r];  // in range: the tiers queue no other
+    if constexpr (kLdsBits) {
+      for (int64_t i = t; i < (bit_words + 3) / 4; i += NT) reinterpret_cast<uint4 *>(bits)[i] = make_uint4(0, 0, 0, 0);
+    } else {
+      for (int64_t i = t; i < bit_words; i += NT)
+        __hip_atomic_store(bits + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (t == 0) {
+      visit(root);
+      ent[0] = root;
+      parent[0] = -1;
+      pred[0] = -1;
+      has_child[0] = 0;
+      level_begin[0] = 0;
+      level_begin[1] = 1;
+    }
+    __syncthreads();
+    int32_t lb = 0, le = 1;   // the level being expanded: nodes [lb, le)
+    int32_t levels = 1;       // levels with stored begins: level l is [level_begin[l], level_begin[l + 1])
+    int32_t last_wins = 0;    // entities reached at the depth limit, or any number above max_walks (stored from le on)
+    bool overflow = false;
+    for (int32_t lev = 0; lev < a.depth && lb < le && !overflow; ++lev) {
       const int32_t nlev = le - lb;
-      const bool small = nlev <= kLevelLds;  // uniform across the block
-      int32_t carry = 0;
-      for (int32_t c0 = lb; c0 < le; c0 += kThreads) {
+      const bool last = lev + 1 == a.depth;
+      // The level's nodes with records: row start and degree prefix. The pairs
+      // of a level are at most the CSR's records, so their number fits 31 bits
+      // (if rows of an inconsistent CSR overlap it may not: record indices are
+      // checked).
+      int32_t carry = 0, nx = 0;
+      for (int32_t c0 = 0; c0 < nlev; c0 += NT) {
         const int32_t i = c0 + t;
         int32_t d = 0, lo = 0;
-        if (i < le) {
-          const int32_t u = tree.get_ent(i);
+        if (i < nlev) {
+          const int32_t u = ent[lb + i];
           lo = a.row_ptr[u];
           const int32_t hi = a.row_ptr[u + 1];
           if (uint32_t(lo) <= uint32_t(hi) && uint32_t(hi) <= E) d = hi - lo;
           else flags |= RDF2V_STATUS_BAD_CSR;
         }
-        int32_t tot;
-        const int32_t ex = block_exclusive_scan<kThreads>(d, scan_scratch, tot);
-        if (i < le) {
-          if (small) {
-            dpre_s[i - lb] = carry + ex;
-            rowlo_s[i - lb] = lo;
-          } else {
-            st(dpre + (i - lb), carry + ex);
-          }
+        int32_t tot, with_rows;
+        const int32_t ex = block_scan<NT>(d, scratch(), tot);
+        const int32_t at = nx + block_scan<NT>(d > 0 ? 1 : 0, scratch(), with_rows);
+        if (d > 0) {
+          x_node[at] = lb + i;
+          x_lo[at] = lo;
+          x_pre[at] = carry + ex;
         }
         carry += tot;
+        nx += with_rows;
       }
       const int32_t total = carry;
-      if (t == 0) {
-        if (small) dpre_s[nlev] = total;
-        else st(dpre + nlev, total);
-      }
-      // Pair q of the level: the level entity (index lo_i) it belongs to and the
-      // pair's record index.
-      auto locate = [&](int32_t q, int32_t &lo_i, uint32_t &j) {
-        lo_i = 0;
-        int32_t hi_i = nlev;  // largest i with dpre[i] <= q
-        if (small) {
-          while (hi_i - lo_i > 1) {
-            const int32_t mid = (lo_i + hi_i) >> 1;
-            if (dpre_s[mid] <= q) lo_i = mid;
-            else hi_i = mid;
+      int32_t added = 0;  // nodes of the next level so far (at the depth limit: up to max_walks or a batch more)
+      int32_t more = 0;   // whether this thread reached one that was not counted
+      __syncthreads();
+      for (int32_t i0 = 0; i0 < nx && !overflow; i0 += kWideWindow) {
+        // The next kWideWindow of them: their prefix, rows and child marks in LDS.
+        const int32_t nw = min(kWideWindow, nx - i0);
+        if (t < nw) {
+          win_pre[t] = uint32_t(x_pre[i0 + t]);
+          win_lo[t] = x_lo[i0 + t];
+          win_child[t] = 0;
+        } else if (t < kWideWindow) {
+          win_pre[t] = 0xFFFFFFFFu;
+        }
+        if (t < kWave) win_pre[kWideWindow + t] = 0xFFFFFFFFu;
+        const uint32_t q_end = uint32_t(i0 + nw < nx ? x_pre[i0 + nw] : total);
+        __syncthreads();
+        // The window node of pair q (uniform): the largest whose prefix is at
+        // most q, from 64 samples and the 16 entries after the last that is.
+        auto node_of = [&](uint32_t q) -> int32_t {
+          constexpr int kStep = kWideWindow / kWave;
+          const int32_t s = (__popcll(__ballot(win_pre[lane_id() * kStep] <= q)) - 1) * kStep;
+          return s + __popcll(__ballot(lane_id() < kStep && win_pre[s + lane_id() % kStep] <= q)) - 1;
+        };
+        for (uint32_t c0 = win_pre[0]; c0 < q_end;) {
+          const bool marks_only = last && added >= a.max_walks;  // uniform
+          if (marks_only) {
+            // Every walk of the depth limit is known: what is left to learn is
+            // which nodes still reach something new. On one long row that
+            // takes no order, so it streams through without a barrier.
+            const int32_t n = node_of(c0);
+            const uint32_t row_end = min(win_pre[n + 1], q_end);
+            if (row_end - c0 >= uint32_t(kWideStreamRow)) {
+              const uint32_t j0 = uint32_t(win_lo[n]) - win_pre[n];
+              bool any = false;
+              for (uint32_t q0 = c0 + uint32_t(t); q0 < row_end; q0 += kWideChunk) {
+                int32_t x[R];
+#pragma unroll
+                for (int k = 0; k < R; ++k) {
+                  const uint32_t q = q0 + uint32_t(k * NT);
+                  x[k] = -1;
+                  if (q < row_end && j0 + q < E) x[k] = edges[j0 + q].y;
+                  else if (k > 0) x[k] = x[0];
+                }
+#pragma unroll
+                for (int k = 0; k < R; ++k) {
+                  if (uint32_t(x[k]) >= uint32_t(V)) flags |= RDF2V_STATUS_ID_OUT_OF_RANGE;
+                  else if (!visited(x[k])) {
+                    visit(x[k]);
+                    any = true;
+                  }
+                }
+              }
+              if (any) {
+                win_child[n] = 1;
+                more = 1;
+              }
+              c0 = row_end;
+              __syncthreads();
+              continue;
+            }
           }
-          j = uint32_t(rowlo_s[lo_i] + (q - dpre_s[lo_i]));
-        } else {
-          while (hi_i - lo_i > 1) {
-            const int32_t mid = (lo_i + hi_i) >> 1;
-            if (ld(dpre + mid) <= q) lo_i = mid;
-            else hi_i = mid;
+          // Filter: wave w takes pairs c0 + w * 64 R + k * 64 + lane.
+          int32_t node_k[R];
+          int2 rec_k[R];
+          uint32_t mask = 0;
+          const uint32_t first = c0 + uint32_t(wave_index() * kWave * R);
+#pragma unroll
+          for (int k = 0; k < R; ++k) {
+            node_k[k] = -1;
+            rec_k[k] = make_int2(0, -1);
           }
-          const int32_t u = tree.get_ent(lb + lo_i);
-          j = uint32_t(a.row_ptr[u] + (q - ld(dpre + lo_i)));
+          if (first < q_end) {  // uniform
+            int32_t n0 = node_of(first);
+            int32_t n[R];
+#pragma unroll
+            for (int k = 0; k < R; ++k) n[k] = n0;
+            if (win_pre[n0 + 1] < first + kWave * R) {  // uniform: the wave's pairs cross a row's end
+              // Per round, the rows that begin among its 64 pairs (at most 64,
+              // each at a pair of its own) as a mask of those pairs.
+#pragma unroll
+              for (int k = 0; k < R; ++k) {
+                const uint32_t at = win_pre[n0 + 1 + lane_id()] - (first + uint32_t(k * kWave));
+                const uint32_t lo = wave_sum(at < 32u ? 1u << at : 0u);
+                const uint32_t hi = wave_sum(at - 32u < 32u ? 1u << (at - 32u) : 0u);
+                const uint64_t begins = (uint64_t(hi) << 32) | lo;
+                n[k] = min(n0 + lanes_below(begins) + int32_t((begins >> lane_id()) & 1u), nw - 1);
+                n0 = min(n0 + __popcll(begins), nw - 1);
+              }
+            }
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+              const uint32_t q = first + uint32_t(k * kWave + lane_id());
+              const uint32_t j_rec = uint32_t(win_lo[n[k]]) + (q - win_pre[n[k]]);
+              if (q < q_end && j_rec < E) {  // below E in a consistent CSR
+                node_k[k] = n[k];
+                rec_k[k] = edges[j_rec];
+              }
+            }
+          }
+#pragma unroll
+          for (int k = 0; k < R; ++k) {
+            if (node_k[k] < 0) continue;
+            if (uint32_t(rec_k[k].y) >= uint32_t(V)) flags |= RDF2V_STATUS_ID_OUT_OF_RANGE;
+            else if (!visited(rec_k[k].y)) mask |= 1u << k;
+          }
+          int32_t rank[R], cands;
+          rank_wide_chunk<NT, R>(mask, rank, cands, scratch());
+          // Settle the candidates NT at a time, in pair order.
+          for (int32_t base = 0; base < cands && !overflow; base += NT) {
+            for (int i = t; i < kWideSlots; i += NT) table[i] = 0;
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+              const int32_t at = rank[k] - base;
+              if (((mask >> k) & 1u) && at >= 0 && at < NT) {
+                c_ent[at] = rec_k[k].y;
+                c_pred[at] = rec_k[k].x;
+                c_node[at] = node_k[k];
+              }
+            }
+            __syncthreads();
+            const int32_t n_batch = min(cands - base, NT);
+            int32_t slot = -1, x = 0;
+            if (t < n_batch) {
+              x = c_ent[t];
+              // an earlier batch of this chunk may have reached it since
+              if (base == 0 || !visited(x)) {
+                slot = entity_slot<11>(x);
+                static_assert(kWideSlots == 1 << 11, "entity_slot's table size");
+                for (;;) {  // ends: the table has twice as many slots as candidates
+                  const uint32_t cur = atomicCAS(&table[slot], 0u, uint32_t(t) + 1u);
+                  if (cur == 0u) break;
+                  if (c_ent[cur - 1] == x) {
+                    atomicMin(&table[slot], uint32_t(t) + 1u);
+                    break;
+                  }
+                  slot = (slot + 1) & (kWideSlots - 1);
+                }
+              }
+            }
+            __syncthreads();
+            const bool win = slot >= 0 && table[slot] == uint32_t(t) + 1u;
+            int32_t ex = 0, tot = 0, keep = 0;  // keep: nodes to store
+            if (!marks_only) {
+              ex = block_scan<NT>(win ? 1 : 0, scratch(), tot);
+              keep = last ? min(tot, max(0, a.max_walks - added)) : tot;
+            }
+            if (keep > 0 && int64_t(le) + added + keep > p.node_cap) {  // uniform
+              overflow = true;
+            } else if (win) {
+              visit(x);
+              win_child[c_node[t]] = 1;
+              if (marks_only) more = 1;
+              if (ex < keep) {
+                const int32_t pos = le + added + ex;
+                ent[pos] = x;
+                parent[pos] = x_node[i0 + c_node[t]];
+                pred[pos] = c_pred[t];
+                has_child[pos] = 0;
+              }
+            }
+            added += tot;
+            __syncthreads();
+          }
+          if (overflow) break;
+          c0 += kWideChunk;
         }
-      };
-      --stamp;
-      const uint64_t hi_bits = uint64_t(stamp) << 32;
-      __syncthreads();
-      // Offers: pair q reaches x; entities already in this root's tree are skipped.
-      for (int32_t q = t; q < total; q += kThreads) {
-        int32_t lo_i;
-        uint32_t j;
-        locate(q, lo_i, j);
-        const int32_t x = edges[j].y;
-        if (uint32_t(x) >= uint32_t(V)) {
-          flags |= RDF2V_STATUS_ID_OUT_OF_RANGE;
-          continue;
-        }
-        if (ld(mark + x) != mark_id) atomicMin(reinterpret_cast<unsigned long long *>(offer + x),
-                                               (unsigned long long)(hi_bits | uint32_t(q)));
+        if (t < nw && win_child[t]) has_child[x_node[i0 + t]] = 1;
+        __syncthreads();
       }
-      __syncthreads();
-      // Winners in q order become the next level.
-      int32_t added = 0;
-      for (int32_t c0 = 0; c0 < total; c0 += kThreads) {
-        const int32_t q = c0 + t;
-        int32_t win = 0, x = 0, p = 0, node = 0;
-        if (q < total) {
-          int32_t lo_i;
-          uint32_t j;
-          locate(q, lo_i, j);
-          node = lb + lo_i;
-          const int2 rec = edges[j];
-          p = rec.x;
-          x = rec.y;
-          if (uint32_t(x) < uint32_t(V)) win = ld64(offer + x) == (hi_bits | uint32_t(q));
+      if (overflow) break;
+      if (last) {
+        last_wins = added;
+        if (added >= a.max_walks && __syncthreads_or(more)) last_wins = max(added, a.max_walks + 1);
+      } else {
+        lb = le;
+        le += added;
+        if (added > 0) {
+          ++levels;
+          if (t == 0) level_begin[levels] = le;
         }
-        int32_t tot;
-        const int32_t ex = block_exclusive_scan<kThreads>(win, scan_scratch, tot);
-        if (win) {
-          const int32_t pos = le + added + ex;
-          tree.add(pos, x, node, p, lev + 1);
-          tree.set_child(node);
-          st(mark + x, mark_id);
-        }
-        added += tot;
+        __syncthreads();
       }
-      lb = le;
-      le += added;
-      __syncthreads();
     }
-    // Leaves in the order reached: the first max_walks become walks.
+    if (overflow) {
+      if (t == 0 && p.out_queue != nullptr) p.out_queue[atomicAdd(p.out_count, 1)] = int32_t(r);
+      __syncthreads();
+      continue;
+    }
+    // Walks: the leaves among the stored levels in the order reached, then the
+    // entities at the depth limit.
     int32_t leaves = 0;
-    for (int32_t c0 = 0; c0 < le; c0 += kThreads) {
+    const int32_t kept_last = min(last_wins, a.max_walks);
+    for (int32_t c0 = 0; c0 < le + kept_last && leaves <= a.max_walks; c0 += NT) {
       const int32_t i = c0 + t;
-      const int32_t leaf = i < le ? int32_t(tree.leaf(i)) : 0;
+      const bool deep = i >= le;  // at the depth limit
+      const int32_t leaf = i < le + kept_last ? int32_t(deep || has_child[i] == 0) : 0;
       int32_t tot;
-      const int32_t ex = block_exclusive_scan<kThreads>(leaf, scan_scratch, tot);
+      const int32_t ex = block_scan<NT>(leaf, scratch(), tot);
       const int32_t idx = leaves + ex;
       if (leaf && idx < a.max_walks) {
-        const int32_t h = tree.get_lev(i);
+        int32_t h = a.depth;
+        if (!deep) {
+          h = 0;
+          while (h + 1 < levels && level_begin[h + 1] <= i) ++h;
+        }
         int32_t *row = a.tokens + (r * a.max_walks + idx) * width;
         int32_t node = i;
         for (int32_t step = h; step >= 1; --step) {
-          row[2 * step] = tree.get_ent(node);
-          row[2 * step - 1] = V + tree.get_pred(node);
-          node = tree.get_par(node);
+          row[2 * step] = ent[node];
+          row[2 * step - 1] = V + pred[node];
+          node = parent[node];
         }
         row[0] = root;
         for (int64_t j = 2 * int64_t(h) + 1; j < width; ++j) row[j] = -1;
@@ -765,9 +967,11 @@ __global__ __launch_bounds__(kThreads) void bfs_walks_kernel(const BfsArgs a) {
       }
       leaves += tot;
     }
+    // `leaves` now counts every walk, or more than max_walks; entities at the
+    // depth limit beyond those kept make the root over-full as well.
     if (t == 0) {
       a.counts[r] = min(leaves, a.max_walks);
-      if (leaves > a.max_walks) flags |= RDF2V_STATUS_CAPACITY;
+      if (leaves > a.max_walks || last_wins > kept_last) flags |= RDF2V_STATUS_CAPACITY;
     }
     __syncthreads();
   }
@@ -807,8 +1011,7 @@ int bfs_first_tier(int32_t num_entities, int64_t num_edges, int64_t num_roots, i
   return first;
 }
 
-int64_t bfs_walks_grid(int32_t num_entities, int64_t num_roots) {
-  // Workspace pass: enough workgroups to fill the chip, at most ~4 GiB of slices.
+int64_t bfs_workspace_units(int32_t num_entities, int64_t num_roots) {
   const int64_t per = int64_t(slice_bytes(num_entities));
   int64_t g = std::max<int64_t>(1, (int64_t(1) << 32) / std::max<int64_t>(per, 1));
   g = std::min<int64_t>(g, 2048);
@@ -817,7 +1020,55 @@ int64_t bfs_walks_grid(int32_t num_entities, int64_t num_roots) {
 }
 
 size_t bfs_walks_workspace_bytes(int32_t num_entities, int64_t num_roots) {
-  return queue_bytes(num_roots) + size_t(bfs_walks_grid(num_entities, num_roots)) * slice_bytes(num_entities);
+  return queue_bytes(num_roots) + size_t(bfs_workspace_units(num_entities, num_roots)) * slice_bytes(num_entities);
+}
+
+// The bitmap pass over queue 2 (an empty queue costs one load per workgroup).
+// As many workgroups as the chip can hold, each with an equal slice of the
+// workspace; slices smaller than V nodes send the roots that outgrow them to a
+// second run with slices of V nodes (at least one fits: 36 bytes per entity
+// against 25 and a bit).
+rdf2v_status launch_wide(const BfsArgs &a, char *slices, size_t bytes, hipStream_t stream) {
+  const int64_t V = a.num_entities;
+  int lds = 0, cus = 0, dev = 0;
+  RDF2V_HIP_TRY(hipGetDevice(&dev));
+  RDF2V_HIP_TRY(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+  RDF2V_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+  const size_t bitmap = wide_bitmap_bytes(V);
+  const bool in_lds = bitmap + kWideStaticLds <= size_t(lds);
+  const size_t head = in_lds ? 0 : bitmap;  // bytes of a slice before its nodes
+  auto run = [&](WidePass p, int64_t groups) -> rdf2v_status {
+    const dim3 grid{unsigned(groups)}, block{kWideThreads};
+    if (in_lds) bfs_wide_kernel<true><<<grid, block, bitmap, stream>>>(a, p);
+    else bfs_wide_kernel<false><<<grid, block, 0, stream>>>(a, p);
+    RDF2V_LAUNCH_CHECK();
+    return RDF2V_OK;
+  };
+  const int64_t per_cu = in_lds && 2 * (bitmap + kWideStaticLds) > size_t(lds) ? 1 : 2;
+  int64_t groups = std::min<int64_t>(a.num_roots, std::max(1, cus) * per_cu);
+  // at least 64K nodes (or V of them) per slice
+  const size_t least = head + wide_slice_bytes(std::min<int64_t>(V, 65536));
+  groups = std::max<int64_t>(1, std::min<int64_t>(groups, int64_t(bytes / least)));
+  WidePass p;
+  p.in_queue = a.queue[2];
+  p.in_count = a.queue_counts + 2;
+  p.taken = a.queue_counts + kWideTaken;
+  p.slices = slices;
+  p.slice_bytes = bytes / size_t(groups) / 256 * 256;
+  p.node_cap = int32_t(std::min<int64_t>(V, wide_slice_nodes(p.slice_bytes - head)));
+  const bool all_fit = p.node_cap >= V;
+  p.out_queue = all_fit ? nullptr : a.queue[0];
+  p.out_count = all_fit ? nullptr : a.queue_counts + kWide2Length;
+  const rdf2v_status st = run(p, groups);
+  if (st != RDF2V_OK || all_fit) return st;
+  p.in_queue = a.queue[0];
+  p.in_count = a.queue_counts + kWide2Length;
+  p.taken = a.queue_counts + kWide2Taken;
+  p.slice_bytes = head + wide_slice_bytes(V);
+  p.node_cap = int32_t(V);
+  p.out_queue = p.out_count = nullptr;
+  groups = std::max<int64_t>(1, std::min<int64_t>(groups, int64_t(bytes / p.slice_bytes)));
+  return run(p, groups);
 }
 
 rdf2v_status launch_bfs_walks(const int32_t *row_ptr, const int32_t *edges, int64_t num_edges,
@@ -837,8 +1088,6 @@ rdf2v_status launch_bfs_walks(const int32_t *row_ptr, const int32_t *edges, int6
   a.status = status_dev;
   a.queue_counts = reinterpret_cast<int32_t *>(ws);
   for (int i = 0; i < 3; ++i) a.queue[i] = reinterpret_cast<int32_t *>(ws + 256 + i * align_up(size_t(num_roots) * 4, 256));
-  a.workspace = ws + queue_bytes(num_roots);
-  a.slice_bytes = slice_bytes(num_entities);
   a.num_roots = num_roots;
   a.num_edges = num_edges;
   a.num_entities = num_entities;
@@ -862,10 +1111,8 @@ rdf2v_status launch_bfs_walks(const int32_t *row_ptr, const int32_t *edges, int6
     else launch_tier<BigTier>(a, in_q, in_c, taken, a.queue[2], a.queue_counts + 2, grid, stream);
     RDF2V_LAUNCH_CHECK();
   }
-  const int64_t grid2 = bfs_walks_grid(num_entities, num_roots);
-  bfs_walks_kernel<<<dim3(unsigned(grid2)), dim3(kThreads), 0, stream>>>(a);
-  RDF2V_LAUNCH_CHECK();
-  return RDF2V_OK;
+  return launch_wide(a, ws + queue_bytes(num_roots),
+                     size_t(bfs_workspace_units(num_entities, num_roots)) * slice_bytes(num_entities), stream);
 }
 
 }  // namespace rdf2v

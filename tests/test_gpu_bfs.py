@@ -216,3 +216,33 @@ def test_inconsistent_csr_is_flagged_not_read():
         torch.cuda.synchronize()
         assert int(st.item()) & rd.RDF2V_STATUS_BAD_CSR, roots
         assert bool((cnt >= 0).all()) and bool((cnt <= 8).all())
+
+
+@pytest.mark.parametrize("V,fan,depth,max_walks", [
+    (30_000, 9_000, 2, 64),          # a row long enough to be streamed once the walks are known
+    (30_000, 9_000, 3, 40_000),      # every walk kept: levels of many row windows, in order
+    (1_000_000, 60_000, 2, 300),     # the largest bitmaps that fit LDS
+    (1_300_000, 60_000, 3, 300),     # bitmap in the workspace
+    (1_300_000, 420_000, 2, 300),    # more tree nodes than a slice of 512 holds: rerun with larger slices
+])
+def test_trees_beyond_the_lds_tiers(V, fan, depth, max_walks):
+    say(f"[bfs] hub trees V={V} fan={fan} depth={depth}")
+    P = 9
+    rng = np.random.default_rng(V + fan + depth)
+    ids = rng.permutation(V).astype(np.int32)
+    root, hub, rest = ids[0], ids[1], ids[2:]
+    hub_row = rng.choice(rest, 3 * fan if 3 * fan < V else fan).astype(np.int32)  # with repeats
+    n_more = min(V, 50_000)
+    s = np.concatenate([np.full(fan, root), np.full(len(hub_row), hub), rng.choice(rest[:fan], n_more)])
+    o = np.concatenate([rest[:fan], hub_row, rng.choice(ids, n_more)])
+    s = np.concatenate([s, rest[:3], rest[fan // 2:fan // 2 + 2]]).astype(np.int32)  # ways into the hub
+    o = np.concatenate([o, np.full(5, hub)]).astype(np.int32)
+    order = rng.permutation(len(s))
+    s, o = s[order], o[order]
+    p = rng.integers(0, P, len(s)).astype(np.int32)
+    rp, ed = oracle.build_csr(s, p, o, V, P)
+    csr = gpu_csr(s, p, o, V, P)
+    many = rest[-560:] if max_walks < 1000 else rest[-20:]
+    roots = np.concatenate([[root, hub, rest[0], root], many, rest[fan // 2:fan // 2 + 1]]).astype(np.int32)
+    counts = _compare(csr, rp, ed, V, P, roots, depth, max_walks, "hub trees")
+    assert counts.max() > 60
