@@ -3,22 +3,34 @@
 // The CSR's rows must keep the triples' input order (a stable sort by subject),
 // so that walk parity is exact and independent of scheduling. Atomics cannot
 // give that order; an LSD radix sort on the subject id can, because every pass
-// is a stable counting sort on one digit. Each pass runs three kernels:
-//   1. radix_count:   per 4096-triple tile, a histogram of the pass's digit
+// is a stable counting sort on one digit. A pass is two or three launches:
+//   1. radix_count:   per tile of up to 8,192 triples, a histogram of the pass's digit
 //                     (LDS atomics), written digit-major to a count table;
-//   2. scan:          exclusive scan of that table (reduce, scan of block
-//                     sums, apply) -> the global start of (digit, tile);
+//   2. row_scan:      exclusive scan of each digit's row of that table (one
+//                     workgroup per digit) and the digit's total;
 //   3. radix_scatter: per tile, the stable rank of every triple among the
 //                     tile's triples with the same digit (wave ballots give the
 //                     lanes sharing a digit, per-wave LDS counters carry the
 //                     count across rounds), a local reorder through LDS, then
 //                     writes of runs of equal digits to their global slots.
-// The first pass also checks every id range. After the last pass the sorted
-// subjects give row_ptr[v] = (number of subjects < v) by binary search, so no
-// kernel needs global atomics (power-law hubs would serialise them).
+// The first pass also checks every id range. row_ptr comes from one pass over
+// the sorted subjects, so no kernel needs global atomics (power-law hubs would
+// serialise them). Up to one tile of triples over few entities is sorted by a
+// single workgroup in one launch (csr_small_kernel).
+//
+// What bounds a pass is HBM traffic (12 B read and written per triple), so the
+// sort takes as few passes as possible: digits of up to 10 bits, against a
+// tile of 8,192 triples that keeps the runs of a 1,024-bin pass at 8 triples.
+// The last pass sorts by the top digit, whose value follows from the position,
+// so it writes only the low 16 bits of the subjects (or none if there are no
+// lower bits).
 //
 // Workspace: two key buffers (4 B/triple each), one payload buffer (8 B/triple;
-// edges_out is the other), the count table and the scan's block sums.
+// edges_out is the other), the count table and the digit totals. The wide
+// tables of the first and the last pass lie in parts of the key buffers those
+// passes leave free.
+
+#include <algorithm>
 
 #include "common.hpp"
 #include "launch.hpp"
@@ -27,51 +39,49 @@
 namespace rdf2v {
 namespace {
 
-constexpr int kSortThreads = 512;
-constexpr int kSortItems = 8;
-constexpr int kTile = kSortThreads * kSortItems;     // triples per tile
-constexpr int kMaxDigitBits = 9;
+typedef int32_t v2i32 __attribute__((ext_vector_type(2)));
+
+// A tile is kSortThreads triples per round and kRounds rounds (2, 4 or 8; the
+// plan picks one): wave w of its workgroup owns kRounds * 64 consecutive
+// triples, taken 64 a round.
+constexpr int kSortThreads = 1024;
+constexpr int kMostRounds = 8;
+constexpr int kMostTile = kSortThreads * kMostRounds;
+constexpr int kMaxDigitBits = 10;
 constexpr int kMaxBins = 1 << kMaxDigitBits;
 constexpr int kTileWaves = kSortThreads / kWave;
-constexpr int kWaveItems = kTile / kTileWaves;       // consecutive triples per wave
-constexpr int kRounds = kWaveItems / kWave;          // rounds of 64 per wave
-
-constexpr int kScanThreads = 256;
-constexpr int kScanItems = 16;
-constexpr int kScanTile = kScanThreads * kScanItems;
 
 static_assert(kMaxBins <= kSortThreads, "one thread per digit in the tile prefix step");
+static_assert(kMostTile <= 65535, "positions inside a tile are kept in 16 bits");
+
+inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+// Entries per digit in the count table: the tiles, padded so that a row starts 16-byte aligned.
+__host__ __device__ inline int64_t row_stride(int64_t tiles) { return (tiles + 3) / 4 * 4; }
 
 // ---------------------------------------------------------------------------
 // Radix pass, step 1: per-tile digit histogram (+ subject id validation on
 // pass 0; the first scatter, which reads predicates and objects anyway,
-// validates those).
+// validates those). Pass 0 also marks every row_ptr entry as not yet known.
 // ---------------------------------------------------------------------------
 // Each thread reads kCountItems keys as 16-byte vectors (all loads issued
-// before any histogram update) and counts them in its wave's own LDS
-// histogram, so lanes of different waves never contend for a bin.
+// before any histogram update) and counts them in LDS.
 constexpr int kCountThreads = 256;
-constexpr int kCountWaves = kCountThreads / kWave;
-constexpr int kCountItems = kTile / kCountThreads;  // keys per thread
 
-template <bool kValidate>
+template <bool kFirst, int kRounds>
 __global__ __launch_bounds__(kCountThreads) void radix_count_kernel(
     const uint32_t *__restrict__ keys, int64_t n, int shift, int bits, int32_t num_entities,
-    int32_t *__restrict__ counts, int64_t tiles, int32_t *status) {
-  __shared__ int hist[kCountWaves * kMaxBins];
+    int32_t *__restrict__ counts, int64_t tiles, int32_t *__restrict__ row_ptr, int32_t *status) {
+  __shared__ int hist[kMaxBins];
+  constexpr int kTile = kSortThreads * kRounds;
+  constexpr int kCountItems = kTile / kCountThreads;  // keys per thread
   constexpr int kVec = 4;
   constexpr int kLoads = kCountItems / kVec;
   const int bins = 1 << bits;
   const uint32_t mask = uint32_t(bins - 1);
-  const int wave = threadIdx.x / kWave;
-  for (int i = threadIdx.x; i < kCountWaves * bins; i += kCountThreads) hist[i] = 0;
-  __syncthreads();
-  int *wave_hist = hist + wave * bins;
   const int64_t tile = xcd_tile(blockIdx.x, tiles);
   const int64_t base = tile * kTile;
   const bool full = base + kTile <= n && (reinterpret_cast<uintptr_t>(keys) & 15) == 0;
   uint32_t k[kCountItems];
-  int bad = 0;
   if (full) {
     // 16-byte loads: vector v of the tile holds keys 4v .. 4v+3.
     const uint4 *k4 = reinterpret_cast<const uint4 *>(keys + base);
@@ -80,7 +90,17 @@ __global__ __launch_bounds__(kCountThreads) void radix_count_kernel(
       const uint4 v = k4[i * kCountThreads + threadIdx.x];
       k[kVec * i + 0] = v.x; k[kVec * i + 1] = v.y; k[kVec * i + 2] = v.z; k[kVec * i + 3] = v.w;
     }
-    if (kValidate) {
+  }
+  for (int i = threadIdx.x; i < bins; i += kCountThreads) hist[i] = 0;
+  if (kFirst && row_ptr != nullptr) {
+    const int64_t nv = int64_t(num_entities) + 1;
+    for (int64_t v = int64_t(blockIdx.x) * kCountThreads + threadIdx.x; v < nv; v += int64_t(gridDim.x) * kCountThreads)
+      row_ptr[v] = -1;
+  }
+  __syncthreads();
+  int bad = 0;
+  if (full) {
+    if (kFirst) {
 #pragma unroll
       for (int i = 0; i < kCountItems; ++i) bad |= k[i] >= uint32_t(num_entities);
     }
@@ -95,52 +115,188 @@ __global__ __launch_bounds__(kCountThreads) void radix_count_kernel(
       const uint32_t d0 = __builtin_amdgcn_readfirstlane(d);
       const uint64_t same = __ballot(d == d0);
       if (d != d0)
-        atomicAdd(&wave_hist[d], 1);
+        atomicAdd(&hist[d], 1);
       else if (lane == 0)
-        atomicAdd(&wave_hist[d0], __popcll(same));
+        atomicAdd(&hist[d0], __popcll(same));
     }
   } else {
     // ragged last tile or unaligned input: scalar loads of the same items
-#pragma unroll
     for (int i = 0; i < kCountItems; ++i) {
       const int64_t idx = base + int64_t(i / kVec) * (kCountThreads * kVec) + threadIdx.x * kVec + (i % kVec);
       if (idx < n) {
         const uint32_t key = keys[idx];
-        atomicAdd(&wave_hist[(key >> shift) & mask], 1);
-        if (kValidate) bad |= key >= uint32_t(num_entities);
+        atomicAdd(&hist[(key >> shift) & mask], 1);
+        if (kFirst) bad |= key >= uint32_t(num_entities);
       }
     }
   }
-  if (kValidate) {
+  if (kFirst) {
     if (__syncthreads_or(bad) && threadIdx.x == 0 && status != nullptr)
       atomicOr(status, RDF2V_STATUS_ID_OUT_OF_RANGE);
   } else {
     __syncthreads();
   }
-  for (int d = threadIdx.x; d < bins; d += kCountThreads) {
-    int c = 0;
+  const int64_t stride = row_stride(tiles);
+  for (int d = threadIdx.x; d < bins; d += kCountThreads) counts[int64_t(d) * stride + tile] = hist[d];
+}
+
+// ---------------------------------------------------------------------------
+// Radix pass, step 2: workgroup d scans digit d's counts over the tiles, in
+// place, and writes the digit's total. (The scatter's workgroups add the
+// totals of the lower digits themselves.)
+// ---------------------------------------------------------------------------
+constexpr int kScanThreads = 256;
+constexpr int kScanItems = 16;
+constexpr int kScanTile = kScanThreads * kScanItems;
+
+__global__ __launch_bounds__(kScanThreads) void row_scan_kernel(int32_t *__restrict__ counts, int64_t tiles,
+                                                                int32_t *__restrict__ totals) {
+  __shared__ int scratch[kScanThreads / kWave];
+  int32_t *row = counts + int64_t(blockIdx.x) * row_stride(tiles);
+  int carry = 0;
+  for (int64_t base = 0; base < tiles; base += kScanTile) {
+    const int64_t i0 = base + int64_t(threadIdx.x) * kScanItems;
+    int v[kScanItems];
 #pragma unroll
-    for (int w = 0; w < kCountWaves; ++w) c += hist[w * bins + d];
-    counts[int64_t(d) * tiles + tile] = c;
+    for (int k = 0; k < kScanItems; k += 4) {
+      int4 x = make_int4(0, 0, 0, 0);
+      if (i0 + k < tiles) x = *reinterpret_cast<const int4 *>(row + i0 + k);  // rows are padded to 4
+      v[k] = x.x; v[k + 1] = x.y; v[k + 2] = x.z; v[k + 3] = x.w;
+    }
+    int sum = 0;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) sum += i0 + k < tiles ? v[k] : 0;
+    int tot;
+    int ex = carry + block_exclusive_scan<kScanThreads>(sum, scratch, tot);
+#pragma unroll
+    for (int k = 0; k < kScanItems; k += 4) {
+      int4 x;
+      x.x = ex; ex += v[k];
+      x.y = ex; ex += v[k + 1];
+      x.z = ex; ex += v[k + 2];
+      x.w = ex; ex += v[k + 3];
+      if (i0 + k < tiles) *reinterpret_cast<int4 *>(row + i0 + k) = x;
+    }
+    carry += tot;
   }
+  if (threadIdx.x == 0) totals[blockIdx.x] = carry;
 }
 
 // ---------------------------------------------------------------------------
 // Radix pass, step 3: stable scatter of one tile.
 // ---------------------------------------------------------------------------
-template <bool kFirst>
-__global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
+
+// Exclusive scan over the block of two int32 values per thread at once.
+template <int NT>
+__device__ __forceinline__ int2 block_exclusive_scan2(int2 x, int2 *scratch) {
+  constexpr int kWaves = NT / kWave;
+  const int lane = lane_id();
+  const int wave = threadIdx.x / kWave;
+  int2 v = x;
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int a = __shfl_up(v.x, off, kWave), b = __shfl_up(v.y, off, kWave);
+    if (lane >= off) {
+      v.x += a;
+      v.y += b;
+    }
+  }
+  if (lane == kWave - 1) scratch[wave] = v;
+  __syncthreads();
+  // sums of the waves before: one wave total per lane, added over the lanes below `wave`
+  int2 before = lane < wave ? scratch[lane] : make_int2(0, 0);
+#pragma unroll
+  for (int off = 1; off < kWaves; off <<= 1) {
+    before.x += __shfl_xor(before.x, off, kWave);
+    before.y += __shfl_xor(before.y, off, kWave);
+  }
+  before.x = __builtin_amdgcn_readfirstlane(before.x);
+  before.y = __builtin_amdgcn_readfirstlane(before.y);
+  return make_int2(before.x + v.x - x.x, before.y + v.y - x.y);
+}
+
+// Position of each of the thread's items (item r of wave w: (w * kRounds + r)
+// * 64 + lane) in the tile's stable order by the digit (key >> shift) & (bins
+// - 1), and for thread d < bins the tile-local start of digit d (x) and the sum
+// of `total` over the lower digits (y). kBits >= the digit's bits.
+// wave_count: kTileWaves * bins counters, zeroed here; they and digit_start
+// (one per digit) are free again after the barrier that the caller puts behind
+// the call.
+template <int kBits, int kRounds>
+__device__ __forceinline__ int2 tile_positions(const uint32_t (&key)[kRounds], int tile_n, int shift, int bins,
+                                               int total, uint16_t *wave_count, int *digit_start, int2 *scratch,
+                                               uint32_t (&pos)[kRounds]) {
+  const uint32_t mask = uint32_t(bins - 1);
+  const int lane = lane_id();
+  const int wave = threadIdx.x / kWave;
+  for (int i = threadIdx.x; i < kTileWaves * bins / 2; i += kSortThreads) reinterpret_cast<uint32_t *>(wave_count)[i] = 0;
+  __syncthreads();
+  uint16_t *mine = wave_count + wave * bins;
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    const bool valid = (wave * kRounds + r) * kWave + lane < tile_n;
+    const uint32_t d = (key[r] >> shift) & mask;
+    const uint32_t before = valid ? mine[d] : 0;
+    // Lanes of this round holding the same digit: per bit, the lanes whose bit
+    // is the lane's own (in halves: four instructions a bit).
+    const uint64_t all = __ballot(valid);
+    uint32_t lo = uint32_t(all), hi = uint32_t(all >> 32);
+#pragma unroll
+    for (int b = 0; b < kBits; ++b) {
+      const uint32_t own = uint32_t(int32_t(d << (31 - b)) >> 31);  // the lane's bit in every position
+      const uint64_t m = __ballot(own != 0);
+      lo &= ~(uint32_t(m) ^ own);
+      hi &= ~(uint32_t(m >> 32) ^ own);
+    }
+    const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+    pos[r] = before + below;
+    // The lowest lane of each digit group advances the wave's counter; its
+    // store depends on the load above, so every lane's load precedes it.
+    if (valid && below == 0) mine[d] = uint16_t(before + __popc(lo) + __popc(hi));
+    __builtin_amdgcn_sched_barrier(0);  // one round's masks in registers at a time
+  }
+  __syncthreads();
+  // Tile-local start of every (wave, digit) run.
+  const int d = threadIdx.x;
+  int sum = 0;
+  if (d < bins) {
+#pragma unroll
+    for (int w = 0; w < kTileWaves; ++w) {  // counts -> starts within the digit
+      const int c = wave_count[w * bins + d];
+      wave_count[w * bins + d] = uint16_t(sum);
+      sum += c;
+    }
+  }
+  const int2 start = block_exclusive_scan2<kSortThreads>(make_int2(sum, total), scratch);
+  if (d < bins) digit_start[d] = start.x;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    // min: always inside the tile; keeps a logic slip from leaving the tile
+    const uint32_t dr = (key[r] >> shift) & mask;
+    pos[r] = min(uint32_t(digit_start[dr]) + mine[dr] + pos[r], uint32_t(kSortThreads * kRounds - 1));
+  }
+  return start;
+}
+
+// Bytes of LDS that the counters, the keys and the payloads of a tile use in turn.
+template <int kRounds>
+constexpr int kStageBytes = kSortThreads * kRounds * 8 > kTileWaves * kMaxBins * 2 ? kSortThreads * kRounds * 8
+                                                                                   : kTileWaves * kMaxBins * 2;
+
+// kKeyOut: how the pass writes its keys: 4 B each, their low 16 bits (the last
+// pass: keys_out is then a uint16_t array), or not at all (0).
+template <bool kFirst, int kKeyOut, int kBits, int kRounds>
+__global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(8))) void radix_scatter_kernel(
     const uint32_t *__restrict__ keys_in, const int2 *__restrict__ pay_in,
     const int32_t *__restrict__ pred_in, const int32_t *__restrict__ obj_in,
-    uint32_t *__restrict__ keys_out, int2 *__restrict__ pay_out, int64_t n, int shift, int bits,
-    const int32_t *__restrict__ offsets, int64_t tiles, int32_t num_entities, int32_t num_predicates,
-    int32_t *status) {
-  __shared__ int wave_count[kTileWaves][kMaxBins];
-  __shared__ int global_minus_local[kMaxBins];
-  __shared__ uint32_t s_keys[kTile];
-  __shared__ int2 s_pay[kTile];
-  __shared__ int scan_scratch[kSortThreads / kWave];
-
+    void *__restrict__ keys_out, int2 *__restrict__ pay_out, int64_t n, int shift, int bits,
+    const int32_t *__restrict__ offsets, const int32_t *__restrict__ totals, int32_t *__restrict__ bases_out,
+    int64_t tiles, int32_t num_entities, int32_t num_predicates, int32_t *status) {
+  constexpr int kTile = kSortThreads * kRounds;
+  __shared__ __align__(16) char stage[kStageBytes<kRounds>];
+  __shared__ int digit_start[kMaxBins];
+  __shared__ int2 scan_scratch[kSortThreads / kWave];
   const int bins = 1 << bits;
   const uint32_t mask = uint32_t(bins - 1);
   const int lane = lane_id();
@@ -149,30 +305,66 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
   const int64_t base = tile * kTile;
   const int tile_n = int(min(int64_t(kTile), n - base));
 
-  for (int i = threadIdx.x; i < kTileWaves * kMaxBins; i += kSortThreads) (&wave_count[0][0])[i] = 0;
-  __syncthreads();
-
-  // Thread d's global start of digit d in this tile, issued with the tile's loads
-  // below so that it is not waited for on its own after the ranking barrier.
-  const int32_t digit_global = threadIdx.x < bins ? offsets[int64_t(threadIdx.x) * tiles + tile] : 0;
-
-  // Wave `wave` owns tile items [wave*kWaveItems, (wave+1)*kWaveItems), visited in order.
-  // All of the wave's loads are issued before any ranking, so they are in
-  // flight together.
+  // The wave's keys are loaded together, with thread d's start of digit d among
+  // the tiles and the digit's total; its payloads after the ranking (64
+  // registers hold no more), in flight while the keys are written.
   uint32_t key[kRounds];
-  int2 pay[kRounds];
-  int rank[kRounds];
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {
-    const int local = wave * kWaveItems + r * kWave + lane;
-    const int64_t idx = base + local;
-    key[r] = 0;
+    const int local = (wave * kRounds + r) * kWave + lane;
+    key[r] = local < tile_n ? __builtin_nontemporal_load(keys_in + base + local) : 0;
+  }
+  const int32_t digit_offset = threadIdx.x < bins ? offsets[int64_t(threadIdx.x) * row_stride(tiles) + tile] : 0;
+  const int32_t digit_total = threadIdx.x < bins ? totals[threadIdx.x] : 0;
+
+  uint32_t pos[kRounds];
+  const int2 start = tile_positions<kBits, kRounds>(key, tile_n, shift, bins, digit_total,
+                                           reinterpret_cast<uint16_t *>(stage), digit_start, scan_scratch, pos);
+  int2 pay[kRounds];
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    const int local = (wave * kRounds + r) * kWave + lane;
     pay[r] = make_int2(0, 0);
     if (local < tile_n) {
-      key[r] = keys_in[idx];
-      pay[r] = kFirst ? make_int2(pred_in[idx], obj_in[idx]) : pay_in[idx];
+      if (kFirst) {
+        pay[r] = make_int2(__builtin_nontemporal_load(pred_in + base + local), __builtin_nontemporal_load(obj_in + base + local));
+      } else {
+        const v2i32 v = __builtin_nontemporal_load(reinterpret_cast<const v2i32 *>(pay_in + base) + local);
+        pay[r] = make_int2(v.x, v.y);
+      }
     }
   }
+  __syncthreads();
+  int *global_minus_local = digit_start;
+  if (threadIdx.x < bins) {
+    global_minus_local[threadIdx.x] = start.y + digit_offset - start.x;
+    if (bases_out != nullptr && blockIdx.x == 0) bases_out[threadIdx.x] = start.y;
+  }
+  // The keys through LDS first, then the payloads through the same bytes: 68 KB
+  // of LDS in all, so two workgroups share a CU and one ranks while the other
+  // loads or writes.
+  uint32_t *s_keys = reinterpret_cast<uint32_t *>(stage);
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r)
+    if ((wave * kRounds + r) * kWave + lane < tile_n) s_keys[pos[r]] = key[r];
+  __syncthreads();
+  int32_t to[kRounds];  // global slot of tile position threadIdx.x + i * kSortThreads
+#pragma unroll
+  for (int i = 0; i < kRounds; ++i) {
+    const int j = threadIdx.x + i * kSortThreads;
+    to[i] = -1;
+    if (j < tile_n) {
+      const uint32_t k = s_keys[j];
+      const uint32_t g = uint32_t(global_minus_local[(k >> shift) & mask] + j);
+      if (g < uint32_t(n)) {  // always true for consistent counts; never write outside the arrays
+        to[i] = int32_t(g);
+        if (kKeyOut == 4) static_cast<uint32_t *>(keys_out)[g] = k;
+        if (kKeyOut == 2) static_cast<uint16_t *>(keys_out)[g] = uint16_t(k);
+      }
+    }
+    if (i % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+  }
+  __syncthreads();
   if (kFirst) {  // predicate and object ids (subjects were checked by the count pass)
     int bad = 0;
 #pragma unroll
@@ -180,138 +372,109 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
       bad |= (uint32_t(pay[r].x) >= uint32_t(num_predicates)) | (uint32_t(pay[r].y) >= uint32_t(num_entities));
     if (__ballot(bad) != 0 && lane == 0 && status != nullptr) atomicOr(status, RDF2V_STATUS_ID_OUT_OF_RANGE);
   }
+  int2 *s_pay = reinterpret_cast<int2 *>(stage);
 #pragma unroll
-  for (int r = 0; r < kRounds; ++r) {
-    const int local = wave * kWaveItems + r * kWave + lane;
-    const bool valid = local < tile_n;
-    const uint32_t k = key[r];
-    const uint32_t d = (k >> shift) & mask;
-    // Lanes of this round holding the same digit.
-    uint64_t peers = __ballot(valid);
-    for (int b = 0; b < bits; ++b) {
-      const bool bit = (d >> b) & 1u;
-      const uint64_t m = __ballot(bit);
-      peers &= bit ? m : ~m;
-    }
-    const int below = __popcll(peers & lanes_below(lane));
-    const int before = valid ? wave_count[wave][d] : 0;
-    rank[r] = before + below;
-    // The lowest lane of each digit group advances the wave's counter; its
-    // store depends on the load above, so every lane's load precedes it.
-    if (valid && below == 0) wave_count[wave][d] = before + __popcll(peers);
-  }
+  for (int r = 0; r < kRounds; ++r)
+    if ((wave * kRounds + r) * kWave + lane < tile_n) s_pay[pos[r]] = pay[r];
   __syncthreads();
-
-  // Tile-local start of every (wave, digit) run, and the shift from tile-local
-  // to global slot per digit.
-  {
-    const int d = threadIdx.x;
-    int c[kTileWaves];
-    int total = 0;
 #pragma unroll
-    for (int w = 0; w < kTileWaves; ++w) {
-      c[w] = d < bins ? wave_count[w][d] : 0;
-      total += c[w];
-    }
-    int tile_total;
-    const int start = block_exclusive_scan<kSortThreads>(total, scan_scratch, tile_total);
-    if (d < bins) {
-      int run = start;
-#pragma unroll
-      for (int w = 0; w < kTileWaves; ++w) {
-        wave_count[w][d] = run;
-        run += c[w];
-      }
-      global_minus_local[d] = digit_global - start;
-    }
-  }
-  __syncthreads();
-
-#pragma unroll
-  for (int r = 0; r < kRounds; ++r) {
-    const int local = wave * kWaveItems + r * kWave + lane;
-    if (local < tile_n) {
-      const int pos = wave_count[wave][(key[r] >> shift) & mask] + rank[r];
-      if (pos < kTile) {  // always true; keeps a logic slip from leaving the tile
-        s_keys[pos] = key[r];
-        s_pay[pos] = pay[r];
-      }
-    }
-  }
-  __syncthreads();
-
-  for (int j = threadIdx.x; j < tile_n; j += kSortThreads) {
-    const uint32_t k = s_keys[j];
-    const int64_t g = int64_t(global_minus_local[(k >> shift) & mask]) + j;
-    if (g >= 0 && g < n) {  // always true for consistent counts; never write outside the arrays
-      keys_out[g] = k;
-      pay_out[g] = s_pay[j];
-    }
-  }
+  for (int i = 0; i < kRounds; ++i)
+    if (to[i] >= 0) pay_out[uint32_t(to[i])] = s_pay[threadIdx.x + i * kSortThreads];
 }
 
 // ---------------------------------------------------------------------------
-// Exclusive scan of int32 (reduce -> scan of block sums -> apply).
+// One workgroup, one launch: at most kMostTile triples. The passes exchange keys
+// and payloads through LDS. With at most kSmallEntities entities row_ptr is
+// the scan of a histogram of the subjects; with more, the sorted subjects go
+// to keys_out for the row_ptr kernels. What bounds it is the chain of LDS
+// round trips and barriers; the passes as kernels of their own would be bound
+// by the gaps between thirteen launches (figures at launch_csr_build).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kScanThreads) void scan_reduce_kernel(const int32_t *__restrict__ in,
-                                                                   int64_t n,
-                                                                   int32_t *__restrict__ partials) {
-  __shared__ int scratch[kScanThreads / kWave];
-  const int64_t base = int64_t(blockIdx.x) * kScanTile;
-  int s = 0;
-#pragma unroll 4
-  for (int i = 0; i < kScanItems; ++i) {
-    const int64_t idx = base + int64_t(i) * kScanThreads + threadIdx.x;
-    if (idx < n) s += in[idx];
-  }
-  const int total = block_sum<kScanThreads>(s, scratch);
-  if (threadIdx.x == 0) partials[blockIdx.x] = total;
-}
+constexpr int kSmallEntities = kStageBytes<kMostRounds> / 4;
 
-// One block: exclusive scan of the block sums in place; partials[nb] = total.
-__global__ __launch_bounds__(kScanThreads) void scan_partials_kernel(int32_t *partials, int64_t nb,
-                                                                     int64_t *total_out) {
-  __shared__ int scratch[kScanThreads / kWave];
-  int carry = 0;
-  for (int64_t base = 0; base < nb; base += kScanThreads) {
-    const int64_t idx = base + threadIdx.x;
-    const int x = idx < nb ? partials[idx] : 0;
-    int tot;
-    const int ex = block_exclusive_scan<kScanThreads>(x, scratch, tot);
-    if (idx < nb) partials[idx] = carry + ex;
-    carry += tot;
+__global__ __launch_bounds__(kSortThreads) void csr_small_kernel(
+    const uint32_t *__restrict__ subj, const int32_t *__restrict__ pred, const int32_t *__restrict__ obj, int n,
+    int32_t num_entities, int32_t num_predicates, int total_bits, int32_t *__restrict__ row_ptr,
+    int2 *__restrict__ edges, uint32_t *__restrict__ keys_out, int32_t *status) {
+  constexpr int kRounds = kMostRounds;
+  __shared__ __align__(16) char stage[kStageBytes<kRounds>];
+  __shared__ int digit_start[kMaxBins];
+  __shared__ int2 scan_scratch[kSortThreads / kWave];
+  const bool with_row_ptr = num_entities <= kSmallEntities;
+  const int lane = lane_id();
+  const int wave = threadIdx.x / kWave;
+  uint32_t key[kRounds];
+  int2 pay[kRounds];
+  bool valid[kRounds];
+  int bad = 0;
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    const int i = (wave * kRounds + r) * kWave + lane;
+    valid[r] = i < n;
+    key[r] = 0;
+    pay[r] = make_int2(0, 0);
+    if (valid[r]) {
+      key[r] = subj[i];
+      pay[r] = make_int2(pred[i], obj[i]);
+      bad |= (key[r] >= uint32_t(num_entities)) | (uint32_t(pay[r].x) >= uint32_t(num_predicates)) |
+             (uint32_t(pay[r].y) >= uint32_t(num_entities));
+    }
   }
-  if (threadIdx.x == 0) {
-    partials[nb] = carry;
-    if (total_out != nullptr) *total_out = carry;
-  }
-}
+  if (__ballot(bad) != 0 && lane == 0 && status != nullptr) atomicOr(status, RDF2V_STATUS_ID_OUT_OF_RANGE);
 
-__global__ __launch_bounds__(kScanThreads) void scan_apply_kernel(const int32_t *in, int64_t n,
-                                                                  const int32_t *__restrict__ partials,
-                                                                  int32_t *out) {
-  __shared__ int scratch[kScanThreads / kWave];
-  const int64_t base = int64_t(blockIdx.x) * kScanTile;
-  int carry = partials[blockIdx.x];
-  for (int i = 0; i < kScanItems; ++i) {
-    const int64_t idx = base + int64_t(i) * kScanThreads + threadIdx.x;
-    const int x = idx < n ? in[idx] : 0;
-    int tot;
-    const int ex = block_exclusive_scan<kScanThreads>(x, scratch, tot);
-    if (idx < n) out[idx] = carry + ex;
-    carry += tot;
+  if (with_row_ptr) {
+    const int per = (num_entities + kSortThreads - 1) / kSortThreads;  // consecutive entities per thread
+    int *hist = reinterpret_cast<int *>(stage);
+    for (int v = threadIdx.x; v < per * kSortThreads; v += kSortThreads) hist[v] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r)
+      if (valid[r] && key[r] < uint32_t(num_entities)) atomicAdd(&hist[key[r]], 1);
+    __syncthreads();
+    int sum = 0;
+    for (int i = 0; i < per; ++i) sum += hist[threadIdx.x * per + i];
+    int before = block_exclusive_scan2<kSortThreads>(make_int2(sum, 0), scan_scratch).x;
+    for (int i = 0; i < per; ++i) {
+      const int v = threadIdx.x * per + i;
+      if (v < num_entities) row_ptr[v] = before;
+      before += hist[v];
+    }
+    if (threadIdx.x == 0) row_ptr[num_entities] = n;
+    __syncthreads();
   }
-}
 
-rdf2v_status scan_exclusive(int32_t *data, int64_t n, int32_t *partials, int64_t nb,
-                            hipStream_t stream) {
-  scan_reduce_kernel<<<dim3(unsigned(nb)), dim3(kScanThreads), 0, stream>>>(data, n, partials);
-  RDF2V_LAUNCH_CHECK();
-  scan_partials_kernel<<<dim3(1), dim3(kScanThreads), 0, stream>>>(partials, nb, nullptr);
-  RDF2V_LAUNCH_CHECK();
-  scan_apply_kernel<<<dim3(unsigned(nb)), dim3(kScanThreads), 0, stream>>>(data, n, partials, data);
-  RDF2V_LAUNCH_CHECK();
-  return RDF2V_OK;
+  const int passes = (total_bits + kMaxDigitBits - 1) / kMaxDigitBits;  // at most four
+  for (int pass = 0, shift = 0; pass < passes; ++pass) {
+    const int bits = (total_bits - shift + passes - pass - 1) / (passes - pass);
+    uint32_t pos[kRounds];
+    tile_positions<kMaxDigitBits, kRounds>(key, n, shift, 1 << bits, 0, reinterpret_cast<uint16_t *>(stage), digit_start, scan_scratch,
+                      pos);
+    __syncthreads();
+    uint32_t *s_keys = reinterpret_cast<uint32_t *>(stage);
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r)
+      if (valid[r]) s_keys[pos[r]] = key[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) key[r] = valid[r] ? s_keys[(wave * kRounds + r) * kWave + lane] : 0;
+    __syncthreads();
+    int2 *s_pay = reinterpret_cast<int2 *>(stage);
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r)
+      if (valid[r]) s_pay[pos[r]] = pay[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r)
+      if (valid[r]) pay[r] = s_pay[(wave * kRounds + r) * kWave + lane];
+    __syncthreads();
+    shift += bits;
+  }
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    const int i = (wave * kRounds + r) * kWave + lane;
+    if (valid[r]) edges[i] = pay[r];
+    if (valid[r] && !with_row_ptr) keys_out[i] = key[r];
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -319,59 +482,126 @@ rdf2v_status scan_exclusive(int32_t *data, int64_t n, int32_t *partials, int64_t
 // subjects in one pass: where the subject changes from a (at position i-1) to
 // b (at i), every v in (a, b] has row_ptr[v] = i; the subjects v above the
 // last one get n. A thread writes at most kGapRun of those entries; longer
-// runs of entities without out-edges keep the -1 that row_ptr_fill_kernel put
+// runs of entities without out-edges keep the -1 that the first count pass put
 // there, and row_ptr_fixup_kernel finds each of them by binary search.
 // ---------------------------------------------------------------------------
 constexpr int kGapRun = 64;
 
-__global__ __launch_bounds__(256) void row_ptr_fill_kernel(int32_t *__restrict__ row_ptr, int64_t nv) {
-  const int64_t v = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (v < nv) row_ptr[v] = -1;
+// The sorted subjects as the last pass left them: the low bits of each, and
+// where each top digit begins. kKey: bytes of a stored key (4: the whole
+// subject, and the digits are not used; 2; 0: there are no low bits).
+struct SortedKeys {
+  const void *keys;
+  const int32_t *bases;  // [bins]
+  int bins;
+  int low_bits;
+};
+
+template <int kKey>
+__device__ __forceinline__ uint32_t stored_key(const SortedKeys &k, int64_t i) {
+  if (kKey == 4) return static_cast<const uint32_t *>(k.keys)[i];
+  if (kKey == 2) return static_cast<const uint16_t *>(k.keys)[i] & ((1u << k.low_bits) - 1);
+  return 0;
 }
 
-// Each thread takes kBoundItems consecutive positions (two 16-byte loads).
-constexpr int kBoundItems = 8;
+// Each thread takes consecutive positions (two 16-byte loads of keys). The top
+// digit of a wave's first position comes from two ballots over the bases; where
+// none begins among the wave's positions, as nearly everywhere, that is the
+// digit of them all. (A search per thread through the bases in LDS took 32 us
+// at 20M triples, twice the 4-byte keys' time.)
+constexpr int kBoundThreads = 256;
+template <int kKey>
+constexpr int kBoundItems = kKey == 4 ? 8 : 16;
 
-__global__ __launch_bounds__(256) void row_ptr_bounds_kernel(const uint32_t *__restrict__ sorted_keys,
-                                                             int64_t n, int32_t num_entities,
-                                                             int32_t *__restrict__ row_ptr) {
-  const int64_t i0 = (int64_t(blockIdx.x) * 256 + threadIdx.x) * kBoundItems;
-  if (i0 > n) return;
-  uint32_t k[kBoundItems];
-  if (i0 + kBoundItems <= n && (reinterpret_cast<uintptr_t>(sorted_keys) & 15) == 0) {
-    const uint4 *k4 = reinterpret_cast<const uint4 *>(sorted_keys + i0);
-    const uint4 v0 = k4[0], v1 = k4[1];
-    k[0] = v0.x; k[1] = v0.y; k[2] = v0.z; k[3] = v0.w;
-    k[4] = v1.x; k[5] = v1.y; k[6] = v1.z; k[7] = v1.w;
+template <int kKey>
+__global__ __launch_bounds__(kBoundThreads) void row_ptr_bounds_kernel(const SortedKeys sorted,
+                                                                       int64_t n_triples, int32_t num_entities,
+                                                                       int32_t *__restrict__ row_ptr) {
+  // Positions and ids are below 2^31: unsigned 32-bit arithmetic throughout.
+  constexpr uint32_t kItems = kBoundItems<kKey>;
+  const uint32_t n = uint32_t(n_triples), V = uint32_t(num_entities);
+  const uint32_t lane = uint32_t(lane_id());
+  const uint32_t w0 = (blockIdx.x * uint32_t(kBoundThreads) + threadIdx.x - lane) * kItems;  // the wave's first
+  if (w0 > n) return;  // uniform per wave
+  const uint32_t i0 = w0 + lane * kItems;
+  uint32_t k[kItems];
+  if (i0 + kItems <= n && (reinterpret_cast<uintptr_t>(sorted.keys) & 15) == 0 && kKey != 0) {
+    const uint4 *k4 = reinterpret_cast<const uint4 *>(static_cast<const char *>(sorted.keys) + size_t(i0) * kKey);
+    const uint4 v[2] = {k4[0], k4[1]};
+#pragma unroll
+    for (uint32_t j = 0; j < 2; ++j) {
+      const uint32_t w[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+#pragma unroll
+      for (uint32_t c = 0; c < 4; ++c) {
+        if (kKey == 4) {
+          k[4 * j + c] = w[c];
+        } else {
+          const uint32_t low = (1u << sorted.low_bits) - 1;
+          k[(8 * j + 2 * c) % kItems] = w[c] & low;
+          k[(8 * j + 2 * c + 1) % kItems] = (w[c] >> 16) & low;
+        }
+      }
+    }
   } else {
 #pragma unroll
-    for (int j = 0; j < kBoundItems; ++j) k[j] = i0 + j < n ? sorted_keys[i0 + j] : 0u;
+    for (uint32_t j = 0; j < kItems; ++j) k[j] = i0 + j < n ? stored_key<kKey>(sorted, i0 + j) : 0u;
   }
-  // entities in (a, b] start at position i; a = -1 before the first subject, b = V after the last
-  int64_t a = i0 == 0 ? -1 : int64_t(sorted_keys[i0 - 1]);
-#pragma unroll
-  for (int j = 0; j < kBoundItems; ++j) {
-    const int64_t i = i0 + j;
-    if (i > n) break;
-    const int64_t b = i == n ? int64_t(num_entities) : int64_t(k[j]);
-    if (b != a) {
-      const int64_t hi = min(b, int64_t(num_entities));  // ids >= V cannot occur after validation
-      const int64_t lo = max(a + 1, hi - (kGapRun - 1));
-      for (int64_t v = lo; v <= hi; ++v) row_ptr[v] = int32_t(i);
+  const uint32_t prev = i0 > 0 && i0 <= n ? stored_key<kKey>(sorted, i0 - 1) : 0u;
+  uint32_t d = 0;  // top digit of position i0 - 1, then of each position in turn
+  uint32_t next = 0xffffffffu;  // where digit d + 1 begins
+  if (kKey != 4) {
+    // largest digit whose base is at or below `at`: 64 samples, then the bases between two of them
+    const uint32_t bins = uint32_t(sorted.bins);
+    const uint32_t *bases = reinterpret_cast<const uint32_t *>(sorted.bases);
+    const uint32_t at = min(w0 > 0 ? w0 - 1 : 0u, n - 1);
+    const uint32_t step = max(1u, bins / kWave);  // bins is a power of two, at most 1024
+    const uint32_t s = (__popcll(__ballot(lane * step < bins && bases[min(lane * step, bins - 1)] <= at)) - 1) * step;
+    d = s + __popcll(__ballot(lane < step && bases[min(s + lane, bins - 1)] <= at)) - 1;
+    next = d + 1 < bins ? bases[d + 1] : 0xffffffffu;
+    const uint32_t before = min(i0 > 0 ? i0 - 1 : 0u, n - 1);
+    while (next <= before) {
+      ++d;
+      next = d + 1 < bins ? bases[d + 1] : 0xffffffffu;
     }
-    a = b;
+  }
+  if (i0 > n) return;
+  // entities in (a, b] start at position i; a = -1 before the first subject, b = V after the last
+  auto whole = [&](uint32_t low) -> uint32_t { return kKey == 4 ? low : (d << sorted.low_bits) | low; };
+  uint32_t first = i0 == 0 ? 0u : whole(prev) + 1;  // a + 1
+#pragma unroll
+  for (uint32_t j = 0; j < kItems; ++j) {
+    const uint32_t i = i0 + j;
+    if (i > n) break;
+    while (next <= i && i < n) {
+      ++d;
+      next = d + 1 < uint32_t(sorted.bins) ? uint32_t(sorted.bases[d + 1]) : 0xffffffffu;
+    }
+    const uint32_t b = i == n ? V : whole(k[j]);
+    if (b >= first) {
+      const uint32_t hi = min(b, V);  // ids >= V cannot occur after validation
+      const uint32_t lo = max(first, hi >= uint32_t(kGapRun) ? hi - (kGapRun - 1) : 0u);
+      for (uint32_t v = lo; v <= hi; ++v) row_ptr[v] = int32_t(i);
+    }
+    first = b + 1;
   }
 }
 
-__global__ __launch_bounds__(256) void row_ptr_fixup_kernel(const uint32_t *__restrict__ sorted_keys,
-                                                            int64_t n, int32_t num_entities,
+template <int kKey>
+__global__ __launch_bounds__(256) void row_ptr_fixup_kernel(const SortedKeys sorted, int64_t n, int32_t num_entities,
                                                             int32_t *__restrict__ row_ptr) {
   const int64_t v = int64_t(blockIdx.x) * 256 + threadIdx.x;
   if (v > num_entities || row_ptr[v] >= 0) return;
   int64_t lo = 0, hi = n;
+  uint32_t want = uint32_t(v);
+  if (kKey != 4) {  // inside the range of v's top digit
+    const int64_t d = v >> sorted.low_bits;
+    lo = d < sorted.bins ? sorted.bases[d] : n;
+    hi = d + 1 < sorted.bins ? int64_t(sorted.bases[d + 1]) : n;
+    want &= (1u << sorted.low_bits) - 1;
+  }
   while (lo < hi) {
     const int64_t mid = (lo + hi) >> 1;
-    if (sorted_keys[mid] < uint32_t(v)) lo = mid + 1;
+    if (stored_key<kKey>(sorted, mid) < want) lo = mid + 1;
     else hi = mid;
   }
   row_ptr[v] = int32_t(lo);
@@ -383,71 +613,238 @@ __global__ __launch_bounds__(256) void fill_kernel(int32_t *p, int64_t n, int32_
 }
 
 // ---------------------------------------------------------------------------
-// Entities with out-degree >= 1, ascending (count per block, scan, compact).
+// Entities with out-degree >= 1, ascending: a count per block of kStartTile
+// entities (one launch, left out when there is one block only), then each block
+// adds the counts before its own and writes its entities.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kScanThreads) void nonsink_count_kernel(const int32_t *__restrict__ row_ptr,
-                                                                     int32_t num_entities,
-                                                                     int32_t *__restrict__ partials) {
-  __shared__ int scratch[kScanThreads / kWave];
-  const int64_t base = int64_t(blockIdx.x) * kScanTile;
-  int s = 0;
-  for (int i = 0; i < kScanItems; ++i) {
-    const int64_t v = base + int64_t(i) * kScanThreads + threadIdx.x;
-    if (v < num_entities) s += row_ptr[v + 1] > row_ptr[v];
+constexpr int kStartThreads = 1024;
+constexpr int kStartItems = 16;
+constexpr int kStartTile = kStartThreads * kStartItems;
+constexpr int kStartWaves = kStartThreads / kWave;
+
+// Bit i: entity v0 + i * 64 + lane of the calling wave has out-edges (v0 = the
+// wave's first of kStartItems * 64 entities).
+__device__ __forceinline__ uint32_t nonsink_flags(const int32_t *__restrict__ row_ptr, int32_t num_entities, int64_t v0) {
+  int32_t lo[kStartItems], hi[kStartItems];
+#pragma unroll
+  for (int i = 0; i < kStartItems; ++i) {
+    const int64_t v = v0 + i * kWave + lane_id();
+    lo[i] = hi[i] = 0;
+    if (v < num_entities) {
+      lo[i] = row_ptr[v];
+      hi[i] = row_ptr[v + 1];
+    }
   }
-  const int total = block_sum<kScanThreads>(s, scratch);
+  uint32_t f = 0;
+#pragma unroll
+  for (int i = 0; i < kStartItems; ++i) f |= hi[i] > lo[i] ? 1u << i : 0u;
+  return f;
+}
+
+__global__ __launch_bounds__(kStartThreads) void nonsink_count_kernel(const int32_t *__restrict__ row_ptr,
+                                                                      int32_t num_entities,
+                                                                      int32_t *__restrict__ partials) {
+  __shared__ int scratch[kStartWaves];
+  const int64_t v0 = int64_t(blockIdx.x) * kStartTile + int64_t(threadIdx.x / kWave) * kWave * kStartItems;
+  const int total = block_sum<kStartThreads, int>(int(__popc(nonsink_flags(row_ptr, num_entities, v0))), scratch);
   if (threadIdx.x == 0) partials[blockIdx.x] = total;
 }
 
-__global__ __launch_bounds__(kScanThreads) void nonsink_compact_kernel(const int32_t *__restrict__ row_ptr,
-                                                                       int32_t num_entities,
-                                                                       const int32_t *__restrict__ partials,
-                                                                       int32_t *__restrict__ out) {
-  __shared__ int scratch[kScanThreads / kWave];
-  const int64_t base = int64_t(blockIdx.x) * kScanTile;
-  int carry = partials[blockIdx.x];
-  for (int i = 0; i < kScanItems; ++i) {
-    const int64_t v = base + int64_t(i) * kScanThreads + threadIdx.x;
-    const int f = (v < num_entities) ? (row_ptr[v + 1] > row_ptr[v]) : 0;
-    int tot;
-    const int ex = block_exclusive_scan<kScanThreads>(f, scratch, tot);
-    if (f) out[carry + ex] = int32_t(v);
-    carry += tot;
+__global__ __launch_bounds__(kStartThreads) void nonsink_compact_kernel(const int32_t *__restrict__ row_ptr,
+                                                                        int32_t num_entities,
+                                                                        const int32_t *__restrict__ partials,
+                                                                        int32_t *__restrict__ out,
+                                                                        int64_t *__restrict__ count_out) {
+  __shared__ int2 scratch[kStartWaves];
+  const int wave = threadIdx.x / kWave;
+  const int64_t v0 = int64_t(blockIdx.x) * kStartTile + int64_t(wave) * kWave * kStartItems;
+  const uint32_t f = nonsink_flags(row_ptr, num_entities, v0);
+  int before = 0;  // this thread's share of the counts of the blocks before
+  for (int64_t b = threadIdx.x; b < int64_t(blockIdx.x); b += kStartThreads) before += partials[b];
+  uint64_t m[kStartItems];
+  int in_wave = 0;
+#pragma unroll
+  for (int i = 0; i < kStartItems; ++i) {
+    m[i] = __ballot((f >> i) & 1u);
+    in_wave += __popcll(m[i]);
   }
+  // one sum over the waves: their counts, and the counts of the blocks before
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) before += __shfl_xor(before, off, kWave);
+  if (lane_id() == 0) scratch[wave] = make_int2(in_wave, before);
+  __syncthreads();
+  int64_t at = 0;
+  int total = 0;
+#pragma unroll
+  for (int w = 0; w < kStartWaves; ++w) {
+    const int2 s = scratch[w];
+    at += s.y + (w < wave ? s.x : 0);
+    total += s.x + s.y;
+  }
+#pragma unroll
+  for (int i = 0; i < kStartItems; ++i) {
+    if ((f >> i) & 1u) out[at + __popcll(m[i] & lanes_below(lane_id()))] = int32_t(v0 + i * kWave + lane_id());
+    at += __popcll(m[i]);
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *count_out = total;
 }
 
-inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+}  // namespace
+
+namespace {
+
+// Sizes of the count table of the 4,096-triple tiles and 8-bit digits that the
+// workspace size is defined by (callers hold workspaces of that size): the
+// passes below fit their tables into it and into free parts of the key buffers.
+struct TableSpace {
+  size_t counts, partials;
+};
+TableSpace reserved_tables(int64_t num_triples, int total_bits) {
+  int passes = total_bits == 0 ? 1 : int(ceil_div(total_bits, 8));
+  if (passes == 3 && total_bits <= 18) passes = 2;
+  const int widest = total_bits == 0 ? 1 : int(ceil_div(total_bits, passes));
+  const int64_t count_len = (int64_t(1) << widest) * ceil_div(num_triples, 4096);
+  return {align_up(size_t(count_len) * 4, 256), align_up(size_t(ceil_div(count_len, kScanTile) + 1) * 4, 256)};
+}
+
+int subject_bits(int32_t num_entities) {
+  return num_entities > 1 ? 32 - __builtin_clz(uint32_t(num_entities - 1)) : 0;
+}
+
+// Table bytes of a pass of `bits`: counts, totals, and the top digit's bases.
+size_t table_bytes(int64_t tiles, int bits) {
+  return align_up((size_t(1) << bits) * size_t(row_stride(tiles)) * 4, 256) + 2 * align_up(size_t(4) << bits, 256);
+}
 
 }  // namespace
 
 SortPlan plan_csr_build(int64_t num_triples, int32_t num_entities) {
   SortPlan p;
   if (num_triples <= 0) return p;
-  int total_bits = 0;
-  if (num_entities > 1) total_bits = 32 - __builtin_clz(uint32_t(num_entities - 1));
-  // Digits of at most 8 bits, except that ids of 17 or 18 bits take two 9-bit
-  // passes instead of three: a 512-bin pass costs about 1.4x a 256-bin one
-  // (shorter runs per tile, a count table twice as long), which pays when it
-  // saves one pass in three but not one in four.
-  p.passes = total_bits == 0 ? 1 : int(ceil_div(total_bits, 8));
-  if (p.passes == 3 && total_bits <= 2 * kMaxDigitBits) p.passes = 2;
-  // The bits are spread as evenly as the pass count allows, the first passes
-  // taking the odd ones: a pass of fewer bits has fewer bins and longer runs.
-  for (int k = 0; k < p.passes; ++k)
-    p.pass_bits[k] = total_bits == 0 ? 1 : total_bits / p.passes + (k < total_bits % p.passes ? 1 : 0);
-  p.digit_bits = p.pass_bits[0];
-  p.tiles = ceil_div(num_triples, kTile);
-  p.count_len = (int64_t(1) << p.digit_bits) * p.tiles;
-  p.count_blocks = ceil_div(p.count_len, kScanTile);
+  const int total_bits = subject_bits(num_entities);
+  const size_t T = size_t(num_triples);
+  const TableSpace space = reserved_tables(num_triples, total_bits);
   size_t off = 0;
-  p.off_keys_a = off;   off = align_up(off + size_t(num_triples) * 4, 256);
-  p.off_keys_b = off;   off = align_up(off + size_t(num_triples) * 4, 256);
-  p.off_payload = off;  off = align_up(off + size_t(num_triples) * 8, 256);
-  p.off_counts = off;   off = align_up(off + size_t(p.count_len) * 4, 256);
-  p.off_partials = off; off = align_up(off + size_t(p.count_blocks + 1) * 4, 256);
-  p.bytes = off;
+  p.off_keys_a = off;  off = align_up(off + T * 4, 256);
+  p.off_keys_b = off;  off = align_up(off + T * 4, 256);
+  p.off_payload = off; off = align_up(off + T * 8, 256);
+  const size_t off_tables = off;
+  p.bytes = off + space.counts + space.partials;
+  p.total_bits = total_bits;
+  if (num_triples <= kMostTile) return p;  // passes == 0: csr_small_kernel
+  const int bits = total_bits == 0 ? 1 : total_bits;
+  const size_t in_row_ptr = (size_t(num_entities) + 1) * 4;  // less up to 256 bytes of alignment
+  // As few passes as digits of at most kMaxDigitBits allow, the bits spread
+  // evenly with the odd ones last, or more in the last pass where that brings
+  // the bits below it to 16, so that it can write 2-byte keys. Every pass needs
+  // room for its table: the reserved one; else, for the first pass, the idle
+  // key buffer, for the last one the part of its key buffer that narrow keys
+  // leave, for any that leaves no bases behind the row_ptr output. Where that
+  // is not to be had (some tens of thousands of triples), narrower digits are.
+  // Rounds of a tile: as long as the tiles are fewer than about two per CU,
+  // smaller tiles use more of the chip (1M triples, scatter of 8 bits: 13.9 us
+  // with 8 rounds in 123 tiles).
+  const int rounds = num_triples >= (int64_t(4) << 20) ? 8 : num_triples >= (int64_t(2) << 20) ? 4 : 2;
+  for (int most = kMaxDigitBits; most > 0; --most)
+  for (p.rounds = rounds; p.rounds <= kMostRounds; p.rounds *= 2) {
+    p.tiles = ceil_div(num_triples, kSortThreads * p.rounds);
+    p.passes = int(ceil_div(bits, most));
+    if (p.passes > 4) break;
+    const int last = p.passes - 1;
+    for (int k = 0; k < p.passes; ++k) p.pass_bits[k] = bits / p.passes + (k >= p.passes - bits % p.passes ? 1 : 0);
+    if (p.passes == 3 && bits - p.pass_bits[last] > 16 && bits - 16 <= most) p.pass_bits[last] = bits - 16;
+    const int low = bits - p.pass_bits[last];
+    if (p.passes == 3) {  // the middle pass has the least room
+      p.pass_bits[0] = std::min(most, low - (low - 1) / 2);
+      p.pass_bits[1] = low - p.pass_bits[0];
+    }
+    p.key_out = low == 0 ? 0 : (low <= 16 ? 2 : 4);
+    bool fits = true;
+    for (int k = 0; k < p.passes; ++k) {
+      const size_t need = table_bytes(p.tiles, p.pass_bits[k]);
+      const size_t own_keys = align_up(T * size_t(p.key_out), 256);
+      const size_t out = k % 2 == 0 ? p.off_keys_a : p.off_keys_b;
+      p.table_in_row_ptr[k] = false;
+      if (need <= space.counts + space.partials) p.off_tables[k] = off_tables;
+      else if (k == 0 && last > 0 && need <= align_up(T * 4, 256)) p.off_tables[k] = p.off_keys_b;
+      else if (k == last && need + own_keys <= align_up(T * 4, 256)) p.off_tables[k] = out + own_keys;
+      else if ((k < last || p.key_out == 4) && need + 256 <= in_row_ptr) p.table_in_row_ptr[k] = true;
+      else fits = false;
+    }
+    if (fits) return p;
+  }
+  p.passes = -1;  // cannot happen: for 2 to 8 tiles digits of 7 or 8 bits fit, beyond that wider ones
   return p;
 }
+
+namespace {
+
+// What one pass reads and writes.
+struct PassArgs {
+  const uint32_t *keys_in;
+  const int2 *pay_in;
+  const int32_t *pred, *obj;  // first pass, instead of pay_in
+  void *keys_out;
+  int2 *pay_out;
+  int64_t n;
+  int shift, bits, key_out;
+  int32_t *counts, *totals, *bases;
+  int64_t tiles;
+  int32_t num_entities, num_predicates;
+  int32_t *row_ptr;  // first pass: to be marked, or NULL
+  int32_t *status;
+};
+
+template <bool kFirst, int kRounds, int kKeyOut>
+void launch_scatter(const PassArgs &p, hipStream_t stream) {
+  const dim3 grid{unsigned(p.tiles)}, block{kSortThreads};
+  auto run = [&](auto kernel) {
+    kernel<<<grid, block, 0, stream>>>(p.keys_in, p.pay_in, p.pred, p.obj, p.keys_out, p.pay_out, p.n, p.shift, p.bits,
+                                       p.counts, p.totals, p.bases, p.tiles, p.num_entities, p.num_predicates, p.status);
+  };
+  if (p.bits <= 8) run(radix_scatter_kernel<kFirst, kKeyOut, 8, kRounds>);
+  else run(radix_scatter_kernel<kFirst, kKeyOut, kMaxDigitBits, kRounds>);
+}
+
+template <bool kFirst, int kRounds>
+rdf2v_status launch_pass(const PassArgs &p, hipStream_t stream) {
+  radix_count_kernel<kFirst, kRounds><<<dim3(unsigned(p.tiles)), dim3(kCountThreads), 0, stream>>>(
+      p.keys_in, p.n, p.shift, p.bits, p.num_entities, p.counts, p.tiles, p.row_ptr, p.status);
+  RDF2V_LAUNCH_CHECK();
+  row_scan_kernel<<<dim3(1u << p.bits), dim3(kScanThreads), 0, stream>>>(p.counts, p.tiles, p.totals);
+  RDF2V_LAUNCH_CHECK();
+  if (p.key_out == 4) launch_scatter<kFirst, kRounds, 4>(p, stream);
+  else if (p.key_out == 2) launch_scatter<kFirst, kRounds, 2>(p, stream);
+  else launch_scatter<kFirst, kRounds, 0>(p, stream);
+  RDF2V_LAUNCH_CHECK();
+  return RDF2V_OK;
+}
+
+template <int kRounds>
+rdf2v_status launch_pass(bool first, const PassArgs &p, hipStream_t stream) {
+  return first ? launch_pass<true, kRounds>(p, stream) : launch_pass<false, kRounds>(p, stream);
+}
+
+rdf2v_status launch_row_ptr_fill(int32_t *row_ptr, int32_t num_entities, hipStream_t stream) {
+  const int64_t nv = int64_t(num_entities) + 1;
+  fill_kernel<<<dim3(unsigned(ceil_div(nv, 256))), dim3(256), 0, stream>>>(row_ptr, nv, -1);
+  RDF2V_LAUNCH_CHECK();
+  return RDF2V_OK;
+}
+
+template <int kKey>
+rdf2v_status launch_row_ptr(const SortedKeys &sorted, int64_t T, int32_t num_entities, int32_t *row_ptr,
+                            hipStream_t stream) {
+  row_ptr_bounds_kernel<kKey><<<dim3(unsigned(ceil_div(T + 1, kBoundThreads * kBoundItems<kKey>))), dim3(kBoundThreads), 0,
+                                stream>>>(sorted, T, num_entities, row_ptr);
+  RDF2V_LAUNCH_CHECK();
+  row_ptr_fixup_kernel<kKey><<<dim3(unsigned(ceil_div(int64_t(num_entities) + 1, 256))), dim3(256), 0, stream>>>(
+      sorted, T, num_entities, row_ptr);
+  RDF2V_LAUNCH_CHECK();
+  return RDF2V_OK;
+}
+
+}  // namespace
 
 rdf2v_status launch_csr_build(const int32_t *subj, const int32_t *pred, const int32_t *obj,
                               int64_t num_triples, int32_t num_entities, int32_t num_predicates,
@@ -460,56 +857,63 @@ rdf2v_status launch_csr_build(const int32_t *subj, const int32_t *pred, const in
     RDF2V_LAUNCH_CHECK();
     return RDF2V_OK;
   }
-  char *ws = static_cast<char *>(workspace);
-  uint32_t *keys_a = reinterpret_cast<uint32_t *>(ws + plan.off_keys_a);
-  uint32_t *keys_b = reinterpret_cast<uint32_t *>(ws + plan.off_keys_b);
-  int2 *pay_tmp = reinterpret_cast<int2 *>(ws + plan.off_payload);
-  int32_t *counts = reinterpret_cast<int32_t *>(ws + plan.off_counts);
-  int32_t *partials = reinterpret_cast<int32_t *>(ws + plan.off_partials);
-  int2 *edges2 = reinterpret_cast<int2 *>(edges_out);
-
   const uint32_t *keys_in = reinterpret_cast<const uint32_t *>(subj);
-  const int2 *pay_in = nullptr;
-  int shift = 0;
-  for (int pass = 0; pass < plan.passes; ++pass) {
-    const int bits = plan.pass_bits[pass];
-    const int64_t count_len = (int64_t(1) << bits) * plan.tiles;
-    uint32_t *keys_out = (pass % 2 == 0) ? keys_a : keys_b;
-    // The last pass must land in edges_out, so the payload alternates backwards from it.
-    int2 *pay_out = ((plan.passes - 1 - pass) % 2 == 0) ? edges2 : pay_tmp;
-    const dim3 grid(unsigned(plan.tiles));
-    if (pass == 0)
-      radix_count_kernel<true><<<grid, dim3(kCountThreads), 0, stream>>>(
-          keys_in, T, shift, bits, num_entities, counts, plan.tiles, status_dev);
-    else
-      radix_count_kernel<false><<<grid, dim3(kCountThreads), 0, stream>>>(
-          keys_in, T, shift, bits, num_entities, counts, plan.tiles, nullptr);
+  int2 *edges2 = reinterpret_cast<int2 *>(edges_out);
+  char *ws = static_cast<char *>(workspace);
+  if (plan.passes < 0) return RDF2V_ERR_WORKSPACE;
+  if (plan.passes == 0) {
+    uint32_t *keys = reinterpret_cast<uint32_t *>(ws + plan.off_keys_a);
+    csr_small_kernel<<<dim3(1), dim3(kSortThreads), 0, stream>>>(keys_in, pred, obj, int(T), num_entities,
+                                                                num_predicates, plan.total_bits, row_ptr_out, edges2,
+                                                                keys, status_dev);
     RDF2V_LAUNCH_CHECK();
-    const rdf2v_status st = scan_exclusive(counts, count_len, partials, ceil_div(count_len, kScanTile), stream);
+    if (num_entities <= kSmallEntities) return RDF2V_OK;
+    const rdf2v_status st = launch_row_ptr_fill(row_ptr_out, num_entities, stream);
     if (st != RDF2V_OK) return st;
-    if (pass == 0)
-      radix_scatter_kernel<true><<<grid, dim3(kSortThreads), 0, stream>>>(
-          keys_in, nullptr, pred, obj, keys_out, pay_out, T, shift, bits, counts,
-          plan.tiles, num_entities, num_predicates, status_dev);
-    else
-      radix_scatter_kernel<false><<<grid, dim3(kSortThreads), 0, stream>>>(
-          keys_in, pay_in, nullptr, nullptr, keys_out, pay_out, T, shift, bits, counts,
-          plan.tiles, num_entities, num_predicates, nullptr);
-    RDF2V_LAUNCH_CHECK();
-    keys_in = keys_out;
-    pay_in = pay_out;
-    shift += bits;
+    return launch_row_ptr<4>({keys, nullptr, 0, 0}, T, num_entities, row_ptr_out, stream);
   }
-  const int64_t nv = int64_t(num_entities) + 1;
-  row_ptr_fill_kernel<<<dim3(unsigned(ceil_div(nv, 256))), dim3(256), 0, stream>>>(row_ptr_out, nv);
-  RDF2V_LAUNCH_CHECK();
-  row_ptr_bounds_kernel<<<dim3(unsigned(ceil_div(T + 1, 256 * kBoundItems))), dim3(256), 0, stream>>>(
-      keys_in, T, num_entities, row_ptr_out);
-  RDF2V_LAUNCH_CHECK();
-  row_ptr_fixup_kernel<<<dim3(unsigned(ceil_div(nv, 256))), dim3(256), 0, stream>>>(keys_in, T, num_entities,
-                                                                                   row_ptr_out);
-  RDF2V_LAUNCH_CHECK();
-  return RDF2V_OK;
+  int2 *pay_tmp = reinterpret_cast<int2 *>(ws + plan.off_payload);
+  bool fill_later = false;  // row_ptr_out holds a table until the sort is done
+  for (int pass = 0; pass < plan.passes; ++pass) fill_later = fill_later || plan.table_in_row_ptr[pass];
+  PassArgs p{};
+  p.keys_in = keys_in;
+  p.pred = pred;
+  p.obj = obj;
+  p.n = T;
+  p.tiles = plan.tiles;
+  p.num_entities = num_entities;
+  p.num_predicates = num_predicates;
+  for (int pass = 0; pass < plan.passes; ++pass) {
+    const bool first = pass == 0, last = pass == plan.passes - 1;
+    p.bits = plan.pass_bits[pass];
+    p.keys_out = ws + (pass % 2 == 0 ? plan.off_keys_a : plan.off_keys_b);
+    p.key_out = last ? plan.key_out : 4;
+    // The last pass must land in edges_out, so the payload alternates backwards from it.
+    p.pay_out = ((plan.passes - 1 - pass) % 2 == 0) ? edges2 : pay_tmp;
+    p.counts = plan.table_in_row_ptr[pass]
+                   ? reinterpret_cast<int32_t *>(align_up(reinterpret_cast<uintptr_t>(row_ptr_out), 256))
+                   : reinterpret_cast<int32_t *>(ws + plan.off_tables[pass]);
+    p.totals = p.counts + align_up((size_t(1) << p.bits) * size_t(row_stride(plan.tiles)) * 4, 256) / 4;
+    p.bases = last ? p.totals + align_up(size_t(4) << p.bits, 256) / 4 : nullptr;
+    p.row_ptr = first && !fill_later ? row_ptr_out : nullptr;
+    p.status = first ? status_dev : nullptr;
+    const rdf2v_status st = plan.rounds == 2   ? launch_pass<2>(first, p, stream)
+                            : plan.rounds == 4 ? launch_pass<4>(first, p, stream)
+                                               : launch_pass<8>(first, p, stream);
+    if (st != RDF2V_OK) return st;
+    p.keys_in = static_cast<const uint32_t *>(p.keys_out);
+    p.pay_in = p.pay_out;
+    p.shift += p.bits;
+  }
+  if (fill_later) {
+    const rdf2v_status st = launch_row_ptr_fill(row_ptr_out, num_entities, stream);
+    if (st != RDF2V_OK) return st;
+  }
+  const int top = plan.pass_bits[plan.passes - 1];
+  const SortedKeys sorted{p.keys_in, p.bases, 1 << top, p.shift - top};
+  if (plan.key_out == 4) return launch_row_ptr<4>(sorted, T, num_entities, row_ptr_out, stream);
+  if (plan.key_out == 2) return launch_row_ptr<2>(sorted, T, num_entities, row_ptr_out, stream);
+  return launch_row_ptr<0>(sorted, T, num_entities, row_ptr_out, stream);
 }
 
 size_t nonsink_workspace_bytes(int32_t num_entities) {
@@ -519,20 +923,16 @@ size_t nonsink_workspace_bytes(int32_t num_entities) {
 
 rdf2v_status launch_nonsink_starts(const int32_t *row_ptr, int32_t num_entities, int32_t *starts_out,
                                    int64_t *count_out, void *workspace, hipStream_t stream) {
-  const int64_t nb = ceil_div(int64_t(num_entities), kScanTile);
+  // no entities: one block that finds none and writes the count
+  const int64_t nb = num_entities > 0 ? ceil_div(int64_t(num_entities), kStartTile) : 1;
   int32_t *partials = static_cast<int32_t *>(workspace);
-  if (nb > 0) {
-    nonsink_count_kernel<<<dim3(unsigned(nb)), dim3(kScanThreads), 0, stream>>>(row_ptr, num_entities,
-                                                                               partials);
+  if (nb > 1) {
+    nonsink_count_kernel<<<dim3(unsigned(nb)), dim3(kStartThreads), 0, stream>>>(row_ptr, num_entities, partials);
     RDF2V_LAUNCH_CHECK();
   }
-  scan_partials_kernel<<<dim3(1), dim3(kScanThreads), 0, stream>>>(partials, nb, count_out);
+  nonsink_compact_kernel<<<dim3(unsigned(nb)), dim3(kStartThreads), 0, stream>>>(row_ptr, num_entities, partials,
+                                                                                starts_out, count_out);
   RDF2V_LAUNCH_CHECK();
-  if (nb > 0) {
-    nonsink_compact_kernel<<<dim3(unsigned(nb)), dim3(kScanThreads), 0, stream>>>(
-        row_ptr, num_entities, partials, starts_out);
-    RDF2V_LAUNCH_CHECK();
-  }
   return RDF2V_OK;
 }
 

@@ -12,15 +12,19 @@
 
 namespace rdf2v {
 
-// Layout of the rdf2v_build_csr workspace for (num_triples, num_entities).
+// Passes of rdf2v_build_csr and the layout of its workspace for (num_triples,
+// num_entities). The size depends on both only through buffers of 16 B per
+// triple and a reserved count table; the passes fit themselves into it.
 struct SortPlan {
-  int passes = 0;      // LSD radix passes over the subject id
-  int digit_bits = 0;  // bits of the widest pass (<= 9); sizes the count table
+  int total_bits = 0;               // bits of a subject id
+  int passes = 0;                   // LSD radix passes; 0: one workgroup sorts in one launch
   int pass_bits[4] = {0, 0, 0, 0};  // bits of each pass, lowest digit first
-  int64_t tiles = 0;   // 4096-triple tiles
-  int64_t count_len = 0;     // digit-major count table length = bins * tiles
-  int64_t count_blocks = 0;  // scan blocks over the count table
-  size_t off_keys_a = 0, off_keys_b = 0, off_payload = 0, off_counts = 0, off_partials = 0;
+  int rounds = 8;                   // tiles of 1,024 triples times this
+  int key_out = 4;                  // bytes of a key the last pass writes (0, 2 or 4)
+  int64_t tiles = 0;
+  size_t off_keys_a = 0, off_keys_b = 0, off_payload = 0;
+  size_t off_tables[4] = {0, 0, 0, 0};  // count table, totals and bases of each pass ...
+  bool table_in_row_ptr[4] = {false, false, false, false};  // ... or they lie in the row_ptr output
   size_t bytes = 0;
 };
 SortPlan plan_csr_build(int64_t num_triples, int32_t num_entities);

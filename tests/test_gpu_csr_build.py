@@ -11,6 +11,7 @@ made to reach the edge cases of its kernels, bit-exact (row_ptr and edges whole)
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import paper_2508_01073_amd as rd
@@ -85,3 +86,33 @@ def test_bad_ids_still_flagged_in_every_column():
     st = new_status()
     rd.rdf2v_build_csr(*(to_dev(c) for c in base), V, P, status=st)
     assert int(st.item()) == 0
+
+
+@pytest.mark.parametrize("T,V", [
+    (1, 1), (8192, 16_384), (8191, 16_385), (77, 1 << 24),     # one workgroup, row_ptr inside it or not
+    (8193, 1), (8193, 1000), (8193, 16_385),                   # two tiles; keys of 0 and 2 bytes
+    (8193, 1 << 26), (12_289, 1 << 26),                        # a table in row_ptr, 4-byte and 2-byte last keys
+    (30_001, 1 << 20), (100_003, 262_145),                     # two passes of 9 and 10 bits
+    (1 << 21, 100_000), ((1 << 21) + 5, 3), ((1 << 22) + 1, 3_000_000),  # tiles of 2, 4 and 8 rounds
+    (1_000_003, (1 << 25) + 1),                                # 9, 7 and 10 bits
+])
+def test_tile_and_digit_plans(T, V):
+    say(f"[csr] plan T={T} V={V}")
+    rng = np.random.default_rng(T + V)
+    s = rng.integers(0, V, T).astype(np.int32)
+    s[rng.random(T) < 0.3] = V - 1                # a hub at the top of the id range
+    s[rng.random(T) < 0.2] = V // 3
+    p = rng.integers(0, 7, T).astype(np.int32)
+    o = rng.integers(0, V, T).astype(np.int32)
+    st = new_status()
+    csr = rd.rdf2v_build_csr(to_dev(s), to_dev(p), to_dev(o), V, 7, status=st)
+    starts = rd.rdf2v_nonsink_starts(csr)
+    torch.cuda.synchronize()
+    assert int(st.item()) == 0
+    order = np.argsort(s, kind="stable")
+    assert np.array_equal(csr.edges.cpu().numpy(), np.stack([p[order], o[order]], axis=1))
+    degree = np.bincount(s, minlength=V)
+    row_ptr = np.zeros(V + 1, np.int64)
+    np.cumsum(degree, out=row_ptr[1:])
+    assert np.array_equal(csr.row_ptr.cpu().numpy(), row_ptr)
+    assert np.array_equal(starts.cpu().numpy(), np.flatnonzero(degree))
