@@ -21,6 +21,10 @@
 // What bounds a pass is HBM traffic (12 B read and written per triple), so the
 // sort takes as few passes as possible: digits of up to 10 bits, against a
 // tile of 8,192 triples that keeps the runs of a 1,024-bin pass at 8 triples.
+// 20M triples over 1M entities: two passes of 10 bits, 120 + 106 us of scatter
+// (4.0 TB/s), against 100 + 2 x 96 us for 7, 7 and 6 bits in 4,096-triple
+// tiles; with count, scan and row_ptr 322 us against 418. 500M over 50M: 9, 7
+// and 10 bits, 2.75 + 2.49 + 2.61 ms, against 10.1 ms in four passes.
 // The last pass sorts by the top digit, whose value follows from the position,
 // so it writes only the low 16 bits of the subjects (or none if there are no
 // lower bits).
@@ -305,6 +309,9 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(8)
   const int64_t base = tile * kTile;
   const int tile_n = int(min(int64_t(kTile), n - base));
 
+  // Inputs are read once, past the caches (non-temporal), which leaves L2 to
+  // the lines that neighbouring tiles fill together: 127 -> 120 and 119 -> 106
+  // us for the two passes over 20M triples.
   // The wave's keys are loaded together, with thread d's start of digit d among
   // the tiles and the digit's total; its payloads after the ranking (64
   // registers hold no more), in flight while the keys are written.
@@ -388,7 +395,8 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(8)
 // the scan of a histogram of the subjects; with more, the sorted subjects go
 // to keys_out for the row_ptr kernels. What bounds it is the chain of LDS
 // round trips and barriers; the passes as kernels of their own would be bound
-// by the gaps between thirteen launches (figures at launch_csr_build).
+// by the gaps between thirteen launches (5,000 triples over 1,000
+// entities: 14.6 us of kernel time in one launch, against 48 us in thirteen).
 // ---------------------------------------------------------------------------
 constexpr int kSmallEntities = kStageBytes<kMostRounds> / 4;
 
@@ -815,7 +823,7 @@ rdf2v_status launch_pass(const PassArgs &p, hipStream_t stream) {
   RDF2V_LAUNCH_CHECK();
   if (p.key_out == 4) launch_scatter<kFirst, kRounds, 4>(p, stream);
   else if (p.key_out == 2) launch_scatter<kFirst, kRounds, 2>(p, stream);
-  else launch_scatter<kFirst, kRounds, 0>(p, stream);
+  else if constexpr (kFirst) launch_scatter<kFirst, kRounds, 0>(p, stream);  // one pass in all
   RDF2V_LAUNCH_CHECK();
   return RDF2V_OK;
 }
