@@ -23,7 +23,9 @@
 //      global memory; equal tags are settled against the representative's
 //      bytes whenever the inline copy does not decide.
 //   Either pass lowers minpos (read first, atomicMin only if smaller) and
-//   parks the slot index in the id output.
+//   parks the slot index in the id output. Steps 3 to 5 run over both
+//   sequences in one launch each (sixteen launches became nine to eleven: the
+//   5,000-triple pipeline went from 206 to 177 us).
 //   3. mark_kernel: every used slot sets bit minpos of a bitset over the
 //      occurrences (the first occurrences of all strings) and writes minpos
 //      to a compact per-slot array.
@@ -178,12 +180,7 @@ __device__ __forceinline__ uint64_t hash_step(uint64_t h, uint64_t w) {
   return h ^ (h >> 29);
 }
 
-template <int kScope>
-__device__ __forceinline__ uint64_t load_u64(const uint64_t *p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, kScope);
-}
-
-constexpr int32_t kDeferred = -2;  // parked in the id output: left to the general pass
+constexpr int32_t kDeferred = -2;  // left to the general pass
 constexpr int kRegWords = 8;       // words of a string kept in registers and read with the key
 constexpr int kBatchPairs = 3;     // further pairs of inline words read together
 
@@ -343,10 +340,11 @@ __device__ __forceinline__ void stage_spans(const Seq &seq, const int64_t (&span
 // repeated within a block costs one lookup, so the slots of frequent strings
 // are not hammered by every occurrence. Occurrences whose strings are not
 // staged or too long for an inline copy, and lookups that were deferred, are
-// parked as kDeferred for the general pass.
+// left to the general pass as bits of `deferred`.
 template <bool kPaired, int kBlock, bool kGroupEqual, bool kWide>
 __global__ __launch_bounds__(kBlock) void insert_kernel(Seq seq, int64_t n, Slot *__restrict__ table,
-                                                        int64_t mask, int32_t *status) {
+                                                        int64_t mask, uint64_t *__restrict__ deferred,
+                                                        int32_t *status) {
   constexpr int kCols = kPaired ? 2 : 1;
   constexpr int kWords = kBlock * kStageWordsPerString;
   constexpr int kPerCol = kWords / kCols;  // includes kPad tail words
@@ -419,13 +417,13 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(Seq seq, int64_t n, Slot
   h = fmix64(h);
 
   int32_t *out = ((kPaired && col == 1) ? seq.out[kCols - 1] : seq.out[0]) + seq_row<kPaired>(q);
+  int32_t parked = kDeferred;
   if constexpr (!kGroupEqual) {
     if (fast) {
       const int32_t r = find_or_claim(table, mask, h, q, lds, at, len, wr);
       if (r == -1 && status != nullptr) atomicOr(status, RDF2V_STATUS_CAPACITY);
       *out = r;
-    } else if (active) {
-      *out = kDeferred;
+      parked = r;
     }
   } else {
     blk_hash[tid] = h;
@@ -468,8 +466,14 @@ __global__ __launch_bounds__(kBlock) void insert_kernel(Seq seq, int64_t n, Slot
       if (r == -1 && status != nullptr) atomicOr(status, RDF2V_STATUS_CAPACITY);
     }
     __syncthreads();
-    if (active) *out = fast ? loc_slot[e] : kDeferred;
+    if (fast) {
+      parked = loc_slot[e];
+      *out = parked;
+    }
   }
+  // One word per 64 occurrences says which of them the general pass takes.
+  const uint64_t left = __ballot(active && parked == kDeferred);
+  if (lane_id() == 0 && active) deferred[q >> 6] = left;
 }
 
 // Byte equality of two strings of the same length `len` in global memory.
@@ -483,25 +487,32 @@ __device__ __forceinline__ bool same_string_global(const StrCol *ca, int64_t sa,
 
 // General pass over the deferred occurrences (bad offsets, strings outside
 // their block's stage, strings too long for an inline copy, compares left
-// undecided): the same hash and table, with strings read from global memory,
-// table loads at agent scope, and equal tags settled against the
-// representative's bytes whenever the inline copy does not decide.
+// undecided): the same hash and table, with strings read from global memory
+// and equal tags settled against the representative's bytes whenever the
+// inline copy does not decide. A chain of dependent reads per occurrence, so
+// those of one step are in flight together. (Table loads at agent scope, which
+// go past L2, queue at the lines of frequent strings: 148 + 111 us on 20M
+// triples.)
+// Returns the slot (-1: the table is full), also left in the id output.
 template <bool kPaired>
-__global__ __launch_bounds__(kThreads) void insert_general_kernel(Seq seq, int64_t n, Slot *__restrict__ table,
-                                                                  int64_t mask, int32_t *status) {
-  const int64_t q = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-  if (q >= n) return;
+__device__ __forceinline__ int32_t insert_general(const Seq &seq, int64_t q, Slot *__restrict__ table, int64_t mask,
+                                               int32_t *status) {
   const int col = seq_col<kPaired>(q);
   int32_t *out = ((kPaired && col == 1) ? seq.out[1] : seq.out[0]) + seq_row<kPaired>(q);
-  if (*out != kDeferred) return;
   const StrCol cv = (kPaired && col == 1) ? seq.col[1] : seq.col[0];
   const StrCol *c = &cv;
   int bad = 0;
   int64_t start, len;
   string_range(*c, seq_row<kPaired>(q), start, len, bad);
   const int64_t words = (len + 6) / 7;
+  uint64_t wr[kRegWords];
+#pragma unroll
+  for (int i = 0; i < kRegWords; ++i) wr[i] = i < words ? word7_global(c, start, len, i) : 0;
   uint64_t h = hash_seed(len);
-  for (int64_t i = 0; i < words; ++i) h = hash_step(h, word7_global(c, start, len, i));
+#pragma unroll
+  for (int i = 0; i < kRegWords; ++i)
+    if (i < words) h = hash_step(h, wr[i]);
+  for (int64_t i = kRegWords; i < words; ++i) h = hash_step(h, word7_global(c, start, len, i));
   h = fmix64(h);
   const uint64_t ident = ((h >> 44) << 12) | uint64_t(min(len, kLenField));
   const uint64_t mine = (ident << 32) | uint32_t(q);
@@ -510,8 +521,14 @@ __global__ __launch_bounds__(kThreads) void insert_general_kernel(Seq seq, int64
   int64_t found = -1;
   for (int64_t probe = 0; probe <= mask; ++probe, s = (s + 1) & mask) {
     Slot *sl = table + s;
-    uint64_t k = load_u64<__HIP_MEMORY_SCOPE_AGENT>(&sl->key);
-    if (k == kEmpty) {
+    // Through the caches, as in the fast pass: what that pass wrote is visible
+    // here, and what this one adds is at worst seen as empty or unwritten.
+    const uint4 k4 = load16(&sl->key);
+    uint4 pr[kRegWords / 2];
+#pragma unroll
+    for (int j = 0; j < kRegWords / 2; ++j) pr[j] = 2 * j < nw ? load16(&sl->words[2 * j]) : make_uint4(0, 0, 0, 0);
+    uint64_t k = u64_of(k4.x, k4.y);
+    if (k4.x == 0xffffffffu || k4.y == 0xffffffffu) {  // empty, or seen while it changed
       const uint64_t prev = atomicCAS(reinterpret_cast<unsigned long long *>(&sl->key),
                                       static_cast<unsigned long long>(kEmpty),
                                       static_cast<unsigned long long>(mine));
@@ -527,15 +544,17 @@ __global__ __launch_bounds__(kThreads) void insert_general_kernel(Seq seq, int64
     if ((k >> 32) != ident) continue;
     int same = -1;
     if (nw >= 0) {
-      bool unwritten = false, differ = false;
-      for (int i = 0; i < nw && !differ; ++i) {
-        const uint64_t w = load_u64<__HIP_MEMORY_SCOPE_AGENT>(&sl->words[i]);
-        if ((w & ~kLow56) != kWritten)
-          unwritten = true;
-        else if (w != (word7_global(c, start, len, i) | kWritten))
-          differ = true;
+      int seen = 0;  // bit k set: some word had state k
+#pragma unroll
+      for (int j = 0; j < kRegWords / 2; ++j) {
+        if (2 * j < nw) seen |= 1 << word_state(u64_of(pr[j].x, pr[j].y), wr[2 * j]);
+        if (2 * j + 1 < nw) seen |= 1 << word_state(u64_of(pr[j].z, pr[j].w), wr[2 * j + 1]);
       }
-      same = differ ? 0 : (unwritten ? -1 : 1);
+      for (int i = kRegWords; i < nw && !(seen & 2); ++i) {
+        const uint4 v = load16(&sl->words[i & ~1]);
+        seen |= 1 << word_state((i & 1) ? u64_of(v.z, v.w) : u64_of(v.x, v.y), word7_global(c, start, len, i));
+      }
+      same = (seen & 2) ? 0 : ((seen & 4) ? -1 : 1);
     }
     if (same < 0) {
       const int64_t rep = int64_t(uint32_t(k));
@@ -554,121 +573,203 @@ __global__ __launch_bounds__(kThreads) void insert_general_kernel(Seq seq, int64
     *out = -1;
     if (status != nullptr) atomicOr(status, RDF2V_STATUS_CAPACITY);
   } else {
-    int32_t *mp = &table[found].minpos;
-    if (int32_t(q) < __hip_atomic_load(mp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(mp, int32_t(q));
     *out = int32_t(found);
   }
   if (bad && status != nullptr) atomicOr(status, RDF2V_STATUS_BAD_LENGTH);
+  return int32_t(found);
 }
 
-// One 16-byte store per thread, each workgroup writing 4 KiB: the table as 16-byte groups (a
-// slot is eight of them; its first holds key, minpos and spare), then the bitset, two words per
-// thread.
-__global__ __launch_bounds__(kThreads) void init_kernel(Slot *__restrict__ table, int64_t capacity,
-                                                        uint64_t *__restrict__ bits, int64_t words) {
-  constexpr int64_t kGroups = sizeof(Slot) / 16;
-  const int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-  const int64_t table_groups = capacity * kGroups;
-  if (i < table_groups) {
-    const uint4 v = (i % kGroups) == 0 ? make_uint4(0xffffffffu, 0xffffffffu, uint32_t(INT32_MAX), 0u)
-                                       : make_uint4(0u, 0u, 0u, 0u);
-    reinterpret_cast<uint4 *>(table)[i] = v;
-    return;
+// A wave takes the mask of 64 occurrences, clearing it (the masks become the
+// bitset of first occurrences), and ends if none was deferred. One mask per
+// wave: those of the first strings, which meet a table still being filled, are
+// full, and a wave with 64 masks in a row to hand out took 285 + 408 us on 20M
+// triples. A thread per occurrence that looked up its parked id and lowered
+// minpos itself: 131 + 84 us; this: 143 + 51 us, and 16 + 9 us on 5,000
+// triples against 25 + 12.
+template <bool kPaired>
+__global__ __launch_bounds__(kThreads) void insert_general_kernel(Seq seq, uint64_t *__restrict__ deferred,
+                                                                  int64_t words, Slot *__restrict__ table,
+                                                                  int64_t mask, int32_t *status) {
+  const int lane = lane_id();
+  const int64_t w = int64_t(uniform_u64((uint64_t(blockIdx.x) * kThreads + threadIdx.x) / kWave));
+  if (w >= words) return;
+  const uint64_t m = deferred[w];
+  if (m == 0) return;
+  if (lane == 0) deferred[w] = 0;
+  const int64_t q = w * 64 + lane;
+  int32_t slot = -1;
+  if ((m >> lane) & 1u) slot = insert_general<kPaired>(seq, q, table, mask, status);
+  // Of the lanes with one slot the first has the smallest occurrence: it alone
+  // lowers minpos (one update per occurrence queues at the frequent strings).
+  bool first = false;
+  for (uint64_t todo = __ballot(slot >= 0); todo != 0;) {
+    const int l = __builtin_ctzll(todo);
+    first = first || lane == l;
+    todo &= ~__ballot(slot == __builtin_amdgcn_readlane(slot, l));
   }
-  const int64_t w = 2 * (i - table_groups);
-  if (w < words) bits[w] = 0;
-  if (w + 1 < words) bits[w + 1] = 0;
+  if (first) {
+    int32_t *mp = &table[slot].minpos;
+    if (int32_t(q) < __hip_atomic_load(mp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(mp, int32_t(q));
+  }
+}
+
+// The passes below run over both sequences in one launch: the first workgroups
+// take the entities, the rest the predicates.
+struct RankSeq {
+  Slot *table;
+  int64_t capacity;
+  int64_t n;  // occurrences
+  int64_t words;
+  uint64_t *bits;
+  int32_t *prefix;
+  int32_t *ids;
+  int64_t *partials;
+  int64_t partial_blocks;
+  int64_t max_distinct;
+  int64_t *count_out;
+};
+struct RankPair {
+  RankSeq seq[2];
+  unsigned first_blocks;  // workgroups of sequence 0
+};
+struct SeqBlock {
+  int seq;
+  int64_t block;
+};
+__device__ __forceinline__ SeqBlock seq_block(unsigned first_blocks) {
+  return blockIdx.x < first_blocks ? SeqBlock{0, int64_t(blockIdx.x)} : SeqBlock{1, int64_t(blockIdx.x - first_blocks)};
+}
+
+// One 16-byte store per thread, each workgroup writing 4 KiB: the tables as
+// 16-byte groups (a slot is eight of them; its first holds key, minpos and
+// spare).
+__global__ __launch_bounds__(kThreads) void init_kernel(const RankPair pair) {
+  constexpr int64_t kGroups = sizeof(Slot) / 16;
+  const SeqBlock at = seq_block(pair.first_blocks);
+  const RankSeq &r = pair.seq[at.seq];
+  const int64_t i = at.block * kThreads + threadIdx.x;
+  if (i >= r.capacity * kGroups) return;
+  const uint4 v = (i % kGroups) == 0 ? make_uint4(0xffffffffu, 0xffffffffu, uint32_t(INT32_MAX), 0u)
+                                     : make_uint4(0u, 0u, 0u, 0u);
+  reinterpret_cast<uint4 *>(r.table)[i] = v;
 }
 
 // Every used slot's minpos was lowered by the thread that claimed it, so it is
 // an occurrence in [0, n); the range check only guards the bitset. The slot's
 // first occurrence (or -1 for an unused slot) also goes to the compact id
 // array, so that slot_id_kernel reads 4 bytes per slot instead of the table.
-__global__ __launch_bounds__(kThreads) void mark_kernel(const Slot *__restrict__ table, int64_t capacity,
-                                                        int64_t n, unsigned long long *__restrict__ bits,
-                                                        int32_t *__restrict__ ids) {
-  const int64_t s = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-  if (s >= capacity) return;
-  const uint4 k4 = load16(&table[s].key);
+__global__ __launch_bounds__(kThreads) void mark_kernel(const RankPair pair) {
+  const SeqBlock at = seq_block(pair.first_blocks);
+  const RankSeq &r = pair.seq[at.seq];
+  const int64_t s = at.block * kThreads + threadIdx.x;
+  if (s >= r.capacity) return;
+  const uint4 k4 = load16(&r.table[s].key);
   const int32_t m = int32_t(k4.z);
-  const bool used = u64_of(k4.x, k4.y) != kEmpty && m >= 0 && m < n;
-  ids[s] = used ? m : -1;
-  if (used) atomicOr(bits + (m >> 6), 1ull << (m & 63));
+  const bool used = u64_of(k4.x, k4.y) != kEmpty && m >= 0 && m < r.n;
+  r.ids[s] = used ? m : -1;
+  if (used) atomicOr(reinterpret_cast<unsigned long long *>(r.bits) + (m >> 6), 1ull << (m & 63));
 }
 
-__global__ __launch_bounds__(kThreads) void popc_count_kernel(const uint64_t *__restrict__ bits, int64_t words,
-                                                              int64_t *__restrict__ partials) {
+__global__ __launch_bounds__(kThreads) void popc_count_kernel(const RankPair pair) {
   __shared__ int64_t scratch[kThreads / kWave];
-  const int64_t base = int64_t(blockIdx.x) * kWordTile;
+  const SeqBlock at = seq_block(pair.first_blocks);
+  const RankSeq &r = pair.seq[at.seq];
+  const int64_t base = at.block * kWordTile;
   int64_t s = 0;
 #pragma unroll 4
   for (int i = 0; i < kWordsPerThread; ++i) {
     const int64_t w = base + int64_t(i) * kThreads + threadIdx.x;
-    if (w < words) s += __popcll(bits[w]);
+    if (w < r.words) s += __popcll(r.bits[w]);
   }
   const int64_t total = block_sum<kThreads, int64_t>(s, scratch);
-  if (threadIdx.x == 0) partials[blockIdx.x] = total;
+  if (threadIdx.x == 0) r.partials[at.block] = total;
 }
 
-// Exclusive scan of the block partials; the total is the number of distinct
-// strings, checked against the caller's bound.
-__global__ __launch_bounds__(kThreads) void popc_partials_kernel(int64_t *partials, int64_t nb, int64_t max_distinct,
-                                                                 int64_t *count_out, int32_t *status) {
+// The total number of distinct strings, checked against the caller's bound.
+__device__ __forceinline__ void write_distinct(const RankSeq &r, int64_t total, int32_t *status) {
+  *r.count_out = total;
+  if (total > r.max_distinct && status != nullptr) atomicOr(status, RDF2V_STATUS_CAPACITY);
+}
+
+// Exclusive scan of the block partials of sequence blockIdx.x.
+__global__ __launch_bounds__(kThreads) void popc_partials_kernel(const RankPair pair, int32_t *status) {
   __shared__ int64_t scratch[kThreads / kWave];
+  const RankSeq &r = pair.seq[blockIdx.x];
   int64_t carry = 0;
-  for (int64_t base = 0; base < nb; base += kThreads) {
+  for (int64_t base = 0; base < r.partial_blocks; base += kThreads) {
     const int64_t idx = base + threadIdx.x;
-    const int64_t x = idx < nb ? partials[idx] : 0;
+    const int64_t x = idx < r.partial_blocks ? r.partials[idx] : 0;
     int64_t tot;
     const int64_t ex = block_exclusive_scan<kThreads, int64_t>(x, scratch, tot);
-    if (idx < nb) partials[idx] = carry + ex;
+    if (idx < r.partial_blocks) r.partials[idx] = carry + ex;
     carry += tot;
   }
-  if (threadIdx.x == 0) {
-    *count_out = carry;
-    if (carry > max_distinct && status != nullptr) atomicOr(status, RDF2V_STATUS_CAPACITY);
-  }
+  if (threadIdx.x == 0) write_distinct(r, carry, status);
 }
 
-__global__ __launch_bounds__(kThreads) void word_prefix_kernel(const uint64_t *__restrict__ bits, int64_t words,
-                                                               const int64_t *__restrict__ partials,
-                                                               int32_t *__restrict__ prefix) {
-  __shared__ int32_t scratch[kThreads / kWave];
-  const int64_t base = int64_t(blockIdx.x) * kWordTile;
-  int32_t carry = int32_t(partials[blockIdx.x]);
-  for (int i = 0; i < kWordsPerThread; ++i) {
-    const int64_t round0 = base + int64_t(i) * kThreads;
-    if (round0 >= words) break;  // uniform across the block
-    const int64_t w = round0 + threadIdx.x;
-    const int32_t x = w < words ? __popcll(bits[w]) : 0;
+// Prefix of the words [base, end) from `carry` on, NT at a time; returns the new carry.
+template <int NT>
+__device__ __forceinline__ int32_t prefix_words(const RankSeq &r, int64_t base, int64_t end, int32_t carry,
+                                                int32_t *scratch) {
+  for (; base < end; base += NT) {  // uniform across the block
+    const int64_t w = base + threadIdx.x;
+    const int32_t x = w < end ? __popcll(r.bits[w]) : 0;
     int32_t tot;
-    const int32_t ex = block_exclusive_scan<kThreads, int32_t>(x, scratch, tot);
-    if (w < words) prefix[w] = carry + ex;
+    const int32_t ex = block_exclusive_scan<NT, int32_t>(x, scratch, tot);
+    if (w < end) r.prefix[w] = carry + ex;
     carry += tot;
   }
+  return carry;
+}
+
+__global__ __launch_bounds__(kThreads) void word_prefix_kernel(const RankPair pair) {
+  __shared__ int32_t scratch[kThreads / kWave];
+  const SeqBlock at = seq_block(pair.first_blocks);
+  const RankSeq &r = pair.seq[at.seq];
+  const int64_t base = at.block * kWordTile;
+  prefix_words<kThreads>(r, base, min(base + kWordTile, r.words), int32_t(r.partials[at.block]), scratch);
+}
+
+// popc_count, popc_partials and word_prefix in one launch, a workgroup per
+// sequence, where each has at most one tile of words: more would make one
+// workgroup's rounds longer than the two launches that this saves.
+constexpr int kSmallPrefixThreads = 1024;
+__global__ __launch_bounds__(kSmallPrefixThreads) void small_prefix_kernel(const RankPair pair, int32_t *status) {
+  __shared__ int32_t scratch[kSmallPrefixThreads / kWave];
+  const RankSeq &r = pair.seq[blockIdx.x];
+  const int32_t total = prefix_words<kSmallPrefixThreads>(r, 0, r.words, 0, scratch);
+  if (threadIdx.x == 0) write_distinct(r, total, status);
 }
 
 // The id of a used slot: the rank of its first occurrence among all first
 // occurrences (the compact array holds that occurrence, or -1).
-__global__ __launch_bounds__(kThreads) void slot_id_kernel(int64_t capacity, const uint64_t *__restrict__ bits,
-                                                           const int32_t *__restrict__ prefix,
-                                                           int32_t *__restrict__ ids) {
-  const int64_t s = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-  if (s >= capacity) return;
-  const int32_t m = ids[s];
+__global__ __launch_bounds__(kThreads) void slot_id_kernel(const RankPair pair) {
+  const SeqBlock at = seq_block(pair.first_blocks);
+  const RankSeq &r = pair.seq[at.seq];
+  const int64_t s = at.block * kThreads + threadIdx.x;
+  if (s >= r.capacity) return;
+  const int32_t m = r.ids[s];
   if (m < 0) return;
   const int64_t w = m >> 6;
   const uint64_t below = (uint64_t(1) << (m & 63)) - 1;
-  ids[s] = prefix[w] + __popcll(bits[w] & below);
+  r.ids[s] = r.prefix[w] + __popcll(r.bits[w] & below);
 }
 
-template <bool kPaired>
-__global__ __launch_bounds__(kThreads) void assign_kernel(Seq seq, int64_t n, const int32_t *__restrict__ ids) {
-  const int64_t q = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-  if (q >= n) return;
-  int32_t *out = seq.out[seq_col<kPaired>(q)] + seq_row<kPaired>(q);
-  const int32_t s = *out;
-  if (s >= 0) *out = ids[s];
+// Parked slots to ids in the three output columns (the predicates' slots in
+// the second array). The columns stream past the caches, which are left to the
+// id arrays.
+__global__ __launch_bounds__(kThreads) void assign_kernel(int32_t *__restrict__ subj, int32_t *__restrict__ obj,
+                                                          int32_t *__restrict__ pred, int64_t n,
+                                                          const int32_t *__restrict__ ent_ids,
+                                                          const int32_t *__restrict__ pred_ids) {
+  const int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x;
+  if (i >= n) return;
+  const int32_t s = __builtin_nontemporal_load(subj + i), o = __builtin_nontemporal_load(obj + i),
+                p = __builtin_nontemporal_load(pred + i);
+  const int32_t s_id = s >= 0 ? ent_ids[s] : s, o_id = o >= 0 ? ent_ids[o] : o, p_id = p >= 0 ? pred_ids[p] : p;
+  __builtin_nontemporal_store(s_id, subj + i);
+  __builtin_nontemporal_store(o_id, obj + i);
+  __builtin_nontemporal_store(p_id, pred + i);
 }
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -704,54 +805,34 @@ SeqPlan plan_seq(int64_t n, int64_t max_distinct, size_t at) {
   return p;
 }
 
+RankSeq rank_seq(const SeqPlan &p, int64_t max_distinct, char *ws, int64_t *count_out) {
+  return {reinterpret_cast<Slot *>(ws + p.table_off),      p.capacity,
+          p.n,                                             p.words,
+          reinterpret_cast<uint64_t *>(ws + p.bits_off),   reinterpret_cast<int32_t *>(ws + p.prefix_off),
+          reinterpret_cast<int32_t *>(ws + p.ids_off),     reinterpret_cast<int64_t *>(ws + p.partials_off),
+          p.blocks,                                        max_distinct,
+          count_out};
+}
+
+// The fast pass, then the general pass, of one sequence (the table initialised).
 template <bool kPaired>
-rdf2v_status run_seq(const Seq &seq, const SeqPlan &p, int64_t max_distinct, char *ws, int64_t *count_out,
-                     int32_t *status, hipStream_t stream) {
-  Slot *table = reinterpret_cast<Slot *>(ws + p.table_off);
-  int32_t *ids = reinterpret_cast<int32_t *>(ws + p.ids_off);
-  uint64_t *bits = reinterpret_cast<uint64_t *>(ws + p.bits_off);
-  int32_t *prefix = reinterpret_cast<int32_t *>(ws + p.prefix_off);
-  int64_t *partials = reinterpret_cast<int64_t *>(ws + p.partials_off);
-  const int64_t init_items = p.capacity * int64_t(sizeof(Slot) / 16) + ceil_div(p.words, 2);
-  init_kernel<<<dim3(unsigned(ceil_div(init_items, kThreads))), dim3(kThreads), 0, stream>>>(table, p.capacity,
-                                                                                            bits, p.words);
+rdf2v_status insert_seq(const Seq &seq, const RankSeq &r, int32_t *status, hipStream_t stream) {
+  // Entities are mostly distinct within a block, predicates mostly repeated:
+  // group equal strings only where that saves lookups.
+  constexpr int kFastBlock = kPaired ? kFastBlockEntities : kFastBlockPredicates;
+  const dim3 grid(unsigned(ceil_div(r.n, kFastBlock)));
+  bool wide = true;  // every column's bytes start 16-byte aligned
+  for (const StrCol &c : seq.col) wide = wide && (reinterpret_cast<uintptr_t>(c.chars) & 15) == 0;
+  if (wide)
+    insert_kernel<kPaired, kFastBlock, !kPaired, true><<<grid, dim3(kFastBlock), 0, stream>>>(
+        seq, r.n, r.table, r.capacity - 1, r.bits, status);
+  else
+    insert_kernel<kPaired, kFastBlock, !kPaired, false><<<grid, dim3(kFastBlock), 0, stream>>>(
+        seq, r.n, r.table, r.capacity - 1, r.bits, status);
   RDF2V_LAUNCH_CHECK();
-  const unsigned occ_blocks = unsigned(ceil_div(p.n, kThreads));
-  const unsigned slot_blocks = unsigned(ceil_div(p.capacity, kThreads));
-  if (p.n > 0) {
-    // Entities are mostly distinct within a block, predicates mostly repeated:
-    // group equal strings only where that saves lookups.
-    constexpr int kFastBlock = kPaired ? kFastBlockEntities : kFastBlockPredicates;
-    const dim3 grid(unsigned(ceil_div(p.n, kFastBlock)));
-    bool wide = true;  // every column's bytes start 16-byte aligned
-    for (const StrCol &c : seq.col) wide = wide && (reinterpret_cast<uintptr_t>(c.chars) & 15) == 0;
-    if (wide)
-      insert_kernel<kPaired, kFastBlock, !kPaired, true><<<grid, dim3(kFastBlock), 0, stream>>>(seq, p.n, table,
-                                                                                             p.capacity - 1, status);
-    else
-      insert_kernel<kPaired, kFastBlock, !kPaired, false><<<grid, dim3(kFastBlock), 0, stream>>>(seq, p.n, table,
-                                                                                              p.capacity - 1, status);
-    RDF2V_LAUNCH_CHECK();
-    insert_general_kernel<kPaired><<<dim3(occ_blocks), dim3(kThreads), 0, stream>>>(seq, p.n, table,
-                                                                                   p.capacity - 1, status);
-    RDF2V_LAUNCH_CHECK();
-    mark_kernel<<<dim3(slot_blocks), dim3(kThreads), 0, stream>>>(
-        table, p.capacity, p.n, reinterpret_cast<unsigned long long *>(bits), ids);
-    RDF2V_LAUNCH_CHECK();
-    popc_count_kernel<<<dim3(unsigned(p.blocks)), dim3(kThreads), 0, stream>>>(bits, p.words, partials);
-    RDF2V_LAUNCH_CHECK();
-  }
-  popc_partials_kernel<<<dim3(1), dim3(kThreads), 0, stream>>>(partials, p.blocks, max_distinct, count_out,
-                                                               status);
+  insert_general_kernel<kPaired><<<dim3(unsigned(ceil_div(r.n, kThreads))), dim3(kThreads), 0, stream>>>(
+      seq, r.bits, r.words, r.table, r.capacity - 1, status);
   RDF2V_LAUNCH_CHECK();
-  if (p.n > 0) {
-    word_prefix_kernel<<<dim3(unsigned(p.blocks)), dim3(kThreads), 0, stream>>>(bits, p.words, partials, prefix);
-    RDF2V_LAUNCH_CHECK();
-    slot_id_kernel<<<dim3(slot_blocks), dim3(kThreads), 0, stream>>>(p.capacity, bits, prefix, ids);
-    RDF2V_LAUNCH_CHECK();
-    assign_kernel<kPaired><<<dim3(occ_blocks), dim3(kThreads), 0, stream>>>(seq, p.n, ids);
-    RDF2V_LAUNCH_CHECK();
-  }
   return RDF2V_OK;
 }
 
@@ -782,9 +863,41 @@ rdf2v_status launch_build_vocabulary(const VocabColumns &cols, int64_t num_tripl
           {subj_ids, obj_ids}};
   Seq pred{{{cols.chars[1], cols.offsets[1], cols.bytes[1]}, {cols.chars[1], cols.offsets[1], cols.bytes[1]}},
            {pred_ids, pred_ids}};
-  const rdf2v_status st = run_seq<true>(ent, plan.ent, max_entities, ws, counts_out, status_dev, stream);
+  RankPair pair{{rank_seq(plan.ent, max_entities, ws, counts_out), rank_seq(plan.pred, max_predicates, ws, counts_out + 1)}, 0};
+  // Launches `kernel` with a workgroup per `per` of the two amounts.
+  auto both = [&](auto kernel, int64_t ent, int64_t pred, int64_t per) -> rdf2v_status {
+    pair.first_blocks = unsigned(ceil_div(ent, per));
+    kernel<<<dim3(pair.first_blocks + unsigned(ceil_div(pred, per))), dim3(kThreads), 0, stream>>>(pair);
+    RDF2V_LAUNCH_CHECK();
+    return RDF2V_OK;
+  };
+  rdf2v_status st = RDF2V_OK;
+  if (num_triples > 0) {
+    constexpr int64_t kGroups = sizeof(Slot) / 16;
+    st = both(init_kernel, plan.ent.capacity * kGroups, plan.pred.capacity * kGroups, kThreads);
+    if (st == RDF2V_OK) st = insert_seq<true>(ent, pair.seq[0], status_dev, stream);
+    if (st == RDF2V_OK) st = insert_seq<false>(pred, pair.seq[1], status_dev, stream);
+    if (st == RDF2V_OK) st = both(mark_kernel, plan.ent.capacity, plan.pred.capacity, kThreads);
+    if (st != RDF2V_OK) return st;
+  }
+  if (plan.ent.words <= kWordTile) {
+    small_prefix_kernel<<<dim3(2), dim3(kSmallPrefixThreads), 0, stream>>>(pair, status_dev);
+    RDF2V_LAUNCH_CHECK();
+    if (num_triples == 0) return RDF2V_OK;
+  } else {
+    st = both(popc_count_kernel, plan.ent.words, plan.pred.words, kWordTile);
+    if (st != RDF2V_OK) return st;
+    popc_partials_kernel<<<dim3(2), dim3(kThreads), 0, stream>>>(pair, status_dev);
+    RDF2V_LAUNCH_CHECK();
+    st = both(word_prefix_kernel, plan.ent.words, plan.pred.words, kWordTile);
+    if (st != RDF2V_OK) return st;
+  }
+  st = both(slot_id_kernel, plan.ent.capacity, plan.pred.capacity, kThreads);
   if (st != RDF2V_OK) return st;
-  return run_seq<false>(pred, plan.pred, max_predicates, ws, counts_out + 1, status_dev, stream);
+  assign_kernel<<<dim3(unsigned(ceil_div(num_triples, kThreads))), dim3(kThreads), 0, stream>>>(
+      subj_ids, obj_ids, pred_ids, num_triples, pair.seq[0].ids, pair.seq[1].ids);
+  RDF2V_LAUNCH_CHECK();
+  return RDF2V_OK;
 }
 
 }  // namespace rdf2v
