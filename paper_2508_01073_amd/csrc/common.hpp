@@ -27,6 +27,21 @@ __host__ __device__ inline size_t align_up(size_t x, size_t a) { return (x + a -
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 __device__ __forceinline__ uint64_t lanes_below(int lane) { return (uint64_t(1) << lane) - 1; }
 
+// Inclusive prefix sum over the 64 lanes of a wave with DPP moves: shifts by
+// 1, 2, 4 and 8 lanes inside each row of 16, then the last lane of row 0 and of
+// row 2 added to rows 1 and 3, then the last lane of row 1 added to rows 2 and
+// 3 (the row-broadcast scan of AMD's GCN cross-lane notes). Lanes with no
+// source lane or in masked rows add 0.
+__device__ __forceinline__ int32_t wave_inclusive_sum(int32_t x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
 // Exclusive scan of one value per thread over a block of NT threads (NT a
 // multiple of 64, at most 1024). `scratch` holds NT/64 values of LDS. Returns
 // the thread's exclusive prefix; `total` receives the block-wide sum. Contains

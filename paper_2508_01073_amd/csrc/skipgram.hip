@@ -7,10 +7,11 @@
 // by walk, then i, then j.
 //
 // The number of pairs of a walk is a closed form of L and the window, so the
-// output offsets of all walks are one exclusive scan (int64: a corpus easily
-// exceeds 2^31 pairs) and the emit kernel needs no atomics: one thread per
-// (walk, center) computes where its pairs start, again in closed form, and
-// places them. Pure integer streaming work, bound by HBM writes.
+// output offsets are one exclusive scan and the emit kernels need no atomics: a
+// block of them takes a few walks, learns its first output from the scan of the
+// blocks' counts (int64: a corpus easily exceeds 2^31 pairs), and its walks'
+// and centers' places follow in closed form. Pure integer streaming work, bound
+// by HBM writes.
 //
 // CBOW (Sec. 3.2: the library trains Continuous Bag of Words next to
 // Skip-Gram; it predicts a center token from the tokens around it) takes one
@@ -31,17 +32,21 @@ typedef int32_t v2i32 __attribute__((ext_vector_type(2)));
 typedef int32_t v4i32 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
-constexpr int kItems = 16;
-constexpr int kTile = kThreads * kItems;  // walks per scan block
+constexpr int kCountThreads = 1024;  // emit blocks counted per workgroup
+
+// All arithmetic inside a block is 32-bit: a walk has at most 129 tokens, a
+// block at most 32,768 items, and the window is clamped to the row (a wider
+// one reaches no further).
+__device__ __forceinline__ int32_t clamp_window(int32_t window, int32_t width) { return min(window, width); }
 
 // Pairs of a walk with L valid tokens: 2 * sum_{d=1}^{m} (L - d), m = min(window, L - 1).
-__device__ __forceinline__ int64_t walk_pairs(int64_t L, int64_t window) {
-  const int64_t m = min(window, L - 1);
-  return m <= 0 ? 0 : 2 * (m * L - m * (m + 1) / 2);
+__device__ __forceinline__ int32_t walk_pairs(int32_t L, int32_t window) {
+  const int32_t m = min(window, L - 1);
+  return m <= 0 ? 0 : m * (2 * L - m - 1);
 }
 
 // sum_{k=0}^{n-1} min(k, window)
-__device__ __forceinline__ int64_t capped_prefix(int64_t n, int64_t window) {
+__device__ __forceinline__ int32_t capped_prefix(int32_t n, int32_t window) {
   if (n <= 0) return 0;
   if (n <= window + 1) return n * (n - 1) / 2;
   return window * (window + 1) / 2 + (n - 1 - window) * window;
@@ -49,13 +54,12 @@ __device__ __forceinline__ int64_t capped_prefix(int64_t n, int64_t window) {
 
 // Training items of one walk of L valid tokens: pairs, or CBOW examples.
 template <bool kCbow>
-__device__ __forceinline__ int64_t walk_items(int64_t L, int64_t window) {
+__device__ __forceinline__ int32_t walk_items(int32_t L, int32_t window) {
   return kCbow ? L : walk_pairs(L, window);
 }
 
-// Valid length of walk r, clamped to the row; out-of-range lengths raise a flag.
-__device__ __forceinline__ int32_t clamped_len(const int32_t *len, int64_t r, int32_t width, int &bad) {
-  const int32_t L = len[r];
+// A walk's length, clamped to the row; out-of-range lengths raise a flag.
+__device__ __forceinline__ int32_t clamped(int32_t L, int32_t width, int &bad) {
   if (L < 0 || L > width) {
     bad = 1;
     return L < 0 ? 0 : width;
@@ -63,303 +67,247 @@ __device__ __forceinline__ int32_t clamped_len(const int32_t *len, int64_t r, in
   return L;
 }
 
+// Where the emit blocks' outputs begin: the items of `walks` consecutive walks
+// (one emit block) per thread, their exclusive prefix inside the workgroup to
+// firsts, the workgroup's total to partials. A lone workgroup also writes what
+// partials_scan_kernel would.
 template <bool kCbow>
-__global__ __launch_bounds__(kThreads) void pair_count_reduce_kernel(const int32_t *__restrict__ len,
-                                                                     int64_t n, int32_t width,
-                                                                     int32_t window,
-                                                                     int64_t *__restrict__ partials,
-                                                                     int32_t *status) {
-  __shared__ int64_t scratch[kThreads / kWave];
-  const int64_t base = int64_t(blockIdx.x) * kTile;
-  int64_t s = 0;
+__global__ __launch_bounds__(kCountThreads) void item_count_kernel(const int32_t *__restrict__ len, int64_t n,
+                                                                   int32_t width, int32_t window, int32_t walks,
+                                                                   int64_t emit_blocks, int32_t *__restrict__ firsts,
+                                                                   int64_t *__restrict__ partials, int64_t *total_out,
+                                                                   int32_t *status) {
+  __shared__ int32_t scratch[kCountThreads / kWave];
+  const int64_t b = int64_t(blockIdx.x) * kCountThreads + threadIdx.x;
+  const int32_t w = clamp_window(window, width);
+  constexpr int32_t kAhead = 8;  // lengths of a thread in flight together
+  int32_t s = 0;
   int bad = 0;
-#pragma unroll 4
-  for (int i = 0; i < kItems; ++i) {
-    const int64_t r = base + int64_t(i) * kThreads + threadIdx.x;
-    if (r < n) s += walk_items<kCbow>(clamped_len(len, r, width, bad), window);
+  if (b < emit_blocks) {
+    const int64_t r0 = b * walks;
+    const int32_t rows = int32_t(min(int64_t(walks), n - r0));
+    for (int32_t i0 = 0; i0 < rows; i0 += kAhead) {
+      int32_t L[kAhead];
+#pragma unroll
+      for (int32_t k = 0; k < kAhead; ++k) L[k] = i0 + k < rows ? len[r0 + i0 + k] : 0;
+#pragma unroll
+      for (int32_t k = 0; k < kAhead; ++k) s += walk_items<kCbow>(clamped(L[k], width, bad), w);
+    }
   }
-  const int64_t total = block_sum<kThreads, int64_t>(s, scratch);
-  if (threadIdx.x == 0) partials[blockIdx.x] = total;
+  int32_t total;
+  const int32_t ex = block_exclusive_scan<kCountThreads>(s, scratch, total);
+  if (b < emit_blocks) firsts[b] = ex;
+  if (threadIdx.x == 0) {
+    partials[blockIdx.x] = gridDim.x == 1 ? 0 : total;
+    if (gridDim.x == 1) *total_out = total;
+  }
   if (bad && status != nullptr) atomicOr(status, RDF2V_STATUS_BAD_LENGTH);
 }
 
-// One block: exclusive scan of the block sums in place; the total goes to *total_out.
-__global__ __launch_bounds__(kThreads) void pair_partials_kernel(int64_t *partials, int64_t nb,
-                                                                 int64_t *total_out) {
-  __shared__ int64_t scratch[kThreads / kWave];
+// One block: exclusive scan of the workgroup totals in place; the sum goes to *total_out.
+__global__ __launch_bounds__(kCountThreads) void partials_scan_kernel(int64_t *partials, int64_t nb,
+                                                                      int64_t *total_out) {
+  __shared__ int64_t scratch[kCountThreads / kWave];
   int64_t carry = 0;
-  for (int64_t base = 0; base < nb; base += kThreads) {
+  for (int64_t base = 0; base < nb; base += kCountThreads) {
     const int64_t idx = base + threadIdx.x;
     const int64_t x = idx < nb ? partials[idx] : 0;
     int64_t tot;
-    const int64_t ex = block_exclusive_scan<kThreads, int64_t>(x, scratch, tot);
+    const int64_t ex = block_exclusive_scan<kCountThreads, int64_t>(x, scratch, tot);
     if (idx < nb) partials[idx] = carry + ex;
     carry += tot;
   }
-  if (threadIdx.x == 0) {
-    partials[nb] = carry;
-    *total_out = carry;
-  }
+  if (threadIdx.x == 0) *total_out = carry;
 }
 
-template <bool kCbow>
-__global__ __launch_bounds__(kThreads) void pair_offsets_kernel(const int32_t *__restrict__ len, int64_t n,
-                                                                int32_t width, int32_t window,
-                                                                const int64_t *__restrict__ partials,
-                                                                int64_t *__restrict__ offsets) {
-  __shared__ int64_t scratch[kThreads / kWave];
-  const int64_t base = int64_t(blockIdx.x) * kTile;
-  int64_t carry = partials[blockIdx.x];
-  int bad = 0;
-  for (int i = 0; i < kItems; ++i) {
-    const int64_t r = base + int64_t(i) * kThreads + threadIdx.x;
-    const int64_t x = r < n ? walk_items<kCbow>(clamped_len(len, r, width, bad), window) : 0;
-    int64_t tot;
-    const int64_t ex = block_exclusive_scan<kThreads, int64_t>(x, scratch, tot);
-    if (r < n) offsets[r] = carry + ex;
-    carry += tot;
-  }
+// What an emit block works on, shared by the emit kernels: its walk rows and,
+// per walk, the valid length and where its items begin inside the block.
+template <int kBlock>
+struct BlockWalks {
+  int32_t rows[kBlock];
+  int32_t lens[kBlock];
+  int32_t firsts[kBlock];
+  int32_t scan[kBlock / kWave];
+};
+
+struct EmitArgs {
+  const int32_t *tokens;
+  const int32_t *len;
+  int64_t n;
+  int32_t width, window;
+  int32_t walks;              // per emit block: kBlock / width
+  uint32_t width_inverse;     // ceil(2^32 / width); 0 for width 1
+  const int32_t *firsts;
+  const int64_t *partials;
+  int64_t capacity;
+  int32_t *status;
+};
+
+// t / width for t below the block size.
+__device__ __forceinline__ int32_t walk_of(const EmitArgs &a, int32_t t) {
+  return a.width == 1 ? t : int32_t(__umulhi(uint32_t(t), a.width_inverse));
 }
 
-// One thread per (walk, center); walks_per_block = kBlock / width walks per
-// block, whose rows are contiguous in the input and whose pairs form one
-// contiguous output range. With kStage, the block first copies its rows to LDS
-// with one coalesced load, the threads place their pairs in an LDS stage sized
-// at launch to the block's most pairs (dynamic LDS), and the block streams the
-// range out with consecutive, non-temporal 16-byte stores; otherwise each
-// thread reads its row from global memory and writes its pairs directly.
-
-template <bool kStage, int kBlock>
-__global__ __launch_bounds__(kBlock) void pair_emit_kernel(const int32_t *__restrict__ tokens,
-                                                             const int32_t *__restrict__ len, int64_t n,
-                                                             int32_t width, int32_t window,
-                                                             const int64_t *__restrict__ offsets,
-                                                             int2 *__restrict__ pairs, int64_t capacity,
-                                                             int32_t *status) {
-  extern __shared__ int2 stage[];                // kStage: the block's pairs
-  __shared__ int32_t rows[kStage ? kBlock : 1];  // the block's walk rows, walks_per_block * width tokens
-  const int walks_per_block = kBlock / width;
-  const int t = threadIdx.x;
-  const int64_t r0 = int64_t(blockIdx.x) * walks_per_block;
-  const int64_t r_end = min(n, r0 + walks_per_block);
-  const int64_t r = r0 + t / width;
-  const int64_t i = t % width;
-  const bool active = t < walks_per_block * width && r < n;
-  int bad = 0;
-  const int64_t w = window;
-  const int64_t block_first = offsets[r0];
-  int64_t first = 0, L = 0;
-  if (active) {
-    L = clamped_len(len, r, width, bad);
-    first = offsets[r] + capped_prefix(i, w) + capped_prefix(L, w) - capped_prefix(L - i, w);
-  }
-  // The block's pairs end where the next block's begin: the offset of walk
-  // r_end, or the pair count of the last walk added to its offset.
-  __shared__ int64_t block_end;
-  if (kStage) {
-    const int64_t span = (r_end - r0) * width;  // <= kBlock
-    if (t < span) rows[t] = tokens[r0 * width + t];
-    if (t == 0) {
-      if (r_end < n) {
-        block_end = offsets[r_end];
-      } else {
-        int b2 = 0;
-        block_end = offsets[n - 1] + walk_pairs(clamped_len(len, n - 1, width, b2), w);
-      }
-    }
+// Fills s for block blockIdx.x (every global read of the block is issued
+// before the first barrier), ends with a barrier, and returns the number of
+// the block's items; first: the first of them in the output.
+template <bool kCbow, int kBlock>
+__device__ __forceinline__ int32_t load_walks(const EmitArgs &a, BlockWalks<kBlock> &s, int64_t &first) {
+  const int32_t t = threadIdx.x;
+  const int64_t r0 = int64_t(blockIdx.x) * a.walks;
+  const int32_t walks = int32_t(min(int64_t(a.walks), a.n - r0));
+  first = a.partials[blockIdx.x / kCountThreads] + a.firsts[blockIdx.x];
+  int bad = 0;  // reported by the count
+  const int32_t token = t < walks * a.width ? a.tokens[r0 * a.width + t] : 0;
+  const int32_t L = t < walks ? clamped(a.len[r0 + t], a.width, bad) : 0;
+  const int32_t items = walk_items<kCbow>(L, clamp_window(a.window, a.width));
+  s.rows[t] = token;
+  s.lens[t] = L;
+  int32_t total;
+  if (kBlock == kWave || a.walks <= kWave) {  // uniform: the first wave holds every walk
+    const int32_t v = wave_inclusive_sum(items);
+    if (t < kWave) s.firsts[t] = v - items;
+    if (t == kWave - 1) s.scan[0] = v;
+    __syncthreads();
+    total = s.scan[0];
+  } else {
+    s.firsts[t] = block_exclusive_scan<kBlock>(items, s.scan, total);
     __syncthreads();
   }
-  bool full = false;
-  if (active && i < L) {
-    const int32_t *row = kStage ? rows + (t / width) * width : tokens + r * width;
+  return total;
+}
+
+// Streams ints [shift, shift + total) of an LDS stage to dst and on, where
+// shift is dst's offset from 128-byte alignment in ints: the stage has the same
+// offset, so what lies between the ends are 16-byte loads from LDS and 16-byte
+// non-temporal stores, and every wave's store covers whole 128-byte lines
+// (8M walks of 17 tokens, window 5: pairs 2.00 -> 1.69 ms, 4M: CBOW 0.63 -> 0.58
+// ms against alignment to 16 bytes; plain stores 1.62 and 0.74).
+constexpr int kLineInts = 32;
+template <int kBlock>
+__device__ __forceinline__ void stream_out(const int32_t *stage, int32_t shift, int32_t *dst, int32_t total) {
+  const int32_t t = threadIdx.x;
+  int32_t *base = dst - shift;
+  const int32_t end = shift + total;
+  const int32_t g0 = (shift + 3) >> 2, g1 = end >> 2;  // whole groups of four ints
+  const v4i32 *src4 = reinterpret_cast<const v4i32 *>(stage);
+  v4i32 *dst4 = reinterpret_cast<v4i32 *>(base);
+  for (int32_t g = t; g < g1; g += kBlock)
+    if (g >= g0) __builtin_nontemporal_store(src4[g], dst4 + g);
+  // the ints before the first and behind the last of them
+  if (t < 8) {
+    const int32_t q = t < 4 ? 4 * g0 - 4 + t : 4 * max(g0, g1) + (t - 4);
+    if (q >= shift && q < end) __builtin_nontemporal_store(stage[q], base + q);
+  }
+}
+__device__ __forceinline__ int32_t int_shift(const void *p) {
+  return int32_t((reinterpret_cast<uintptr_t>(p) & (4 * kLineInts - 1)) >> 2);
+}
+
+// Pairs: one thread per (walk, center). With kStage the threads place their
+// pairs in an LDS stage sized at launch to the block's most pairs (dynamic
+// LDS), and the block streams its contiguous range out; otherwise each thread
+// writes its pairs directly.
+template <bool kStage, int kBlock>
+__global__ __launch_bounds__(kBlock) void pair_emit_kernel(const EmitArgs a, int2 *__restrict__ pairs) {
+  extern __shared__ __align__(16) int2 stage[];  // kStage: the block's pairs, from the offset of its range on
+  __shared__ BlockWalks<kBlock> s;
+  const int32_t t = threadIdx.x;
+  const int32_t w = clamp_window(a.window, a.width);
+  int64_t block_first;
+  const int32_t total = load_walks<false>(a, s, block_first);
+  const int64_t room = max(int64_t(0), a.capacity - block_first);
+  int2 *dst = pairs + block_first;
+  const int32_t shift = kStage ? int_shift(dst) : 0;
+  const int32_t k_walk = walk_of(a, t), i = t - k_walk * a.width;
+  // threads past the last walk (s.lens is 0 there) and past a walk's end have no center
+  if (k_walk < a.walks && i < s.lens[k_walk]) {
+    const int32_t L = s.lens[k_walk];
+    const int32_t *row = s.rows + k_walk * a.width;
     const int32_t center = row[i];
-    const int64_t j0 = max(int64_t(0), i - w), j1 = min(L - 1, i + w);
-    int64_t k = first;
-    for (int64_t j = j0; j <= j1; ++j) {
+    int32_t k = s.firsts[k_walk] + capped_prefix(i, w) + capped_prefix(L, w) - capped_prefix(L - i, w);
+    const int32_t j0 = max(0, i - w), j1 = min(L - 1, i + w);
+    int2 *out = stage + (shift >> 1);
+    for (int32_t j = j0; j <= j1; ++j) {
       if (j == i) continue;
       const int2 pr = make_int2(center, row[j]);
       if (kStage) {
-        stage[k - block_first] = pr;
-      } else if (k < capacity) {
-        __builtin_nontemporal_store(v2i32{pr.x, pr.y}, reinterpret_cast<v2i32 *>(pairs + k));
-      } else {
-        full = true;
+        out[k] = pr;
+      } else if (k < room) {
+        __builtin_nontemporal_store(v2i32{pr.x, pr.y}, reinterpret_cast<v2i32 *>(dst + k));
       }
       ++k;
     }
   }
   if (kStage) {
     __syncthreads();
-    const int64_t cnt = block_end - block_first;
-    if (block_end > capacity) full = true;
-    const int64_t lim = min(cnt, capacity - block_first);  // pairs of this block that fit
-    // One leading pair if the range does not start 16-byte aligned, then two
-    // pairs per 16-byte store, then a possible trailing pair.
-    const int64_t head = (reinterpret_cast<uintptr_t>(pairs + block_first) & 15) ? 1 : 0;
-    if (t == 0 && head && lim > 0)
-      __builtin_nontemporal_store(v2i32{stage[0].x, stage[0].y}, reinterpret_cast<v2i32 *>(pairs + block_first));
-    const int64_t body = lim > head ? (lim - head) >> 1 : 0;
-    v4i32 *dst = reinterpret_cast<v4i32 *>(pairs + block_first + head);
-    for (int64_t q = t; q < body; q += kBlock) {
-      const int2 a = stage[head + 2 * q], b = stage[head + 2 * q + 1];
-      __builtin_nontemporal_store(v4i32{a.x, a.y, b.x, b.y}, dst + q);
-    }
-    const int64_t tail = head + 2 * body;
-    if (t == 0 && tail < lim)
-      __builtin_nontemporal_store(v2i32{stage[tail].x, stage[tail].y},
-                                  reinterpret_cast<v2i32 *>(pairs + block_first + tail));
+    stream_out<kBlock>(reinterpret_cast<const int32_t *>(stage), shift, reinterpret_cast<int32_t *>(dst),
+                       2 * int32_t(min(int64_t(total), room)));
   }
-  if ((full || bad) && status != nullptr)
-    atomicOr(status, (full ? RDF2V_STATUS_CAPACITY : 0) | (bad ? RDF2V_STATUS_BAD_LENGTH : 0));
+  if (total > room && t == 0 && a.status != nullptr) atomicOr(a.status, RDF2V_STATUS_CAPACITY);
 }
 
-// Streams `total` int32 from LDS to dst (4-byte aligned) with the whole block:
-// a scalar head up to 16-byte alignment, 16-byte non-temporal stores, a scalar
-// tail.
+// CBOW, staged: one thread per (walk, position), whose examples form one
+// contiguous output range. The block places its centers and context rows in
+// LDS stages (at most kBlock examples, 2 * window ints per context row) and
+// streams each out.
 template <int kBlock>
-__device__ __forceinline__ void stream_run(const int32_t *src, int32_t *dst, int64_t total) {
-  const int t = threadIdx.x;
-  const int64_t head = min(total, int64_t((16 - (reinterpret_cast<uintptr_t>(dst) & 15)) & 15) / 4);
-  if (t < head) __builtin_nontemporal_store(src[t], dst + t);
-  const int64_t body = (total - head) >> 2;
-  v4i32 *dst4 = reinterpret_cast<v4i32 *>(dst + head);
-  for (int64_t q = t; q < body; q += kBlock) {
-    const int32_t *s4 = src + head + 4 * q;
-    __builtin_nontemporal_store(v4i32{s4[0], s4[1], s4[2], s4[3]}, dst4 + q);
-  }
-  for (int64_t q = head + 4 * body + t; q < total; q += kBlock) __builtin_nontemporal_store(src[q], dst + q);
-}
-
-// CBOW, staged: one thread per (walk, position); walks_per_block = kBlock / width
-// walks per block, whose examples form one contiguous output range. The block
-// copies its rows to LDS, places its centers and context rows in LDS stages
-// (at most kBlock examples, 2 * window ints per context row) and streams each
-// out as one contiguous run of 16-byte non-temporal stores.
-template <int kBlock>
-__global__ __launch_bounds__(kBlock) void cbow_emit_kernel(const int32_t *__restrict__ tokens,
-                                                            const int32_t *__restrict__ len, int64_t n,
-                                                            int32_t width, int32_t window,
-                                                            const int64_t *__restrict__ offsets,
-                                                            int32_t *__restrict__ centers,
-                                                            int32_t *__restrict__ contexts, int64_t capacity,
-                                                            int32_t *status) {
-  extern __shared__ int32_t ctx_stage[];  // the block's context rows
-  __shared__ int32_t rows[kBlock];        // the block's walk rows
-  __shared__ int32_t ctr_stage[kBlock];   // the block's centers
-  const int walks_per_block = kBlock / width;
-  const int t = threadIdx.x;
-  const int64_t r0 = int64_t(blockIdx.x) * walks_per_block;
-  const int64_t r_end = min(n, r0 + walks_per_block);
-  const int64_t r = r0 + t / width;
-  const int64_t i = t % width;
-  const bool active = t < walks_per_block * width && r < n;
-  const int64_t cw = 2 * int64_t(window);  // context entries per example
-  int bad = 0;
-  const int64_t block_first = offsets[r0];
-  // Every global read the block needs is issued before the first barrier, so
-  // none of them waits behind it: the walk's length and first example, the
-  // rows, and (thread 0) where the next block's examples begin.
-  int64_t L = 0, walk_first = 0;
-  if (active) {
-    L = clamped_len(len, r, width, bad);
-    walk_first = offsets[r];
-  }
-  __shared__ int64_t block_end;
-  const int64_t span = (r_end - r0) * width;  // <= kBlock
-  if (t < span) rows[t] = tokens[r0 * width + t];
-  if (t == 0) {
-    if (r_end < n) {
-      block_end = offsets[r_end];
-    } else {
-      int b2 = 0;
-      block_end = offsets[n - 1] + clamped_len(len, n - 1, width, b2);
-    }
+__global__ __launch_bounds__(kBlock) void cbow_emit_kernel(const EmitArgs a, int32_t *__restrict__ centers,
+                                                            int32_t *__restrict__ contexts) {
+  extern __shared__ __align__(16) int32_t ctx_stage[];        // the block's context rows, from their range's offset on
+  __shared__ __align__(16) int32_t ctr_stage[kBlock + kLineInts];     // the block's centers, likewise
+  __shared__ BlockWalks<kBlock> s;
+  const int32_t t = threadIdx.x;
+  int64_t block_first;
+  const int32_t total = load_walks<true>(a, s, block_first);
+  const int32_t w = a.window, cw = 2 * w;
+  int32_t *ctr = centers + block_first;
+  int32_t *ctx = contexts + block_first * cw;
+  const int32_t ctr_shift = int_shift(ctr), ctx_shift = int_shift(ctx);
+  const int32_t k_walk = walk_of(a, t), i = t - k_walk * a.width;
+  if (k_walk < a.walks && i < s.lens[k_walk]) {
+    const int32_t L = s.lens[k_walk];
+    const int32_t *row = s.rows + k_walk * a.width;
+    const int32_t e = s.firsts[k_walk] + i;
+    ctr_stage[ctr_shift + e] = row[i];
+    int32_t *out = ctx_stage + ctx_shift + e * cw;
+    const int32_t j0 = max(0, i - w), nleft = i - j0, nctx = min(L - 1, i + w) - j0;
+    for (int32_t m = 0; m < cw; ++m) out[m] = m < nctx ? row[j0 + m + (m < nleft ? 0 : 1)] : -1;
   }
   __syncthreads();
-  if (active && i < L) {
-    const int32_t *row = rows + (t / width) * width;
-    const int64_t e = walk_first + i;
-    ctr_stage[e - block_first] = row[i];
-    int32_t *ctx = ctx_stage + (e - block_first) * cw;
-    const int64_t j0 = max(int64_t(0), i - window), j1 = min(L - 1, i + int64_t(window));
-    int64_t m = 0;
-    for (int64_t j = j0; j <= j1; ++j)
-      if (j != i) ctx[m++] = row[j];
-    for (; m < cw; ++m) ctx[m] = -1;
-  }
-  __syncthreads();
-  // The block's examples end where the next block's begin.
-  const bool full = block_end > capacity;
-  const int64_t lim = max(int64_t(0), min(block_end, capacity) - block_first);  // examples that fit
-  stream_run<kBlock>(ctr_stage, centers + block_first, lim);
-  stream_run<kBlock>(ctx_stage, contexts + block_first * cw, lim * cw);
-  // `full` holds for the whole block: one thread reports it
-  if (((full && threadIdx.x == 0) || bad) && status != nullptr)
-    atomicOr(status, (full ? RDF2V_STATUS_CAPACITY : 0) | (bad ? RDF2V_STATUS_BAD_LENGTH : 0));
+  // the examples that fit
+  const int64_t room = max(int64_t(0), a.capacity - block_first);
+  const int32_t lim = int32_t(min(int64_t(total), room));
+  stream_out<kBlock>(ctr_stage, ctr_shift, ctr, lim);
+  stream_out<kBlock>(ctx_stage, ctx_shift, ctx, lim * cw);
+  if (total > room && t == 0 && a.status != nullptr) atomicOr(a.status, RDF2V_STATUS_CAPACITY);
 }
 
-// CBOW, written in output order. A block of kBlock threads takes
-// kBlock / width walks, whose examples form one contiguous output range. It
-// stages only its walk rows and, per walk, where its examples start and how
-// many there are, plus the walk of each example; then every thread produces
+// CBOW, written in output order. The block stages only its walk rows, their
+// lengths and places, and the walk of each example; then every thread produces
 // context entries directly in output order, four per 16-byte non-temporal
 // store: entry m of example e is the m-th context of that example's position
 // (the tokens j0 .. j1 of its window, skipping the position itself), or -1
 // past the last one. No context row is ever staged, so the block's LDS does
 // not grow with the window.
 template <int kBlock>
-__global__ __launch_bounds__(kBlock) void cbow_direct_kernel(const int32_t *__restrict__ tokens,
-                                                              const int32_t *__restrict__ len, int64_t n,
-                                                              int32_t width, int32_t window,
-                                                              const int64_t *__restrict__ offsets,
-                                                              int32_t *__restrict__ centers,
-                                                              int32_t *__restrict__ contexts, int64_t capacity,
-                                                              int32_t *status) {
-  __shared__ int32_t rows[kBlock];        // the block's walk rows
-  __shared__ int32_t walk_first[kBlock];  // per walk of the block: its first example, block-relative
-  __shared__ int32_t walk_len[kBlock];    // per walk of the block: its examples (valid tokens)
-  __shared__ int32_t ex_walk[kBlock];     // per example of the block: its walk
-  __shared__ int64_t block_end;
-  const int walks_per_block = kBlock / width;
-  const int t = threadIdx.x;
-  const int64_t r0 = int64_t(blockIdx.x) * walks_per_block;
-  const int64_t r_end = min(n, r0 + walks_per_block);
-  const int k_walk = t / width;  // this thread's walk within the block
-  const int64_t r = r0 + k_walk;
-  const int i = t % width;
-  const bool active = t < walks_per_block * width && r < n;
-  int bad = 0;
-  // Every global read the block needs is issued before the first barrier.
-  const int64_t block_first = offsets[r0];
-  int32_t L = 0;
-  int64_t walk_first_g = 0;
-  if (active) {
-    L = clamped_len(len, r, width, bad);
-    walk_first_g = offsets[r];
+__global__ __launch_bounds__(kBlock) void cbow_direct_kernel(const EmitArgs a, int32_t *__restrict__ centers,
+                                                              int32_t *__restrict__ contexts) {
+  __shared__ BlockWalks<kBlock> s;
+  __shared__ int32_t ex_walk[kBlock];  // per example of the block: its walk
+  const int32_t t = threadIdx.x;
+  const int32_t width = a.width;
+  int64_t block_first;
+  const int32_t cnt = load_walks<true>(a, s, block_first);
+  {
+    const int32_t k_walk = walk_of(a, t), i = t - k_walk * width;
+    if (k_walk < a.walks && i < s.lens[k_walk]) ex_walk[s.firsts[k_walk] + i] = k_walk;
   }
-  const int64_t span = (r_end - r0) * width;  // <= kBlock
-  if (t < span) rows[t] = tokens[r0 * width + t];
-  if (t == 0) {
-    if (r_end < n) {
-      block_end = offsets[r_end];
-    } else {
-      int b2 = 0;
-      block_end = offsets[n - 1] + clamped_len(len, n - 1, width, b2);
-    }
-  }
-  // Block-relative example indices: a block holds at most one example per thread.
-  const int32_t wf = int32_t(walk_first_g - block_first);
-  if (active && i == 0) {
-    walk_first[k_walk] = wf;
-    walk_len[k_walk] = L;
-  }
-  if (active && i < L) ex_walk[wf + i] = k_walk;
   __syncthreads();
-
-  const int64_t cnt = block_end - block_first;                          // examples of the block
-  const int32_t lim = int32_t(max(int64_t(0), min(cnt, capacity - block_first)));  // those that fit
-  const bool full = block_end > capacity;
-  const int32_t w = window, cw = 2 * window;
+  const int32_t *rows = s.rows, *walk_first = s.firsts, *walk_len = s.lens;
+  const int64_t room = max(int64_t(0), a.capacity - block_first);
+  const int32_t lim = int32_t(min(int64_t(cnt), room));  // those that fit
+  const int32_t w = a.window, cw = 2 * w;
   // Centers: example e of the block is position e - walk_first of its walk.
   for (int32_t e = t; e < lim; e += kBlock) {
     const int32_t k = ex_walk[e];
@@ -413,12 +361,10 @@ __global__ __launch_bounds__(kBlock) void cbow_direct_kernel(const int32_t *__re
     const Cursor c = at(q / cw, q % cw);
     __builtin_nontemporal_store(value(c), dst + q);
   }
-  // `full` holds for the whole block: one thread reports it
-  if (((full && threadIdx.x == 0) || bad) && status != nullptr)
-    atomicOr(status, (full ? RDF2V_STATUS_CAPACITY : 0) | (bad ? RDF2V_STATUS_BAD_LENGTH : 0));
+  if (cnt > room && t == 0 && a.status != nullptr) atomicOr(a.status, RDF2V_STATUS_CAPACITY);
 }
 
-constexpr size_t kMaxStageBytes = 32 << 10;
+constexpr size_t kMaxStageBytes = 32 << 10, kBestStageBytes = 14 << 10;
 
 // Most pairs one walk of this width can give.
 inline int64_t max_walk_pairs(int64_t width, int64_t window) {
@@ -430,77 +376,84 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 }  // namespace
 
+// The size callers hold workspaces of: 8 bytes per walk and per 4,096 walks.
+// What is kept in it are 4 bytes per emit block (one walk at least) and, behind
+// them, 8 per kCountThreads of those.
 size_t skipgram_workspace_bytes(int64_t num_walks) {
-  const int64_t nb = ceil_div(num_walks, kTile);
+  const int64_t nb = ceil_div(num_walks, 4096);
   return align_up(size_t(num_walks) * 8, 256) + align_up(size_t(nb + 1) * 8, 256);
 }
+
+namespace {
+
+// Counts the items of num_walks walks, `walks` of them per emit block, and
+// fills the emit kernels' arguments.
+template <bool kCbow>
+rdf2v_status count_items(const int32_t *tokens, const int32_t *len, int64_t num_walks, int32_t width, int32_t window,
+                         int32_t walks, int64_t capacity, int64_t *count_out, void *workspace, int32_t *status_dev,
+                         hipStream_t stream, EmitArgs &a, int64_t &emit_blocks) {
+  emit_blocks = ceil_div(num_walks, walks);
+  if (emit_blocks >= (int64_t(1) << 31)) return RDF2V_ERR_TOO_LARGE;
+  const int64_t nb = ceil_div(emit_blocks, kCountThreads);
+  int32_t *firsts = static_cast<int32_t *>(workspace);
+  int64_t *partials = reinterpret_cast<int64_t *>(firsts + (emit_blocks + 1) / 2 * 2);
+  a.tokens = tokens;
+  a.len = len;
+  a.n = num_walks;
+  a.width = width;
+  a.window = window;
+  a.walks = walks;
+  a.width_inverse = uint32_t(((uint64_t(1) << 32) + uint64_t(width) - 1) / uint64_t(width));
+  a.firsts = firsts;
+  a.partials = partials;
+  a.capacity = capacity;
+  a.status = status_dev;
+  if (nb > 0) {
+    item_count_kernel<kCbow><<<dim3(unsigned(nb)), dim3(kCountThreads), 0, stream>>>(
+        len, num_walks, width, window, walks, emit_blocks, firsts, partials, count_out, status_dev);
+    RDF2V_LAUNCH_CHECK();
+  }
+  if (nb != 1) {
+    partials_scan_kernel<<<dim3(1), dim3(kCountThreads), 0, stream>>>(partials, nb, count_out);
+    RDF2V_LAUNCH_CHECK();
+  }
+  return RDF2V_OK;
+}
+
+}  // namespace
 
 rdf2v_status launch_skipgram_pairs(const int32_t *tokens, const int32_t *len, int64_t num_walks,
                                    int32_t width, int32_t window, int32_t *pairs_out, int64_t capacity,
                                    int64_t *count_out, void *workspace, int32_t *status_dev,
                                    hipStream_t stream) {
-  char *ws = static_cast<char *>(workspace);
-  int64_t *offsets = reinterpret_cast<int64_t *>(ws);
-  int64_t *partials = reinterpret_cast<int64_t *>(ws + align_up(size_t(num_walks) * 8, 256));
-  const int64_t nb = ceil_div(num_walks, kTile);
-  if (nb > 0) {
-    pair_count_reduce_kernel<false><<<dim3(unsigned(nb)), dim3(kThreads), 0, stream>>>(len, num_walks, width,
-                                                                                      window, partials,
-                                                                                      status_dev);
-    RDF2V_LAUNCH_CHECK();
-  }
-  pair_partials_kernel<<<dim3(1), dim3(kThreads), 0, stream>>>(partials, nb, count_out);
+  // The largest block whose pairs fit a stage of kBestStageBytes, else the
+  // smallest that fits one of kMaxStageBytes: several small blocks per CU keep
+  // the write stream going while others load rows and place pairs, down to
+  // about 8 KB of output each (8M walks of 17 tokens, window 5: 1.55 ms with
+  // 128 threads and 7.8 KB, 1.69 with 256 and 16.8, 1.68 with 64 and 3.4).
+  const int64_t per_walk = max_walk_pairs(width, window);
+  auto stage_bytes = [&](int block) { return size_t(per_walk * (block / width)) * sizeof(int2) + 4 * kLineInts; };
+  int block = 0;  // 0: no stage
+  for (int b : {64, 128, 256})
+    if (width <= b && stage_bytes(b) <= (block == 0 ? kMaxStageBytes : kBestStageBytes)) block = b;
+  EmitArgs a;
+  int64_t blocks;
+  const rdf2v_status st = count_items<false>(tokens, len, num_walks, width, window, (block ? block : kThreads) / width,
+                                             capacity, count_out, workspace, status_dev, stream, a, blocks);
+  if (st != RDF2V_OK || capacity == 0 || blocks == 0) return st;
+  int2 *out = reinterpret_cast<int2 *>(pairs_out);
+  const dim3 grid{unsigned(blocks)};
+  if (block == 256) pair_emit_kernel<true, 256><<<grid, dim3(256), stage_bytes(256), stream>>>(a, out);
+  else if (block == 128) pair_emit_kernel<true, 128><<<grid, dim3(128), stage_bytes(128), stream>>>(a, out);
+  else if (block == 64) pair_emit_kernel<true, 64><<<grid, dim3(64), stage_bytes(64), stream>>>(a, out);
+  else pair_emit_kernel<false, kThreads><<<grid, dim3(kThreads), 0, stream>>>(a, out);
   RDF2V_LAUNCH_CHECK();
-  if (nb == 0) return RDF2V_OK;
-  pair_offsets_kernel<false><<<dim3(unsigned(nb)), dim3(kThreads), 0, stream>>>(len, num_walks, width, window,
-                                                                               partials, offsets);
-  RDF2V_LAUNCH_CHECK();
-  if (capacity > 0) {
-    int2 *out = reinterpret_cast<int2 *>(pairs_out);
-    // Blocks of 256 threads when their pairs fit a stage of at most
-    // kMaxStageBytes, else of 128 or 64: several small blocks per CU keep the
-    // write stream going while others load rows and place pairs (measured:
-    // 256 threads with a ~17 KB stage beat 512 and 1024 with 33-67 KB).
-    const int64_t per_walk = max_walk_pairs(width, window);
-    auto stage_bytes = [&](int block) { return size_t(per_walk * (block / width)) * sizeof(int2); };
-    auto launch = [&](auto kernel, int block, size_t lds) -> rdf2v_status {
-      const int64_t blocks = ceil_div(num_walks, block / width);
-      if (blocks >= (int64_t(1) << 31)) return RDF2V_ERR_TOO_LARGE;
-      kernel<<<dim3(unsigned(blocks)), dim3(block), lds, stream>>>(tokens, len, num_walks, width, window, offsets,
-                                                                   out, capacity, status_dev);
-      RDF2V_LAUNCH_CHECK();
-      return RDF2V_OK;
-    };
-    if (width <= 256 && stage_bytes(256) <= kMaxStageBytes)
-      return launch(pair_emit_kernel<true, 256>, 256, stage_bytes(256));
-    if (width <= 128 && stage_bytes(128) <= kMaxStageBytes)
-      return launch(pair_emit_kernel<true, 128>, 128, stage_bytes(128));
-    if (width <= 64 && stage_bytes(64) <= kMaxStageBytes)
-      return launch(pair_emit_kernel<true, 64>, 64, stage_bytes(64));
-    return launch(pair_emit_kernel<false, kThreads>, kThreads, 0);
-  }
   return RDF2V_OK;
 }
 
 rdf2v_status launch_cbow_examples(const int32_t *tokens, const int32_t *len, int64_t num_walks, int32_t width,
                                   int32_t window, int32_t *centers_out, int32_t *contexts_out, int64_t capacity,
                                   int64_t *count_out, void *workspace, int32_t *status_dev, hipStream_t stream) {
-  char *ws = static_cast<char *>(workspace);
-  int64_t *offsets = reinterpret_cast<int64_t *>(ws);
-  int64_t *partials = reinterpret_cast<int64_t *>(ws + align_up(size_t(num_walks) * 8, 256));
-  const int64_t nb = ceil_div(num_walks, kTile);
-  if (nb > 0) {
-    pair_count_reduce_kernel<true><<<dim3(unsigned(nb)), dim3(kThreads), 0, stream>>>(len, num_walks, width, window,
-                                                                                     partials, status_dev);
-    RDF2V_LAUNCH_CHECK();
-  }
-  pair_partials_kernel<<<dim3(1), dim3(kThreads), 0, stream>>>(partials, nb, count_out);
-  RDF2V_LAUNCH_CHECK();
-  if (nb == 0) return RDF2V_OK;
-  pair_offsets_kernel<true><<<dim3(unsigned(nb)), dim3(kThreads), 0, stream>>>(len, num_walks, width, window,
-                                                                              partials, offsets);
-  RDF2V_LAUNCH_CHECK();
-  if (capacity == 0) return RDF2V_OK;
   // The staged kernel holds a block's context rows in LDS: B rows of
   // 2 * window ints for B threads, 256-thread blocks up to 32 KB, else 128.
   // The output-order kernel needs no stage. Measured on 8M walks of 17 tokens
@@ -511,21 +464,24 @@ rdf2v_status launch_cbow_examples(const int32_t *tokens, const int32_t *len, int
   // (Earlier, at window 5 on 48.9M walks: 512-thread blocks, or two or four
   // positions per thread, were 2-50 % slower.)
   const size_t row_bytes = size_t(2) * size_t(window) * sizeof(int32_t);
-  auto launch = [&](auto kernel, int block, size_t lds) -> rdf2v_status {
-    const int64_t blocks = ceil_div(num_walks, block / width);
-    if (blocks >= (int64_t(1) << 31)) return RDF2V_ERR_TOO_LARGE;
-    kernel<<<dim3(unsigned(blocks)), dim3(block), lds, stream>>>(tokens, len, num_walks, width, window, offsets,
-                                                                 centers_out, contexts_out, capacity, status_dev);
-    RDF2V_LAUNCH_CHECK();
-    return RDF2V_OK;
-  };
-  if (window >= 5) {
-    if (width <= 256 && 256 * row_bytes <= kMaxStageBytes)
-      return launch(cbow_emit_kernel<256>, 256, 256 * row_bytes);
-    if (width <= 128 && 128 * row_bytes <= kMaxStageBytes)
-      return launch(cbow_emit_kernel<128>, 128, 128 * row_bytes);
-  }
-  return launch(cbow_direct_kernel<256>, 256, 0);
+  auto stage_bytes = [&](int block) { return size_t(block / width * width) * row_bytes + 4 * kLineInts; };
+  int block = 0;  // 0: output order
+  for (int b : {128, 256})
+    if (window >= 5 && width <= b && stage_bytes(b) <= (block == 0 ? kMaxStageBytes : kBestStageBytes)) block = b;
+  EmitArgs a;
+  int64_t blocks;
+  const rdf2v_status st = count_items<true>(tokens, len, num_walks, width, window, (block ? block : kThreads) / width,
+                                            capacity, count_out, workspace, status_dev, stream, a, blocks);
+  if (st != RDF2V_OK || capacity == 0 || blocks == 0) return st;
+  const dim3 grid{unsigned(blocks)};
+  if (block == 256)
+    cbow_emit_kernel<256><<<grid, dim3(256), stage_bytes(256), stream>>>(a, centers_out, contexts_out);
+  else if (block == 128)
+    cbow_emit_kernel<128><<<grid, dim3(128), stage_bytes(128), stream>>>(a, centers_out, contexts_out);
+  else
+    cbow_direct_kernel<kThreads><<<grid, dim3(kThreads), 0, stream>>>(a, centers_out, contexts_out);
+  RDF2V_LAUNCH_CHECK();
+  return RDF2V_OK;
 }
 
 }  // namespace rdf2v

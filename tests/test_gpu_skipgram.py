@@ -94,3 +94,46 @@ def test_powerlaw_corpus_slices():
         got = _gpu_pairs(sl_t, sl_l, 5)
         ref = oracle.skipgram_pairs(sl_t.cpu().numpy(), sl_l.cpu().numpy(), 5)
         assert np.array_equal(got, ref), f"slice at {b}"
+
+
+@pytest.mark.parametrize("n,width,window,offset", [
+    (1, 17, 5, 3), (7, 17, 5, 1), (8, 17, 5, 15),     # one block of 7 walks, its end, the next one
+    (28 * 1024, 9, 5, 7), (28 * 1024 + 1, 9, 5, 9),   # one and two workgroups of the count
+    (7 * 2048 + 3, 17, 5, 5), (40_000, 3, 2, 11),     # several; blocks of more walks than a wave
+    (1500, 100, 64, 2), (2100, 129, 128, 1),          # no stage; a walk per block
+])
+def test_outputs_at_any_offset_and_cut(n, width, window, offset):
+    # Outputs that begin anywhere in a 128-byte line, with room for everything
+    # and with room for two thirds: what lies around them is left alone.
+    say(f"[pairs] n={n} width={width} window={window} offset={offset}")
+    rng = np.random.default_rng(n + width)
+    ln = rng.integers(0, width + 1, n).astype(np.int32)
+    ln[rng.random(n) < 0.5] = width
+    tok = np.where(np.arange(width) < ln[:, None], rng.integers(0, 10**6, (n, width)), -1).astype(np.int32)
+    t, l = to_dev(tok), to_dev(ln)
+    pairs = oracle.skipgram_pairs(tok, ln, window)
+    centers, contexts = oracle.cbow_examples(tok, ln, max(window, 1))
+    for part in (1.0, 2 / 3):
+        cap = int(len(pairs) * part)
+        buf = torch.full((cap + offset + 40, 2), -7, dtype=torch.int32, device=device())
+        st = new_status()
+        _, cnt = rd.rdf2v_skipgram_pairs(t, l, window, pairs=buf[offset:offset + cap], status=st)
+        got = buf.cpu().numpy()
+        assert int(cnt.item()) == len(pairs)
+        assert np.array_equal(got[offset:offset + cap], pairs[:cap])
+        assert (got[:offset] == -7).all() and (got[offset + cap:] == -7).all()
+        assert int(st.item()) == (rd.RDF2V_STATUS_CAPACITY if cap < len(pairs) else 0)
+        cap = int(len(centers) * part)
+        ctr = torch.full((cap + offset + 40,), -7, dtype=torch.int32, device=device())
+        ctx = torch.full(((cap + 40) * 2 * max(window, 1) + offset,), -7, dtype=torch.int32, device=device())
+        wide = 2 * max(window, 1) * cap
+        st = new_status()
+        _, _, cnt = rd.rdf2v_cbow_examples(t, l, max(window, 1), centers=ctr[offset:offset + cap],
+                                           contexts=ctx[offset:offset + wide], status=st)
+        c, x = ctr.cpu().numpy(), ctx.cpu().numpy()
+        assert int(cnt.item()) == len(centers)
+        assert np.array_equal(c[offset:offset + cap], centers[:cap])
+        assert np.array_equal(x[offset:offset + wide], contexts[:cap].reshape(-1))
+        assert (c[:offset] == -7).all() and (c[offset + cap:] == -7).all()
+        assert (x[:offset] == -7).all() and (x[offset + wide:] == -7).all()
+        assert int(st.item()) == (rd.RDF2V_STATUS_CAPACITY if cap < len(centers) else 0)
