@@ -385,6 +385,19 @@ rdf2v_status rdf2v_bfs_walks(const rdf2v_csr *csr, const int32_t *roots, int64_t
                              int32_t max_walks, int32_t *tokens_out, int32_t *len_out, int32_t *counts_out,
                              void *workspace, size_t workspace_bytes, int32_t *status_dev, void *stream);
 
+/*
+ * Writes what rdf2v_bfs_walks leaves untouched: rows counts[r] .. max_walks - 1
+ * of every root r become -1 and their lengths 0, as if both outputs had been
+ * filled before that call (which would write most of them twice).
+ *
+ *   counts       [num_roots] int32 (device), as rdf2v_bfs_walks writes them;
+ *                values outside [0, max_walks] are treated as clamped.
+ *   row_width    tokens per row, 2 * depth + 1.
+ *   tokens_out, len_out  as for rdf2v_bfs_walks (device).
+ */
+rdf2v_status rdf2v_bfs_fill_unused(const int32_t *counts, int64_t num_roots, int32_t max_walks, int32_t row_width,
+                                   int32_t *tokens_out, int32_t *len_out, void *stream);
+
 /* Largest num_triples and bound on distinct strings rdf2v_build_vocabulary takes. */
 #define RDF2V_VOCAB_MAX_TRIPLES ((int64_t)1 << 30)
 #define RDF2V_VOCAB_MAX_DISTINCT ((int64_t)1 << 30)

@@ -103,6 +103,8 @@ def _native():
     lib.rdf2v_bfs_walks_workspace_size.restype = sz
     lib.rdf2v_bfs_walks.argtypes = [csr_p, vp, i64, i32, i32, vp, vp, vp, vp, sz, vp, vp]
     lib.rdf2v_bfs_walks.restype = ctypes.c_int
+    lib.rdf2v_bfs_fill_unused.argtypes = [vp, i64, i32, i32, vp, vp, vp]
+    lib.rdf2v_bfs_fill_unused.restype = ctypes.c_int
     lib.rdf2v_skipgram_pairs_workspace_size.argtypes = [i64]
     lib.rdf2v_skipgram_pairs_workspace_size.restype = sz
     lib.rdf2v_skipgram_pairs.argtypes = [vp, vp, i64, i32, i32, vp, i64, vp, vp, sz, vp, vp]
@@ -433,10 +435,13 @@ def rdf2v_bfs_walks(csr: Csr, roots: torch.Tensor, depth: int, max_walks: int, *
     with _on_stream(dev, stream) as h:
         R = int(roots.shape[0])
         width = 2 * depth + 1
+        # the rows no walk takes are filled afterwards: filling both beforehand would write most twice
+        fill = tokens is None and lens is None and max_walks > 0
         if tokens is None:
-            tokens = torch.full((R, max_walks, width), -1, dtype=torch.int32, device=dev)
+            tokens = (torch.empty((R, max_walks, width), dtype=torch.int32, device=dev) if fill else
+                      torch.full((R, max_walks, width), -1, dtype=torch.int32, device=dev))
         if lens is None:
-            lens = torch.zeros((R, max_walks), dtype=torch.int32, device=dev)
+            lens = (torch.empty if fill else torch.zeros)((R, max_walks), dtype=torch.int32, device=dev)
         if counts is None:
             counts = torch.empty(R, dtype=torch.int32, device=dev)
         if workspace is None:
@@ -452,6 +457,9 @@ def rdf2v_bfs_walks(csr: Csr, roots: torch.Tensor, depth: int, max_walks: int, *
                                        _ptr(counts), _ptr(workspace), _ws_bytes(workspace), _ptr(status),
                                        h)
         _check(st, "rdf2v_bfs_walks")
+        if fill:
+            st = _native().rdf2v_bfs_fill_unused(_ptr(counts), R, max_walks, width, _ptr(tokens), _ptr(lens), h)
+            _check(st, "rdf2v_bfs_fill_unused")
         return tokens, lens, counts
 
 

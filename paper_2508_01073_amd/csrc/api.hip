@@ -258,6 +258,17 @@ RDF2V_API rdf2v_status rdf2v_bfs_walks(const rdf2v_csr *csr, const int32_t *root
                                  counts_out, workspace, status_dev, static_cast<hipStream_t>(stream));
 }
 
+RDF2V_API rdf2v_status rdf2v_bfs_fill_unused(const int32_t *counts, int64_t num_roots, int32_t max_walks,
+                                             int32_t row_width, int32_t *tokens_out, int32_t *len_out, void *stream) {
+  if (num_roots < 0 || max_walks < 1 || row_width < 1 || row_width > 2 * RDF2V_MAX_DEPTH + 1)
+    return RDF2V_ERR_INVALID_ARGUMENT;
+  if (num_roots >= kInt32Limit || num_roots > INT64_MAX / max_walks / row_width) return RDF2V_ERR_TOO_LARGE;
+  if (num_roots == 0) return RDF2V_OK;
+  if (counts == nullptr || tokens_out == nullptr || len_out == nullptr) return RDF2V_ERR_INVALID_ARGUMENT;
+  return rdf2v::launch_bfs_fill_unused(counts, num_roots, max_walks, row_width, tokens_out, len_out,
+                                       static_cast<hipStream_t>(stream));
+}
+
 namespace {
 
 bool vocab_sizes_ok(int64_t num_triples, int64_t max_entities, int64_t max_predicates) {

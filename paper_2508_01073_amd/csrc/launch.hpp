@@ -60,6 +60,9 @@ rdf2v_status launch_bfs_walks(const int32_t *row_ptr, const int32_t *edges, int6
                               int32_t *len_out, int32_t *counts_out, void *workspace, int32_t *status_dev,
                               hipStream_t stream);
 
+rdf2v_status launch_bfs_fill_unused(const int32_t *counts, int64_t num_roots, int32_t max_walks, int32_t width,
+                                    int32_t *tokens_out, int32_t *len_out, hipStream_t stream);
+
 // The three string columns of rdf2v_build_vocabulary, in the order subject,
 // predicate, object.
 struct VocabColumns {
