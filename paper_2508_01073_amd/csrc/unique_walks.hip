@@ -4,12 +4,15 @@
 //
 // Main path (groups of at most 1024 rows whose block of rows fits the LDS
 // stage): a block owns whole groups.
-//   1. group_keep_kernel: the block copies its rows to LDS (batched coalesced
-//      loads), hashes every row there (64-bit FNV-1a over length and valid
-//      tokens), and keeps a row unless an earlier row of its group has the same
-//      hash, length and tokens (equal hashes are always confirmed token by
-//      token, so collisions cannot drop a walk). Keep flags go to global
-//      memory, the block's kept count to a partial sum.
+//   1. group_keep_kernel: the block (or, for groups of at most 64 rows, each
+//      wave of wave_keep_kernel) copies its rows to LDS (batched coalesced
+//      loads), hashes every row there over length and valid tokens, and keeps a
+//      row unless an earlier row of its group has the same hash, length and
+//      tokens (equal hashes are always confirmed token by token, so collisions
+//      cannot drop a walk). Keep flags go to global memory, the block's kept
+//      count to a partial sum. (One pass with a decoupled look-back over the
+//      blocks' counts was slower: 534 us for 20M rows, of which the polling
+//      across the chiplets took 230, against 493.)
 //   2. an exclusive scan of the block counts (tiles scanned in parallel, then
 //      the tile totals, then each tile's prefix added).
 //   3. group_compact_kernel: the block stages its rows again, scans its keep
@@ -330,6 +333,135 @@ __global__ __launch_bounds__(NT) void group_keep_kernel(const int32_t *__restric
   if (bad && status != nullptr) atomicOr(status, RDF2V_STATUS_BAD_LENGTH);
 }
 
+// The same for groups of at most 64 rows, with a wave in place of the block:
+// wave w of block b takes rows_per_wave rows (whole groups) and nothing makes
+// one wave wait for another until the block's count, so the rows of many waves
+// are on their way while others hash. 20M rows of 9 tokens in groups of 50: 235
+// us, against 282 for blocks of 250 rows that share barriers, a 64-bit hash
+// (four 32-bit products a token) and 4-byte loads.
+constexpr int kWaveSlots = 2 * kWave;  // table entries per wave: hash bits above 1 + the first row of a walk
+constexpr int kWaveRowBits = 7;
+constexpr int kKeepWaves = kThreads / kWave;
+
+// Orders LDS accesses of the lanes of one wave (the hardware runs them in
+// order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// 32-bit multiplicative hash of a row's length and valid tokens: equal hashes
+// are confirmed, so it need only spread the rows of a wave.
+__device__ __forceinline__ uint32_t short_hash(const int32_t *row, int32_t L, uint32_t seed) {
+  uint32_t h = seed ^ uint32_t(L);
+  for (int32_t j = 0; j < L; ++j) {
+    h = (h ^ uint32_t(row[j])) * 0x9e3779b1u;
+    h ^= h >> 15;
+  }
+  return h;
+}
+
+// Copies `count` ints to LDS with one wave and returns where in `lds` they
+// begin (0 to 3: the copy moves 16-byte groups, so it keeps the source's
+// offset from 16-byte alignment). `lds` is 16-byte aligned and holds count + 7
+// ints.
+__device__ __forceinline__ const int32_t *stage_rows_wave(int32_t *lds, const int32_t *__restrict__ src, int32_t count) {
+  constexpr int kAhead = 4;  // 16-byte loads in flight per lane
+  const int32_t t = lane_id();
+  const int32_t head = min(count, int32_t(((16 - (reinterpret_cast<uintptr_t>(src) & 15)) & 15) / 4));
+  int32_t *dst = lds + ((4 - head) & 3);
+  const int32_t groups = (count - head) >> 2;
+  const int4 *src4 = reinterpret_cast<const int4 *>(src + head);
+  int4 *dst4 = reinterpret_cast<int4 *>(dst + head);
+  // the ints outside the groups, at most three before and three after
+  const int32_t edge = t < head ? t : 4 * groups + t;
+  const bool on_edge = t < head + 3 && edge < count;
+  const int32_t e = count > 0 ? src[min(edge, count - 1)] : 0;
+  for (int32_t base = 0; base < groups; base += kAhead * kWave) {
+    int4 v[kAhead];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k)
+      v[k] = src4[min(base + k * kWave + t, groups - 1)];  // past the end the last one again: no branch, no wait between loads
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k)
+      if (base + k * kWave + t < groups) dst4[base + k * kWave + t] = v[k];
+  }
+  if (on_edge) dst[edge] = e;
+  return dst;
+}
+
+__global__ __launch_bounds__(kThreads) void wave_keep_kernel(const int32_t *__restrict__ tokens,
+                                                             const int32_t *__restrict__ len, int64_t n,
+                                                             int32_t width, int32_t group, int32_t rows_per_wave,
+                                                             int32_t lds_per_wave, uint8_t *__restrict__ keep,
+                                                             int64_t *__restrict__ partials, int32_t *status) {
+  extern __shared__ __align__(16) int32_t tile[];  // lds_per_wave ints per wave
+  __shared__ __align__(16) uint32_t tables[kKeepWaves][kWaveSlots];
+  __shared__ int32_t lens[kKeepWaves][kWave];
+  __shared__ int32_t kept[kKeepWaves];
+  const int lane = lane_id();
+  const int wave = threadIdx.x / kWave;
+  uint32_t *table = tables[wave];
+  const int64_t r0 = (int64_t(blockIdx.x) * kKeepWaves + wave) * rows_per_wave;
+  const int32_t rows = int32_t(max(int64_t(0), min(int64_t(rows_per_wave), n - r0)));
+  int bad = 0;
+  int32_t count = 0;
+  if (rows > 0) {  // uniform per wave
+    reinterpret_cast<uint2 *>(table)[lane] = make_uint2(0, 0);
+    const int32_t raw_len = lane < rows ? len[r0 + lane] : 0;
+    const int32_t *rows_lds = stage_rows_wave(tile + wave * lds_per_wave, tokens + r0 * width, rows * width);
+    const int32_t L = lane < rows ? clamp_len(raw_len, width, bad) : 0;
+    lens[wave][lane] = L;
+    wave_lds_fence();
+    uint32_t slot = 0, mine = 0;
+    if (lane < rows) {
+      const int32_t *row = rows_lds + lane * width;
+      const int32_t g = lane / group;
+      const uint32_t h = short_hash(row, L, uint32_t(g) * 0x85ebca6bu);
+      mine = (h << kWaveRowBits) | uint32_t(lane + 1);
+      slot = h >> (32 - kWaveRowBits);
+      for (;;) {  // ends: twice as many entries as rows
+        const uint32_t cur = atomicCAS(&table[slot], 0u, mine);
+        if (cur == 0u || ((cur ^ mine) >> kWaveRowBits) == 0) break;
+        slot = (slot + 1) & uint32_t(kWaveSlots - 1);
+      }
+      atomicMin(&table[slot], mine);
+    }
+    wave_lds_fence();
+    // The first row with these hash bits is usually the first occurrence of
+    // this walk; when it is not (equal bits of different rows), scan the
+    // group's earlier rows.
+    bool k = lane < rows;
+    if (k && table[slot] != mine) {
+      const int32_t *row = rows_lds + lane * width;
+      auto same_row = [&](int32_t o) {
+        if (lens[wave][o] != L || o / group != lane / group) return false;
+        int32_t differ = 0;  // four tokens a step, their reads in flight together (past the end: the last one again)
+        for (int32_t j = 0; differ == 0 && j < L; j += 4) {
+#pragma unroll
+          for (int32_t c = 0; c < 4; ++c) {
+            const int32_t at = min(j + c, L - 1);
+            differ |= rows_lds[o * width + at] ^ row[at];
+          }
+        }
+        return differ == 0;
+      };
+      k = !same_row(int32_t(table[slot] & ((1u << kWaveRowBits) - 1)) - 1);
+      for (int32_t o = lane / group * group; k && o < lane; ++o) k = !same_row(o);
+    }
+    count = __popcll(__ballot(k));
+    if (lane < rows) keep[r0 + lane] = k ? 1 : 0;
+  }
+  if (lane == 0) kept[wave] = count;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int64_t total = 0;
+    for (int w = 0; w < kKeepWaves; ++w) total += kept[w];
+    partials[blockIdx.x] = total;
+  }
+  if (bad && status != nullptr) atomicOr(status, RDF2V_STATUS_BAD_LENGTH);
+}
+
 template <int NT>
 __global__ __launch_bounds__(NT) void group_compact_kernel(const int32_t *__restrict__ tokens,
                                                                  const int32_t *__restrict__ len, int64_t n,
@@ -389,11 +521,19 @@ rdf2v_status launch_unique_walks(const int32_t *tokens, const int32_t *len, int6
   int64_t *tile_sums = reinterpret_cast<int64_t *>(ws + align_up(size_t(num_walks) * 8, 256) +
                                                    align_up(size_t(num_walks) * 4, 256));
   auto main_path = [&](auto keep_kernel, auto compact_kernel, int nt) -> rdf2v_status {
-    const int32_t rows_per_block = (nt / group) * group;
+    // groups of at most a wave's rows: whole groups per wave
+    const int32_t rows_per_wave = group <= kWave && nt == kThreads ? (kWave / group) * group : 0;
+    const int32_t rows_per_block = rows_per_wave > 0 ? kKeepWaves * rows_per_wave : (nt / group) * group;
     const size_t tile_bytes = size_t(rows_per_block) * width * sizeof(int32_t);
     const int64_t nb = ceil_div(num_walks, rows_per_block);
     if (nb >= (int64_t(1) << 31)) return RDF2V_ERR_TOO_LARGE;
-    if (nb > 0) {
+    if (nb > 0 && rows_per_wave > 0) {
+      const int32_t lds_per_wave = (rows_per_wave * width + 7 + 3) / 4 * 4;
+      wave_keep_kernel<<<dim3(unsigned(nb)), dim3(kThreads), size_t(lds_per_wave) * kKeepWaves * sizeof(int32_t),
+                         stream>>>(tokens, len, num_walks, width, group, rows_per_wave, lds_per_wave, keep_flags,
+                                   block_counts, status_dev);
+      RDF2V_LAUNCH_CHECK();
+    } else if (nb > 0) {
       keep_kernel<<<dim3(unsigned(nb)), dim3(nt), tile_bytes, stream>>>(tokens, len, num_walks, width, group,
                                                                         rows_per_block, keep_flags, block_counts,
                                                                         status_dev);

@@ -146,3 +146,21 @@ def test_unique_walks_many_block_counts(n, width, group):
     ref_t, ref_l = oracle.unique_walks(tok, ln, group)
     got_t, got_l = _gpu_unique(tok, ln, group)
     assert_rows_equal(got_t, got_l, ref_t, ref_l, f"{n} rows group {group}")
+
+
+@pytest.mark.parametrize("n,group,width,offset", [
+    (1, 1, 1, 0), (64, 64, 3, 1), (65, 64, 3, 2), (255, 50, 9, 3), (200, 50, 9, 1), (201, 50, 9, 0),
+    (1000, 33, 17, 2), (999, 7, 2, 1), (4096, 1, 5, 3), (515, 65, 5, 1),   # the last: more rows than a wave
+])
+def test_unique_walks_wave_groups(n, group, width, offset):
+    # groups of at most a wave's rows, rows that begin anywhere in a 16-byte group, few distinct walks
+    say(f"[unique] n={n} group={group} width={width} offset={offset}")
+    rng = np.random.default_rng(n + group)
+    ln = rng.integers(0, width + 1, n).astype(np.int32)
+    tok = rng.integers(0, 3, (n, width)).astype(np.int32)   # past a row's length: not padding, not compared
+    buf = torch.zeros(n * width + 4, dtype=torch.int32, device=device())
+    t = buf[offset:offset + n * width].view(n, width)
+    t.copy_(torch.from_numpy(tok))
+    got_t, got_l = rd.rdf2v_unique_walks(t, to_dev(ln), group, status=new_status())
+    ref_t, ref_l = oracle.unique_walks(tok, ln, group)
+    assert np.array_equal(got_l.cpu().numpy(), ref_l) and np.array_equal(got_t.cpu().numpy(), ref_t)
