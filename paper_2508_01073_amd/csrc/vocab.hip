@@ -579,37 +579,49 @@ __device__ __forceinline__ int32_t insert_general(const Seq &seq, int64_t q, Slo
   return int32_t(found);
 }
 
-// A wave takes the mask of 64 occurrences, clearing it (the masks become the
-// bitset of first occurrences), and ends if none was deferred. One mask per
-// wave: those of the first strings, which meet a table still being filled, are
-// full, and a wave with 64 masks in a row to hand out took 285 + 408 us on 20M
-// triples. A thread per occurrence that looked up its parked id and lowered
-// minpos itself: 131 + 84 us; this: 143 + 51 us, and 16 + 9 us on 5,000
-// triples against 25 + 12.
+// A wave takes up to kMasksPerWave masks of 64 occurrences, clearing them (the
+// masks become the bitset of first occurrences), and works off those with a
+// deferred occurrence. Few have one, so what most waves cost is to start and
+// wait for their masks (20M triples: the call 2,450 us with one mask per wave,
+// its two launches of this 150 + 90 us; 2,365 us with eight). The
+// masks of a wave lie a grid apart: those of the first strings, which meet a
+// table still being filled, are full, and a wave with 64 in a row to hand out
+// took 285 + 408 us. Lookups from a thread per occurrence, each lowering
+// minpos itself: 131 + 84 us, and 25 + 12 us on 5,000 triples.
+constexpr int kMasksPerWave = 8;
+constexpr int64_t kGeneralWaves = 16384;  // below this many masks a wave takes one: the chip holds them all
+
 template <bool kPaired>
 __global__ __launch_bounds__(kThreads) void insert_general_kernel(Seq seq, uint64_t *__restrict__ deferred,
                                                                   int64_t words, Slot *__restrict__ table,
                                                                   int64_t mask, int32_t *status) {
   const int lane = lane_id();
-  const int64_t w = int64_t(uniform_u64((uint64_t(blockIdx.x) * kThreads + threadIdx.x) / kWave));
-  if (w >= words) return;
-  const uint64_t m = deferred[w];
-  if (m == 0) return;
-  if (lane == 0) deferred[w] = 0;
-  const int64_t q = w * 64 + lane;
-  int32_t slot = -1;
-  if ((m >> lane) & 1u) slot = insert_general<kPaired>(seq, q, table, mask, status);
-  // Of the lanes with one slot the first has the smallest occurrence: it alone
-  // lowers minpos (one update per occurrence queues at the frequent strings).
-  bool first = false;
-  for (uint64_t todo = __ballot(slot >= 0); todo != 0;) {
-    const int l = __builtin_ctzll(todo);
-    first = first || lane == l;
-    todo &= ~__ballot(slot == __builtin_amdgcn_readlane(slot, l));
-  }
-  if (first) {
-    int32_t *mp = &table[slot].minpos;
-    if (int32_t(q) < __hip_atomic_load(mp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(mp, int32_t(q));
+  const int64_t wave = int64_t(uniform_u64((uint64_t(blockIdx.x) * kThreads + threadIdx.x) / kWave));
+  const int64_t stride = int64_t(gridDim.x) * (kThreads / kWave);
+  // lane k < kMasksPerWave: the wave's mask k
+  const int64_t at = wave + lane * stride;
+  uint64_t own = 0;
+  if (lane < kMasksPerWave && at < words) own = deferred[at];
+  if (own != 0) deferred[at] = 0;
+  for (uint64_t left = __ballot(own != 0); left != 0; left &= left - 1) {
+    const int k = __builtin_ctzll(left);
+    const uint64_t m = (uint64_t(uint32_t(__builtin_amdgcn_readlane(int(own >> 32), k))) << 32) |
+                       uint32_t(__builtin_amdgcn_readlane(int(own), k));
+    const int64_t q = (wave + k * stride) * 64 + lane;
+    int32_t slot = -1;
+    if ((m >> lane) & 1u) slot = insert_general<kPaired>(seq, q, table, mask, status);
+    // Of the lanes with one slot the first has the smallest occurrence: it alone
+    // lowers minpos (one update per occurrence queues at the frequent strings).
+    bool first = false;
+    for (uint64_t todo = __ballot(slot >= 0); todo != 0;) {
+      const int l = __builtin_ctzll(todo);
+      first = first || lane == l;
+      todo &= ~__ballot(slot == __builtin_amdgcn_readlane(slot, l));
+    }
+    if (first) {
+      int32_t *mp = &table[slot].minpos;
+      if (int32_t(q) < __hip_atomic_load(mp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(mp, int32_t(q));
+    }
   }
 }
 
@@ -830,7 +842,8 @@ rdf2v_status insert_seq(const Seq &seq, const RankSeq &r, int32_t *status, hipSt
     insert_kernel<kPaired, kFastBlock, !kPaired, false><<<grid, dim3(kFastBlock), 0, stream>>>(
         seq, r.n, r.table, r.capacity - 1, r.bits, status);
   RDF2V_LAUNCH_CHECK();
-  insert_general_kernel<kPaired><<<dim3(unsigned(ceil_div(r.n, kThreads))), dim3(kThreads), 0, stream>>>(
+  const int64_t waves = std::max(ceil_div(r.words, kMasksPerWave), std::min(r.words, kGeneralWaves));
+  insert_general_kernel<kPaired><<<dim3(unsigned(ceil_div(waves, kThreads / kWave))), dim3(kThreads), 0, stream>>>(
       seq, r.bits, r.words, r.table, r.capacity - 1, status);
   RDF2V_LAUNCH_CHECK();
   return RDF2V_OK;
