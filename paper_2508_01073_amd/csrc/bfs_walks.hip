@@ -23,7 +23,11 @@
 // workspace, reruns the roots no tier could hold from scratch: it takes the
 // pairs of a level in order, a chunk at a time, with one "reached" bit per
 // entity instead of per-entity offers. All loops are bounded by the tree and
-// level sizes or the table size; a workgroup never waits for another.
+// level sizes or the table size; a workgroup never waits for another. The
+// entities of a level are distinct, so in a consistent CSR their rows hold at
+// most num_edges records; a level of more (rows that overlap, each of them in
+// range) ends its root with RDF2V_STATUS_BAD_CSR, so that the pair numbers of
+// every level that is walked are exact in 31 bits and increase.
 
 #include <algorithm>
 
@@ -203,6 +207,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kWpe))) void
   static_assert(kCap < kSlots && kTreeCap <= kCap && kTreeCap <= 32767, "table and tree sizes");
   static_assert(kSlots % (4 * NT) == 0, "the table is cleared four slots per thread at a time");
   static_assert(R <= 32, "win masks are 32-bit");
+  // Degrees are capped one above kLongRow, so that those of a level add up to
+  // about 2^30 at most whatever row_ptr holds.
+  constexpr int32_t kLongRow = (1 << 30) / kTreeCap;
   __shared__ int32_t scan_scratch[2][R * (NT / kWave)];  // alternated between block-wide scans
   __shared__ __align__(16) int32_t h_key[kSlots];
   __shared__ __align__(16) uint32_t h_val[kSlots];
@@ -255,6 +262,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kWpe))) void
     return -1;
   };
 
+  // A level of more pairs leaves the tier at once: many more than the table
+  // holds entities outgrow it (nearly always: only repeats could keep them in),
+  // a capped degree may be among more than kLongRow, and more than the CSR has
+  // records come from overlapping rows, which the bitmap pass reports.
+  const int32_t most_pairs = min(V > kCap ? kGiveUp * kCap : kLongRow, int32_t(E));
+
   int flags = 0;
   int32_t phase = 0;
   auto scratch = [&]() -> int32_t * { return scan_scratch[phase ^= 1]; };
@@ -285,7 +298,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kWpe))) void
       const bool ok = uint32_t(lo) <= uint32_t(hi) && uint32_t(hi) <= E;
       if (!ok) flags |= RDF2V_STATUS_BAD_CSR;
       t_lo[0] = lo;
-      t_deg[0] = ok ? hi - lo : 0;
+      t_deg[0] = ok ? min(hi - lo, kLongRow + 1) : 0;
       const int32_t s0 = entity_slot<kLog>(root);
       h_key[s0] = root;
       h_val[s0] = 0;
@@ -360,9 +373,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kWpe))) void
       total = carry;
       if (t == 0) dpre_s[nlev] = total;
       __syncthreads();
-      // A level of many more pairs than the table holds entities outgrows the
-      // tier (nearly always: only repeats could keep it in): leave at once.
-      if (V > kCap && total > kGiveUp * kCap) {  // uniform
+      if (total > most_pairs) {  // uniform
         overflow = true;
         break;
       }
@@ -457,7 +468,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kWpe))) void
             t_lev[pos] = uint8_t(lev + 1);
             t_child[pos] = 0;
             t_lo[pos] = row_lo_k[k];
-            t_deg[pos] = ok ? row_hi_k[k] - row_lo_k[k] : 0;
+            t_deg[pos] = ok ? min(row_hi_k[k] - row_lo_k[k], kLongRow + 1) : 0;
             t_child[node] = 1;
             h_val[slot_k[k]] = 0;
           }
@@ -703,14 +714,18 @@ __global__ __launch_bounds__(kWideThreads) void bfs_wide_kernel(const BfsArgs a,
     int32_t lb = 0, le = 1;   // the level being expanded: nodes [lb, le)
     int32_t levels = 1;       // levels with stored begins: level l is [level_begin[l], level_begin[l + 1])
     int32_t last_wins = 0;    // entities reached at the depth limit, or any number above max_walks (stored from le on)
-    bool overflow = false;
+    bool overflow = false, overlap = false;
     for (int32_t lev = 0; lev < a.depth && lb < le && !overflow; ++lev) {
       const int32_t nlev = le - lb;
       const bool last = lev + 1 == a.depth;
       // The level's nodes with records: row start and degree prefix. The pairs
       // of a level are at most the CSR's records, so their number fits 31 bits
-      // (if rows of an inconsistent CSR overlap it may not: record indices are
-      // checked).
+      // unless rows of an inconsistent CSR overlap. The sum of NT degrees is
+      // known exactly all the same: its low 32 bits from the prefix sum, the
+      // rest from the sum of the degrees' bits above 21 (below, each adds less
+      // than 2^21, NT of them less than 2^31), which shares the second scan.
+      constexpr int kHighShift = 21, kNodeBits = 11;
+      static_assert(NT == 1 << 10 && NT < 1 << kNodeBits, "room for the node count below the degrees' high bits");
       int32_t carry = 0, nx = 0;
       for (int32_t c0 = 0; c0 < nlev; c0 += NT) {
         const int32_t i = c0 + t;
@@ -722,17 +737,25 @@ __global__ __launch_bounds__(kWideThreads) void bfs_wide_kernel(const BfsArgs a,
           if (uint32_t(lo) <= uint32_t(hi) && uint32_t(hi) <= E) d = hi - lo;
           else flags |= RDF2V_STATUS_BAD_CSR;
         }
-        int32_t tot, with_rows;
+        int32_t tot, both;
         const int32_t ex = block_scan<NT>(d, scratch(), tot);
-        const int32_t at = nx + block_scan<NT>(d > 0 ? 1 : 0, scratch(), with_rows);
+        const int32_t at = nx + (block_scan<NT>((d > 0 ? 1 : 0) + ((d >> kHighShift) << kNodeBits), scratch(), both) &
+                                 ((1 << kNodeBits) - 1));
+        const uint32_t high = uint32_t(both) >> kNodeBits;
+        const int64_t records = (int64_t(high) << kHighShift) + (uint32_t(tot) - (high << kHighShift));
+        if (carry + records > int64_t(E)) {  // uniform
+          overlap = true;
+          break;
+        }
         if (d > 0) {
           x_node[at] = lb + i;
           x_lo[at] = lo;
           x_pre[at] = carry + ex;
         }
         carry += tot;
-        nx += with_rows;
+        nx += both & ((1 << kNodeBits) - 1);
       }
+      if (overlap) break;
       const int32_t total = carry;
       int32_t added = 0;  // nodes of the next level so far (at the depth limit: up to max_walks or a batch more)
       int32_t more = 0;   // whether this thread reached one that was not counted
@@ -922,6 +945,12 @@ __global__ __launch_bounds__(kWideThreads) void bfs_wide_kernel(const BfsArgs a,
       __syncthreads();
       continue;
     }
+    if (overlap) {
+      if (t == 0) a.counts[r] = 0;
+      flags |= RDF2V_STATUS_BAD_CSR;
+      __syncthreads();
+      continue;
+    }
     // Walks: the leaves among the stored levels in the order reached, then the
     // entities at the depth limit.
     int32_t leaves = 0;
@@ -1069,7 +1098,8 @@ rdf2v_status launch_wide(const BfsArgs &a, char *slices, size_t bytes, hipStream
   const int64_t per_cu = in_lds && 2 * (bitmap + kWideStaticLds) > size_t(lds) ? 1 : 2;
   int64_t groups = std::min<int64_t>(a.num_roots, std::max(1, cus) * per_cu);
   // at least 64K nodes (or V of them) per slice
-  const size_t least = head + wide_slice_bytes(std::min<int64_t>(V, 65536));
+  const int64_t least_nodes = std::min<int64_t>(V, 65536);
+  const size_t least = head + wide_slice_bytes(least_nodes);
   groups = std::max<int64_t>(1, std::min<int64_t>(groups, int64_t(bytes / least)));
   WidePass p;
   p.in_queue = a.queue[2];
@@ -1077,7 +1107,7 @@ rdf2v_status launch_wide(const BfsArgs &a, char *slices, size_t bytes, hipStream
   p.taken = a.queue_counts + kWideTaken;
   p.slices = slices;
   p.slice_bytes = bytes / size_t(groups) / 256 * 256;
-  p.node_cap = int32_t(std::min<int64_t>(V, wide_slice_nodes(p.slice_bytes - head)));
+  p.node_cap = int32_t(std::min<int64_t>(V, std::max(least_nodes, wide_slice_nodes(p.slice_bytes - head))));
   const bool all_fit = p.node_cap >= V;
   p.out_queue = all_fit ? nullptr : a.queue[0];
   p.out_count = all_fit ? nullptr : a.queue_counts + kWide2Length;

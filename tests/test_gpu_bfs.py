@@ -264,3 +264,56 @@ def test_unused_rows_are_filled(depth, max_walks):
     unused = np.arange(max_walks)[None, :] >= cnt[:, None]
     assert (tok[unused] == -1).all() and (ln[unused] == 0).all()
     assert (ln[~unused] > 0).all() and (tok[~unused][:, 0] >= 0).all()
+
+
+@pytest.mark.parametrize("V,E,depth", [
+    (1_200, 300_000, 2),       # an LDS tier: 600 rows, all of them the whole record array
+    (1_200, 300_000, 4),
+    (20, 300_000, 3),          # as few entities as one alignment unit of the workspace holds
+    (1_200, 1_500_000, 3),     # rows longer than a tier expands: the bitmap pass
+    (10_000, 1 << 20, 3),      # bitmap in LDS; 5,000 rows hold more than 2^32 records between them
+    (1_400_000, 1 << 20, 3),   # bitmap in the workspace
+])
+def test_overlapping_rows_end_their_roots(V, E, depth):
+    # row_ptr = 0, E, 0, E, ...: the rows of even entities are in range but all the same, those of
+    # odd entities run backwards and no record leads to them. A level of many even entities has
+    # more pairs than there are records, past 31 and 32 bits: its root ends with the status bit.
+    say(f"[bfs] overlapping rows V={V} E={E} depth={depth}")
+    rng = np.random.default_rng(V + E + depth)
+    row_ptr = torch.tensor([0, E], dtype=torch.int32, device=device()).repeat(V // 2 + 1)[:V + 1].contiguous()
+    edges = to_dev(np.stack([rng.integers(0, 3, E), 2 * rng.integers(0, V // 2, E)], axis=1))
+    csr = rd.Csr(row_ptr, edges, V, 3)
+    roots = 2 * np.arange(min(40, V // 2), dtype=np.int32)
+    max_walks, guard = 16, 64
+    width = 2 * depth + 1
+    tok = torch.full((len(roots) * max_walks * width + 2 * guard,), -9, dtype=torch.int32, device=device())
+    ln = torch.full((len(roots) * max_walks + 2 * guard,), -9, dtype=torch.int32, device=device())
+    st = new_status()
+    _, _, cnt = rd.rdf2v_bfs_walks(csr, to_dev(roots), depth, max_walks, tokens=tok[guard:-guard], lens=ln[guard:-guard],
+                                   status=st)
+    torch.cuda.synchronize()
+    assert int(st.item()) & rd.RDF2V_STATUS_BAD_CSR
+    assert bool((cnt >= 0).all()) and bool((cnt <= max_walks).all())
+    for buf in (tok, ln):
+        assert bool((buf[:guard] == -9).all()) and bool((buf[-guard:] == -9).all())
+
+
+@pytest.mark.parametrize("V", [12, 900])
+def test_rows_longer_than_a_tier_expands(V):
+    # a consistent graph in which three entities have rows of 1.4M records, around the longest row
+    # that an LDS tier takes: as root, below the root and at the depth limit
+    say(f"[bfs] rows of 1.4M records, V={V}")
+    P, far = 4, V - 3
+    rng = np.random.default_rng(V)
+    limit = (1 << 30) // 768
+    sizes = {0: limit + 1, 7: limit, far: limit + 2}
+    s = np.concatenate([np.full(n, v) for v, n in sizes.items()] + [rng.integers(1, V, 4 * V), [3, 3, 5]]).astype(np.int32)
+    o = rng.integers(0, V - 2, len(s)).astype(np.int32)
+    o[-3:] = (far, 4, 7)
+    p = rng.integers(0, P, len(s)).astype(np.int32)
+    rp, ed = oracle.build_csr(s, p, o, V, P)
+    csr = gpu_csr(s, p, o, V, P)
+    roots = np.array([3, 0, 5, far, 7, V - 1, 3], np.int32)
+    for depth in (1, 2, 3):
+        _compare(csr, rp, ed, V, P, roots, depth, V, f"long rows depth {depth}")
+        _compare(csr, rp, ed, V, P, roots, depth, 5, f"long rows depth {depth} truncated")
