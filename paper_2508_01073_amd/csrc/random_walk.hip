@@ -24,6 +24,7 @@
 // CSR or an out-of-range id raises a status bit instead of faulting.
 
 #include "common.hpp"
+#include "grid.hpp"
 #include "walk.hpp"
 
 namespace rdf2v {
@@ -181,14 +182,22 @@ rdf2v_status launch_walk_kernel(const WalkArgs &a, hipStream_t stream) {
   const int64_t blocks = (a.walk_count + kBlock - 1) / kBlock;
   if (blocks >= (int64_t(1) << 31)) return RDF2V_ERR_TOO_LARGE;
   const size_t lds = size_t(kBlock) * width * 4;
-  switch (a.token_kind) {
-    case RDF2V_TOKENS_TRIPLES: launch_kind<kBlock, RDF2V_TOKENS_TRIPLES>(a, blocks, lds, stream); break;
-    case RDF2V_TOKENS_ENTITIES: launch_kind<kBlock, RDF2V_TOKENS_ENTITIES>(a, blocks, lds, stream); break;
-    case RDF2V_TOKENS_PROPERTIES: launch_kind<kBlock, RDF2V_TOKENS_PROPERTIES>(a, blocks, lds, stream); break;
-    default: return RDF2V_ERR_INVALID_ARGUMENT;
-  }
-  RDF2V_LAUNCH_CHECK();
-  return RDF2V_OK;
+  return for_each_launch(blocks, kBlock, 1, [&](int64_t first, int64_t count) -> rdf2v_status {
+    WalkArgs part = a;  // the walks from the launch's first block's on
+    const int64_t row0 = first * kBlock;
+    part.walk_begin += row0;
+    part.walk_count -= row0;
+    part.tokens += row0 * width;
+    part.lens += row0;
+    switch (a.token_kind) {
+      case RDF2V_TOKENS_TRIPLES: launch_kind<kBlock, RDF2V_TOKENS_TRIPLES>(part, count, lds, stream); break;
+      case RDF2V_TOKENS_ENTITIES: launch_kind<kBlock, RDF2V_TOKENS_ENTITIES>(part, count, lds, stream); break;
+      case RDF2V_TOKENS_PROPERTIES: launch_kind<kBlock, RDF2V_TOKENS_PROPERTIES>(part, count, lds, stream); break;
+      default: return RDF2V_ERR_INVALID_ARGUMENT;
+    }
+    RDF2V_LAUNCH_CHECK();
+    return RDF2V_OK;
+  });
 }
 
 }  // namespace

@@ -23,6 +23,7 @@
 #include <algorithm>
 
 #include "common.hpp"
+#include "grid.hpp"
 #include "launch.hpp"
 
 namespace rdf2v {
@@ -420,6 +421,24 @@ rdf2v_status count_items(const int32_t *tokens, const int32_t *len, int64_t num_
   return RDF2V_OK;
 }
 
+// Runs emit(part, grid) over the emit blocks (of `threads` threads) in as few
+// launches as HIP takes: a part's arguments begin at its first block.
+template <class Emit>
+rdf2v_status launch_emit(const EmitArgs &a, int64_t blocks, int threads, Emit emit) {
+  return for_each_launch(blocks, threads, kCountThreads, [&](int64_t first, int64_t count) -> rdf2v_status {
+    EmitArgs part = a;
+    const int64_t r0 = first * a.walks;
+    part.tokens += r0 * a.width;
+    part.len += r0;
+    part.n -= r0;
+    part.firsts += first;
+    part.partials += first / kCountThreads;
+    emit(part, dim3(unsigned(count)));
+    RDF2V_LAUNCH_CHECK();
+    return RDF2V_OK;
+  });
+}
+
 }  // namespace
 
 rdf2v_status launch_skipgram_pairs(const int32_t *tokens, const int32_t *len, int64_t num_walks,
@@ -442,13 +461,12 @@ rdf2v_status launch_skipgram_pairs(const int32_t *tokens, const int32_t *len, in
                                              capacity, count_out, workspace, status_dev, stream, a, blocks);
   if (st != RDF2V_OK || capacity == 0 || blocks == 0) return st;
   int2 *out = reinterpret_cast<int2 *>(pairs_out);
-  const dim3 grid{unsigned(blocks)};
-  if (block == 256) pair_emit_kernel<true, 256><<<grid, dim3(256), stage_bytes(256), stream>>>(a, out);
-  else if (block == 128) pair_emit_kernel<true, 128><<<grid, dim3(128), stage_bytes(128), stream>>>(a, out);
-  else if (block == 64) pair_emit_kernel<true, 64><<<grid, dim3(64), stage_bytes(64), stream>>>(a, out);
-  else pair_emit_kernel<false, kThreads><<<grid, dim3(kThreads), 0, stream>>>(a, out);
-  RDF2V_LAUNCH_CHECK();
-  return RDF2V_OK;
+  return launch_emit(a, blocks, block ? block : kThreads, [&](const EmitArgs &p, dim3 grid) {
+    if (block == 256) pair_emit_kernel<true, 256><<<grid, dim3(256), stage_bytes(256), stream>>>(p, out);
+    else if (block == 128) pair_emit_kernel<true, 128><<<grid, dim3(128), stage_bytes(128), stream>>>(p, out);
+    else if (block == 64) pair_emit_kernel<true, 64><<<grid, dim3(64), stage_bytes(64), stream>>>(p, out);
+    else pair_emit_kernel<false, kThreads><<<grid, dim3(kThreads), 0, stream>>>(p, out);
+  });
 }
 
 rdf2v_status launch_cbow_examples(const int32_t *tokens, const int32_t *len, int64_t num_walks, int32_t width,
@@ -473,15 +491,14 @@ rdf2v_status launch_cbow_examples(const int32_t *tokens, const int32_t *len, int
   const rdf2v_status st = count_items<true>(tokens, len, num_walks, width, window, (block ? block : kThreads) / width,
                                             capacity, count_out, workspace, status_dev, stream, a, blocks);
   if (st != RDF2V_OK || capacity == 0 || blocks == 0) return st;
-  const dim3 grid{unsigned(blocks)};
-  if (block == 256)
-    cbow_emit_kernel<256><<<grid, dim3(256), stage_bytes(256), stream>>>(a, centers_out, contexts_out);
-  else if (block == 128)
-    cbow_emit_kernel<128><<<grid, dim3(128), stage_bytes(128), stream>>>(a, centers_out, contexts_out);
-  else
-    cbow_direct_kernel<kThreads><<<grid, dim3(kThreads), 0, stream>>>(a, centers_out, contexts_out);
-  RDF2V_LAUNCH_CHECK();
-  return RDF2V_OK;
+  return launch_emit(a, blocks, block ? block : kThreads, [&](const EmitArgs &p, dim3 grid) {
+    if (block == 256)
+      cbow_emit_kernel<256><<<grid, dim3(256), stage_bytes(256), stream>>>(p, centers_out, contexts_out);
+    else if (block == 128)
+      cbow_emit_kernel<128><<<grid, dim3(128), stage_bytes(128), stream>>>(p, centers_out, contexts_out);
+    else
+      cbow_direct_kernel<kThreads><<<grid, dim3(kThreads), 0, stream>>>(p, centers_out, contexts_out);
+  });
 }
 
 }  // namespace rdf2v

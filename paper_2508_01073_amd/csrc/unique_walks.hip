@@ -22,6 +22,7 @@
 // over tiles of rows. Integer streaming work.
 
 #include "common.hpp"
+#include "grid.hpp"
 #include "launch.hpp"
 
 namespace rdf2v {
@@ -77,8 +78,8 @@ __global__ __launch_bounds__(kThreads) void keep_kernel(const int32_t *__restric
                                                         const int32_t *__restrict__ len, int64_t n,
                                                         int32_t width, int32_t group,
                                                         const uint64_t *__restrict__ hash,
-                                                        int32_t *__restrict__ keep) {
-  const int64_t r = int64_t(blockIdx.x) * kThreads + threadIdx.x;
+                                                        int32_t *__restrict__ keep, int64_t first_row) {
+  const int64_t r = first_row + int64_t(blockIdx.x) * kThreads + threadIdx.x;
   if (r >= n) return;
   const int64_t g0 = r / group * group;
   const uint64_t h = hash[r];
@@ -527,27 +528,32 @@ rdf2v_status launch_unique_walks(const int32_t *tokens, const int32_t *len, int6
     const size_t tile_bytes = size_t(rows_per_block) * width * sizeof(int32_t);
     const int64_t nb = ceil_div(num_walks, rows_per_block);
     if (nb >= (int64_t(1) << 31)) return RDF2V_ERR_TOO_LARGE;
-    if (nb > 0 && rows_per_wave > 0) {
-      const int32_t lds_per_wave = (rows_per_wave * width + 7 + 3) / 4 * 4;
-      wave_keep_kernel<<<dim3(unsigned(nb)), dim3(kThreads), size_t(lds_per_wave) * kKeepWaves * sizeof(int32_t),
-                         stream>>>(tokens, len, num_walks, width, group, rows_per_wave, lds_per_wave, keep_flags,
-                                   block_counts, status_dev);
+    const int32_t lds_per_wave = (rows_per_wave * width + 7 + 3) / 4 * 4;
+    // Each launch takes the rows from its first block's on.
+    rdf2v_status st = for_each_launch(nb, nt, 1, [&](int64_t first, int64_t count) -> rdf2v_status {
+      const int64_t r0 = first * rows_per_block;
+      const dim3 grid{unsigned(count)};
+      if (rows_per_wave > 0)
+        wave_keep_kernel<<<grid, dim3(kThreads), size_t(lds_per_wave) * kKeepWaves * sizeof(int32_t), stream>>>(
+            tokens + r0 * width, len + r0, num_walks - r0, width, group, rows_per_wave, lds_per_wave, keep_flags + r0,
+            block_counts + first, status_dev);
+      else
+        keep_kernel<<<grid, dim3(nt), tile_bytes, stream>>>(tokens + r0 * width, len + r0, num_walks - r0, width, group,
+                                                            rows_per_block, keep_flags + r0, block_counts + first,
+                                                            status_dev);
       RDF2V_LAUNCH_CHECK();
-    } else if (nb > 0) {
-      keep_kernel<<<dim3(unsigned(nb)), dim3(nt), tile_bytes, stream>>>(tokens, len, num_walks, width, group,
-                                                                        rows_per_block, keep_flags, block_counts,
-                                                                        status_dev);
-      RDF2V_LAUNCH_CHECK();
-    }
-    const rdf2v_status st = scan_counts(block_counts, nb, tile_sums, count_out, stream);
+      return RDF2V_OK;
+    });
+    if (st == RDF2V_OK) st = scan_counts(block_counts, nb, tile_sums, count_out, stream);
     if (st != RDF2V_OK) return st;
-    if (nb > 0) {
-      compact_kernel<<<dim3(unsigned(nb)), dim3(nt), tile_bytes, stream>>>(tokens, len, num_walks, width,
-                                                                           rows_per_block, keep_flags, block_counts,
-                                                                           tokens_out, len_out);
+    return for_each_launch(nb, nt, 1, [&](int64_t first, int64_t count) -> rdf2v_status {
+      const int64_t r0 = first * rows_per_block;
+      compact_kernel<<<dim3(unsigned(count)), dim3(nt), tile_bytes, stream>>>(
+          tokens + r0 * width, len + r0, num_walks - r0, width, rows_per_block, keep_flags + r0, block_counts + first,
+          tokens_out, len_out);
       RDF2V_LAUNCH_CHECK();
-    }
-    return RDF2V_OK;
+      return RDF2V_OK;
+    });
   };
   auto fits = [&](int nt) { return group <= nt && int64_t(nt / group) * group * width <= kGroupStageInts; };
   if (fits(kThreads)) return main_path(group_keep_kernel<kThreads>, group_compact_kernel<kThreads>, kThreads);
@@ -558,17 +564,27 @@ rdf2v_status launch_unique_walks(const int32_t *tokens, const int32_t *len, int6
                                                   align_up(size_t(num_walks) * 4, 256));
   const int64_t nb = ceil_div(num_walks, kTile);
   if (num_walks > 0) {
-    const unsigned rows_blocks = unsigned(ceil_div(num_walks, kThreads));
-    if (int64_t(width) * kThreads <= kStageInts)
-      row_hash_kernel<true><<<dim3(rows_blocks), dim3(kThreads), 0, stream>>>(tokens, len, num_walks, width,
-                                                                             hash, status_dev);
-    else
-      row_hash_kernel<false><<<dim3(rows_blocks), dim3(kThreads), 0, stream>>>(tokens, len, num_walks, width,
-                                                                              hash, status_dev);
-    RDF2V_LAUNCH_CHECK();
-    keep_kernel<<<dim3(rows_blocks), dim3(kThreads), 0, stream>>>(tokens, len, num_walks, width, group, hash,
-                                                                 keep);
-    RDF2V_LAUNCH_CHECK();
+    const int64_t rows_blocks = ceil_div(num_walks, kThreads);
+    rdf2v_status st = for_each_launch(rows_blocks, kThreads, 1, [&](int64_t first, int64_t count) -> rdf2v_status {
+      const int64_t r0 = first * kThreads;
+      const dim3 grid{unsigned(count)}, block{kThreads};
+      if (int64_t(width) * kThreads <= kStageInts)
+        row_hash_kernel<true><<<grid, block, 0, stream>>>(tokens + r0 * width, len + r0, num_walks - r0, width, hash + r0,
+                                                         status_dev);
+      else
+        row_hash_kernel<false><<<grid, block, 0, stream>>>(tokens + r0 * width, len + r0, num_walks - r0, width, hash + r0,
+                                                          status_dev);
+      RDF2V_LAUNCH_CHECK();
+      return RDF2V_OK;
+    });
+    if (st != RDF2V_OK) return st;
+    st = for_each_launch(rows_blocks, kThreads, 1, [&](int64_t first, int64_t count) -> rdf2v_status {
+      keep_kernel<<<dim3(unsigned(count)), dim3(kThreads), 0, stream>>>(tokens, len, num_walks, width, group, hash, keep,
+                                                                       first * kThreads);
+      RDF2V_LAUNCH_CHECK();
+      return RDF2V_OK;
+    });
+    if (st != RDF2V_OK) return st;
     keep_count_kernel<<<dim3(unsigned(nb)), dim3(kThreads), 0, stream>>>(keep, num_walks, partials);
     RDF2V_LAUNCH_CHECK();
   }

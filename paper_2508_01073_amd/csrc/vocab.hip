@@ -42,6 +42,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "grid.hpp"
 #include "launch.hpp"
 
 namespace rdf2v {
@@ -643,13 +644,15 @@ struct RankSeq {
 struct RankPair {
   RankSeq seq[2];
   unsigned first_blocks;  // workgroups of sequence 0
+  unsigned launched;      // workgroups of earlier launches of the same pass
 };
 struct SeqBlock {
   int seq;
   int64_t block;
 };
-__device__ __forceinline__ SeqBlock seq_block(unsigned first_blocks) {
-  return blockIdx.x < first_blocks ? SeqBlock{0, int64_t(blockIdx.x)} : SeqBlock{1, int64_t(blockIdx.x - first_blocks)};
+__device__ __forceinline__ SeqBlock seq_block(const RankPair &pair) {
+  const unsigned b = pair.launched + blockIdx.x;
+  return b < pair.first_blocks ? SeqBlock{0, int64_t(b)} : SeqBlock{1, int64_t(b - pair.first_blocks)};
 }
 
 // One 16-byte store per thread, each workgroup writing 4 KiB: the tables as
@@ -657,7 +660,7 @@ __device__ __forceinline__ SeqBlock seq_block(unsigned first_blocks) {
 // spare).
 __global__ __launch_bounds__(kThreads) void init_kernel(const RankPair pair) {
   constexpr int64_t kGroups = sizeof(Slot) / 16;
-  const SeqBlock at = seq_block(pair.first_blocks);
+  const SeqBlock at = seq_block(pair);
   const RankSeq &r = pair.seq[at.seq];
   const int64_t i = at.block * kThreads + threadIdx.x;
   if (i >= r.capacity * kGroups) return;
@@ -671,7 +674,7 @@ __global__ __launch_bounds__(kThreads) void init_kernel(const RankPair pair) {
 // first occurrence (or -1 for an unused slot) also goes to the compact id
 // array, so that slot_id_kernel reads 4 bytes per slot instead of the table.
 __global__ __launch_bounds__(kThreads) void mark_kernel(const RankPair pair) {
-  const SeqBlock at = seq_block(pair.first_blocks);
+  const SeqBlock at = seq_block(pair);
   const RankSeq &r = pair.seq[at.seq];
   const int64_t s = at.block * kThreads + threadIdx.x;
   if (s >= r.capacity) return;
@@ -684,7 +687,7 @@ __global__ __launch_bounds__(kThreads) void mark_kernel(const RankPair pair) {
 
 __global__ __launch_bounds__(kThreads) void popc_count_kernel(const RankPair pair) {
   __shared__ int64_t scratch[kThreads / kWave];
-  const SeqBlock at = seq_block(pair.first_blocks);
+  const SeqBlock at = seq_block(pair);
   const RankSeq &r = pair.seq[at.seq];
   const int64_t base = at.block * kWordTile;
   int64_t s = 0;
@@ -736,7 +739,7 @@ __device__ __forceinline__ int32_t prefix_words(const RankSeq &r, int64_t base, 
 
 __global__ __launch_bounds__(kThreads) void word_prefix_kernel(const RankPair pair) {
   __shared__ int32_t scratch[kThreads / kWave];
-  const SeqBlock at = seq_block(pair.first_blocks);
+  const SeqBlock at = seq_block(pair);
   const RankSeq &r = pair.seq[at.seq];
   const int64_t base = at.block * kWordTile;
   prefix_words<kThreads>(r, base, min(base + kWordTile, r.words), int32_t(r.partials[at.block]), scratch);
@@ -756,7 +759,7 @@ __global__ __launch_bounds__(kSmallPrefixThreads) void small_prefix_kernel(const
 // The id of a used slot: the rank of its first occurrence among all first
 // occurrences (the compact array holds that occurrence, or -1).
 __global__ __launch_bounds__(kThreads) void slot_id_kernel(const RankPair pair) {
-  const SeqBlock at = seq_block(pair.first_blocks);
+  const SeqBlock at = seq_block(pair);
   const RankSeq &r = pair.seq[at.seq];
   const int64_t s = at.block * kThreads + threadIdx.x;
   if (s >= r.capacity) return;
@@ -876,13 +879,17 @@ rdf2v_status launch_build_vocabulary(const VocabColumns &cols, int64_t num_tripl
           {subj_ids, obj_ids}};
   Seq pred{{{cols.chars[1], cols.offsets[1], cols.bytes[1]}, {cols.chars[1], cols.offsets[1], cols.bytes[1]}},
            {pred_ids, pred_ids}};
-  RankPair pair{{rank_seq(plan.ent, max_entities, ws, counts_out), rank_seq(plan.pred, max_predicates, ws, counts_out + 1)}, 0};
+  RankPair pair{{rank_seq(plan.ent, max_entities, ws, counts_out), rank_seq(plan.pred, max_predicates, ws, counts_out + 1)}, 0, 0};
   // Launches `kernel` with a workgroup per `per` of the two amounts.
   auto both = [&](auto kernel, int64_t ent, int64_t pred, int64_t per) -> rdf2v_status {
     pair.first_blocks = unsigned(ceil_div(ent, per));
-    kernel<<<dim3(pair.first_blocks + unsigned(ceil_div(pred, per))), dim3(kThreads), 0, stream>>>(pair);
-    RDF2V_LAUNCH_CHECK();
-    return RDF2V_OK;
+    return for_each_launch(ceil_div(ent, per) + ceil_div(pred, per), kThreads, 1,
+                           [&](int64_t first, int64_t count) -> rdf2v_status {
+                             pair.launched = unsigned(first);
+                             kernel<<<dim3(unsigned(count)), dim3(kThreads), 0, stream>>>(pair);
+                             RDF2V_LAUNCH_CHECK();
+                             return RDF2V_OK;
+                           });
   };
   rdf2v_status st = RDF2V_OK;
   if (num_triples > 0) {
