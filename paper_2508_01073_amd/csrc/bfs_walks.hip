@@ -992,31 +992,57 @@ __global__ __launch_bounds__(kWideThreads) void bfs_wide_kernel(const BfsArgs a,
   if (flags && a.status != nullptr) atomicOr(a.status, flags);
 }
 
-// The rows past counts[r] of root r = blockIdx.x + k * gridDim.x: one
-// contiguous range of tokens and one of lengths, filled with 16-byte stores
-// between their ends. Bound by HBM writes (100K roots of the 1M-triple uniform
-// graph, depth 3, 14 % of 3.3 GB left unused: 110 us, against 480 us for filling
-// everything beforehand).
-__device__ __forceinline__ void fill_run(int32_t *p, int64_t count, int32_t value) {
+// The rows past counts[r] of a root: one contiguous range of tokens and one of
+// lengths, filled with 16-byte stores between their ends. Bound by HBM writes
+// where they are many (100K roots of the 1M-triple uniform graph, depth 3, 14 % of
+// 3.3 GB left unused: 87 us, against 479 us for filling everything beforehand).
+// 2^lane_bits threads of a workgroup take a root, fewer where a root's rows are few
+// (100K roots of 8 rows of 3 tokens: 73 -> 10 us within a call, from a workgroup
+// each), and 2^slice_bits workgroups share one where there are fewer roots than fill
+// the chip (one root of 1M rows of 9: 301 -> 18 us).
+// kPast: the stores go past the caches. That is faster for what does not fit
+// the Infinity Cache (459 MB: 87 us, 142 with plain stores) and slower for what
+// does (99 MB: 24.6 us, 18.8 with plain ones; 6 MB: 10.3, 9.0; 36 MB: equal).
+template <bool kPast>
+__device__ __forceinline__ void fill_run(int32_t *p, int64_t count, int32_t value, int32_t t, int32_t lanes) {
   typedef int32_t v4i32 __attribute__((ext_vector_type(4)));
-  const int64_t t = threadIdx.x;
   const int64_t head = min(count, int64_t((16 - (reinterpret_cast<uintptr_t>(p) & 15)) & 15) / 4);
   const int64_t groups = (count - head) >> 2;
   if (t < head) p[t] = value;
   v4i32 *p4 = reinterpret_cast<v4i32 *>(p + head);
-  for (int64_t g = t; g < groups; g += blockDim.x) __builtin_nontemporal_store(v4i32{value, value, value, value}, p4 + g);
+  for (int64_t g = t; g < groups; g += lanes) {
+    const v4i32 v = {value, value, value, value};
+    if (kPast) __builtin_nontemporal_store(v, p4 + g);
+    else p4[g] = v;
+  }
   const int64_t tail = head + 4 * groups + t;
   if (tail < count) p[tail] = value;  // at most three: t < 3
 }
 
-__global__ __launch_bounds__(256) void bfs_fill_unused_kernel(const int32_t *__restrict__ counts, int64_t num_roots,
-                                                              int32_t max_walks, int32_t width,
-                                                              int32_t *__restrict__ tokens, int32_t *__restrict__ lens) {
-  for (int64_t r = blockIdx.x; r < num_roots; r += gridDim.x) {
-    const int64_t used = min(max(counts[r], 0), max_walks), unused = max_walks - used;
-    const int64_t row = r * max_walks + used;
-    fill_run(tokens + row * width, unused * width, -1);
-    fill_run(lens + row, unused, 0);
+constexpr int kFillThreads = 256;
+constexpr int kFillLeastLaneBits = 3;   // 8 lanes: above the three ints before and behind the 16-byte stores
+constexpr int64_t kFillSliceInts = 4096;
+constexpr int64_t kFillMostSliced = 65536;  // workgroups that slices add up to at most
+static_assert(kFillSliceInts >= 8 * kFillThreads, "a sliced root has a workgroup to a slice");
+constexpr int64_t kFillCachedInts = int64_t(32) << 20;  // half of the Infinity Cache's 256 MB
+
+template <bool kPast>
+__global__ __launch_bounds__(kFillThreads) void bfs_fill_unused_kernel(const int32_t *__restrict__ counts,
+                                                                       int64_t num_roots, int32_t max_walks, int32_t width,
+                                                                       int32_t lane_bits, int32_t slice_bits, int32_t slice_rows,
+                                                                       int32_t *__restrict__ tokens,
+                                                                       int32_t *__restrict__ lens) {
+  const int32_t lanes = 1 << lane_bits, t = threadIdx.x & (lanes - 1);
+  const uint32_t slice = blockIdx.x & ((1u << slice_bits) - 1);
+  const int32_t first = int32_t(min(slice * uint32_t(slice_rows), uint32_t(max_walks)));
+  const int32_t end = first + min(max_walks - first, slice_rows);
+  const int32_t step = int32_t(gridDim.x >> slice_bits) * (kFillThreads >> lane_bits);
+  const int32_t r0 = int32_t(blockIdx.x >> slice_bits) * (kFillThreads >> lane_bits) + int32_t(threadIdx.x >> lane_bits);
+  for (int64_t r = r0; r < num_roots; r += step) {
+    const int32_t lo = min(max(counts[r], first), end);
+    const int64_t row = r * max_walks + lo;
+    fill_run<kPast>(tokens + row * width, int64_t(end - lo) * width, -1, t, lanes);
+    fill_run<kPast>(lens + row, end - lo, 0, t, lanes);
   }
 }
 
@@ -1024,9 +1050,18 @@ __global__ __launch_bounds__(256) void bfs_fill_unused_kernel(const int32_t *__r
 
 rdf2v_status launch_bfs_fill_unused(const int32_t *counts, int64_t num_roots, int32_t max_walks, int32_t width,
                                     int32_t *tokens_out, int32_t *len_out, hipStream_t stream) {
-  const int64_t blocks = std::min<int64_t>(num_roots, int64_t(1) << 20);
-  bfs_fill_unused_kernel<<<dim3(unsigned(blocks)), dim3(256), 0, stream>>>(counts, num_roots, max_walks, width,
-                                                                          tokens_out, len_out);
+  const int64_t ints = int64_t(max_walks) * width;  // of one root
+  int lane_bits = kFillLeastLaneBits;  // up to two 16-byte stores a lane
+  while (1 << lane_bits < kFillThreads && ints > int64_t(8) << lane_bits) ++lane_bits;
+  int slice_bits = 0;  // slices of about kFillSliceInts
+  while (ints > kFillSliceInts << slice_bits && num_roots << slice_bits < kFillMostSliced / 2) ++slice_bits;
+  const int32_t slice_rows = int32_t((int64_t(max_walks) + (int64_t(1) << slice_bits) - 1) >> slice_bits);
+  const int64_t per_block = kFillThreads >> lane_bits;
+  const int64_t blocks = std::min<int64_t>((num_roots + per_block - 1) / per_block, int64_t(1) << 20) << slice_bits;
+  const bool cached = ints <= kFillCachedInts / num_roots;
+  auto kernel = cached ? bfs_fill_unused_kernel<false> : bfs_fill_unused_kernel<true>;
+  kernel<<<dim3(unsigned(blocks)), dim3(kFillThreads), 0, stream>>>(counts, num_roots, max_walks, width, lane_bits,
+                                                                   slice_bits, slice_rows, tokens_out, len_out);
   RDF2V_LAUNCH_CHECK();
   return RDF2V_OK;
 }

@@ -317,3 +317,33 @@ def test_rows_longer_than_a_tier_expands(V):
     for depth in (1, 2, 3):
         _compare(csr, rp, ed, V, P, roots, depth, V, f"long rows depth {depth}")
         _compare(csr, rp, ed, V, P, roots, depth, 5, f"long rows depth {depth} truncated")
+
+
+@pytest.mark.parametrize("roots,max_walks,width,offset", [
+    (1, 100_000, 9, 1), (3, 30_001, 5, 2), (70, 2_000, 7, 3),   # several workgroups to a root
+    (1, 1, 1, 0), (300, 2, 3, 1), (1001, 7, 5, 2),              # several roots to a workgroup
+    (40, 300, 3, 3), (500, 129, 17, 1), (9, 1, 129, 2),         # about a workgroup to a root
+    (40, 50_001, 17, 3), (150_000, 75, 3, 1),                   # more than the Infinity Cache takes
+])
+def test_fill_unused_writes_the_unused_rows_only(roots, max_walks, width, offset):
+    # outputs that begin anywhere in a 16-byte group, with ints around them that stay as they are
+    say(f"[bfs] fill {roots} roots x {max_walks} rows of {width}")
+    rng = np.random.default_rng(roots + max_walks + width)
+    counts = rng.integers(0, max_walks + 1, roots).astype(np.int32)
+    counts[rng.random(roots) < 0.2] = max_walks
+    for k, odd in enumerate((-3, 0, max_walks + 5, max_walks)):  # outside [0, max_walks]: as clamped
+        if k < roots:
+            counts[k * 7 % roots] = odd
+    guard = 8
+    tok = torch.full((roots * max_walks * width + 2 * guard + offset,), -9, dtype=torch.int32, device=device())
+    ln = torch.full((roots * max_walks + 2 * guard + offset,), -9, dtype=torch.int32, device=device())
+    a, b = guard + offset, guard
+    st = rd._native().rdf2v_bfs_fill_unused(to_dev(counts).data_ptr(), roots, max_walks, width, tok[a:].data_ptr(),
+                                            ln[a:].data_ptr(), torch.cuda.current_stream().cuda_stream)
+    assert st == rd.RDF2V_OK
+    unused = np.arange(max_walks)[None, :] >= np.clip(counts, 0, max_walks)[:, None]
+    ref_t = np.where(unused[:, :, None], -1, np.full((1, 1, width), -9)).reshape(-1)
+    ref_l = np.where(unused, 0, -9).reshape(-1)
+    for buf, ref in ((tok.cpu().numpy(), ref_t), (ln.cpu().numpy(), ref_l)):
+        assert np.array_equal(buf[a:len(buf) - b], ref)
+        assert (buf[:a] == -9).all() and (buf[len(buf) - b:] == -9).all()
