@@ -993,38 +993,45 @@ __global__ __launch_bounds__(kWideThreads) void bfs_wide_kernel(const BfsArgs a,
 }
 
 // The rows past counts[r] of a root: one contiguous range of tokens and one of
-// lengths, filled with 16-byte stores between their ends. Bound by HBM writes
-// where they are many (100K roots of the 1M-triple uniform graph, depth 3, 14 % of
-// 3.3 GB left unused: 87 us, against 479 us for filling everything beforehand).
+// lengths, filled with 16-byte stores between their ends, a wave's stores at
+// whole 128-byte lines. Bound by HBM writes where they are many (100K roots of
+// the 1M-triple uniform graph, depth 3, 14 % of 3.3 GB left unused: 93 us, against
+// 478 us for filling everything beforehand; 26,230 roots with 97 % of 644 MB unused:
+// 126 us, where a fill of everything takes 99, its waves following the address 4
+// KB each; done like that here, the waves that find used rows cost 218 us in the
+// first case).
 // 2^lane_bits threads of a workgroup take a root, fewer where a root's rows are few
 // (100K roots of 8 rows of 3 tokens: 73 -> 10 us within a call, from a workgroup
 // each), and 2^slice_bits workgroups share one where there are fewer roots than fill
 // the chip (one root of 1M rows of 9: 301 -> 18 us).
 // kPast: the stores go past the caches. That is faster for what does not fit
-// the Infinity Cache (459 MB: 87 us, 142 with plain stores) and slower for what
-// does (99 MB: 24.6 us, 18.8 with plain ones; 6 MB: 10.3, 9.0; 36 MB: equal).
+// the Infinity Cache (459 MB: 93 us, 143 with plain stores) and slower for what
+// does (163 MB: 36 us, 30 with plain ones; 99 MB: 24.6, 18.8; 36 MB: equal).
 template <bool kPast>
 __device__ __forceinline__ void fill_run(int32_t *p, int64_t count, int32_t value, int32_t t, int32_t lanes) {
   typedef int32_t v4i32 __attribute__((ext_vector_type(4)));
-  const int64_t head = min(count, int64_t((16 - (reinterpret_cast<uintptr_t>(p) & 15)) & 15) / 4);
-  const int64_t groups = (count - head) >> 2;
-  if (t < head) p[t] = value;
-  v4i32 *p4 = reinterpret_cast<v4i32 *>(p + head);
-  for (int64_t g = t; g < groups; g += lanes) {
+  const int32_t shift = int32_t((reinterpret_cast<uintptr_t>(p) & 127) >> 2);  // ints into a 128-byte line
+  int32_t *line = p - shift;
+  const int64_t end = shift + count, g0 = (shift + 3) >> 2, g1 = end >> 2;  // whole groups of four ints
+  for (int64_t g = t; g < g1; g += lanes) {
     const v4i32 v = {value, value, value, value};
-    if (kPast) __builtin_nontemporal_store(v, p4 + g);
-    else p4[g] = v;
+    if (g < g0) continue;
+    if (kPast) __builtin_nontemporal_store(v, reinterpret_cast<v4i32 *>(line) + g);
+    else reinterpret_cast<v4i32 *>(line)[g] = v;
   }
-  const int64_t tail = head + 4 * groups + t;
-  if (tail < count) p[tail] = value;  // at most three: t < 3
+  // the ints before the first and behind the last of them
+  if (t < 8) {
+    const int64_t q = t < 4 ? 4 * g0 - 4 + t : 4 * max(g0, g1) + (t - 4);
+    if (q >= shift && q < end) line[q] = value;
+  }
 }
 
 constexpr int kFillThreads = 256;
-constexpr int kFillLeastLaneBits = 3;   // 8 lanes: above the three ints before and behind the 16-byte stores
+constexpr int kFillLeastLaneBits = 3;   // 8 lanes for the three ints before and behind the 16-byte stores
 constexpr int64_t kFillSliceInts = 4096;
 constexpr int64_t kFillMostSliced = 65536;  // workgroups that slices add up to at most
 static_assert(kFillSliceInts >= 8 * kFillThreads, "a sliced root has a workgroup to a slice");
-constexpr int64_t kFillCachedInts = int64_t(32) << 20;  // half of the Infinity Cache's 256 MB
+constexpr int64_t kFillCachedInts = int64_t(56) << 20;  // 7/8 of the Infinity Cache's 256 MB
 
 template <bool kPast>
 __global__ __launch_bounds__(kFillThreads) void bfs_fill_unused_kernel(const int32_t *__restrict__ counts,
@@ -1058,7 +1065,7 @@ rdf2v_status launch_bfs_fill_unused(const int32_t *counts, int64_t num_roots, in
   const int32_t slice_rows = int32_t((int64_t(max_walks) + (int64_t(1) << slice_bits) - 1) >> slice_bits);
   const int64_t per_block = kFillThreads >> lane_bits;
   const int64_t blocks = std::min<int64_t>((num_roots + per_block - 1) / per_block, int64_t(1) << 20) << slice_bits;
-  const bool cached = ints <= kFillCachedInts / num_roots;
+  const bool cached = ints + max_walks <= kFillCachedInts / num_roots;
   auto kernel = cached ? bfs_fill_unused_kernel<false> : bfs_fill_unused_kernel<true>;
   kernel<<<dim3(unsigned(blocks)), dim3(kFillThreads), 0, stream>>>(counts, num_roots, max_walks, width, lane_bits,
                                                                    slice_bits, slice_rows, tokens_out, len_out);
