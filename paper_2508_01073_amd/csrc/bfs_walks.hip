@@ -109,7 +109,19 @@ struct BigTier {
 // A level of more than kGiveUp * kCap pairs leaves a tier before its offers
 // (1,000 roots of the 20M-triple power-law graph that no tier can hold: the
 // two tiers took 2.8 + 8.1 ms until their tables were full, 0.06 + 0.09 ms
-// with this and the checks while a table fills).
+// with this and the checks while a table fills). At 2, 4, 8 and 16, in us:
+//   power law, 50K entities, 300K triples, depth 2, 20,000 roots: 1,149, 1,307, 1,390, 1,457
+//   power law, 10K, 60K, depth 3, 5,000 roots:                      928,   940, 1,016, 1,068
+//   power law, 200K, 2M, depth 2, 2,000 roots:                      795,   803,   787,   799
+//   uniform, 100K, 2M, depth 3, 2,000 roots:                        620,   772,   766,   774
+//   4,000 roots with 7,000 pairs to 2,500 entities at depth 2:      499,   232,   233,   231
+//   the same with 24,000 pairs:                                     690,   692,   548,   544
+// So 2 serves graphs whose levels grow with their pairs, and levels of 6,000 to
+// 24,000 pairs that meet few entities pay up to twice for it. (Leaving instead
+// when the first chunk of such a level repeats too little took 239 in the fifth
+// row, but 2.4 % more for the 1M-triple uniform graph, which never gets there,
+// through the registers it holds, and up to 55 % more for some hundred roots
+// of small power-law graphs, whose levels look like few entities at first.)
 constexpr int32_t kGiveUp = 2;
 constexpr int32_t kFreeSlot = -1;
 constexpr uint32_t kNoOffer = 0xFFFFFFFFu;
