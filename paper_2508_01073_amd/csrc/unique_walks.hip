@@ -352,9 +352,12 @@ __device__ __forceinline__ void wave_lds_fence() {
 }
 
 // 32-bit multiplicative hash of a row's length and valid tokens: equal hashes
-// are confirmed, so it need only spread the rows of a wave.
+// are confirmed, so it need only spread the rows of a wave. The length is spread
+// first (constants of xxHash32): left as it is, a first token equal to it made the hash 0, and short rows
+// of tokens below the row's width met in a few slots (groups of 50 rows of 2 such
+// tokens: 257 -> 97 us).
 __device__ __forceinline__ uint32_t short_hash(const int32_t *row, int32_t L, uint32_t seed) {
-  uint32_t h = seed ^ uint32_t(L);
+  uint32_t h = seed ^ (uint32_t(L) * 0x27d4eb2fu + 0x165667b1u);
   for (int32_t j = 0; j < L; ++j) {
     h = (h ^ uint32_t(row[j])) * 0x9e3779b1u;
     h ^= h >> 15;
@@ -415,9 +418,9 @@ __global__ __launch_bounds__(kThreads) void wave_keep_kernel(const int32_t *__re
     lens[wave][lane] = L;
     wave_lds_fence();
     uint32_t slot = 0, mine = 0;
+    const int32_t g = lane / group;
     if (lane < rows) {
       const int32_t *row = rows_lds + lane * width;
-      const int32_t g = lane / group;
       const uint32_t h = short_hash(row, L, uint32_t(g) * 0x85ebca6bu);
       mine = (h << kWaveRowBits) | uint32_t(lane + 1);
       slot = h >> (32 - kWaveRowBits);
@@ -435,8 +438,9 @@ __global__ __launch_bounds__(kThreads) void wave_keep_kernel(const int32_t *__re
     bool k = lane < rows;
     if (k && table[slot] != mine) {
       const int32_t *row = rows_lds + lane * width;
+      const int32_t first_row = g * group;
       auto same_row = [&](int32_t o) {
-        if (lens[wave][o] != L || o / group != lane / group) return false;
+        if (o < first_row || lens[wave][o] != L) return false;
         int32_t differ = 0;  // four tokens a step, their reads in flight together (past the end: the last one again)
         for (int32_t j = 0; differ == 0 && j < L; j += 4) {
 #pragma unroll
@@ -448,7 +452,7 @@ __global__ __launch_bounds__(kThreads) void wave_keep_kernel(const int32_t *__re
         return differ == 0;
       };
       k = !same_row(int32_t(table[slot] & ((1u << kWaveRowBits) - 1)) - 1);
-      for (int32_t o = lane / group * group; k && o < lane; ++o) k = !same_row(o);
+      for (int32_t o = first_row; k && o < lane; ++o) k = !same_row(o);
     }
     count = __popcll(__ballot(k));
     if (lane < rows) keep[r0 + lane] = k ? 1 : 0;
@@ -501,6 +505,16 @@ __global__ __launch_bounds__(NT) void group_compact_kernel(const int32_t *__rest
 
 }  // namespace
 
+// Rows that a wave keeps (whole groups), or 0 where blocks do. A wave with few
+// of its lanes in use loses to a block of narrow rows, whose time is not the
+// rows' bytes: groups of 33 rows of 5 tokens 156 us by waves and 135 by blocks,
+// of 40 139 and 134, of 50 125 and 130, of 64 113 and 127; of 33 rows of 9 tokens
+// 151 and 144, of 11 tokens 138 and 136, of 17 204 and 204 (4M to 6M rows).
+static int32_t wave_rows(int32_t group, int32_t width) {
+  const int32_t rows = group <= kWave ? (kWave / group) * group : 0;
+  return width < 10 && rows < 43 ? 0 : rows;
+}
+
 size_t unique_walks_workspace_bytes(int64_t num_walks) {
   const int64_t nb = ceil_div(num_walks, kTile);
   return align_up(size_t(num_walks) * 8, 256) + align_up(size_t(num_walks) * 4, 256) +
@@ -522,8 +536,7 @@ rdf2v_status launch_unique_walks(const int32_t *tokens, const int32_t *len, int6
   int64_t *tile_sums = reinterpret_cast<int64_t *>(ws + align_up(size_t(num_walks) * 8, 256) +
                                                    align_up(size_t(num_walks) * 4, 256));
   auto main_path = [&](auto keep_kernel, auto compact_kernel, int nt) -> rdf2v_status {
-    // groups of at most a wave's rows: whole groups per wave
-    const int32_t rows_per_wave = group <= kWave && nt == kThreads ? (kWave / group) * group : 0;
+    const int32_t rows_per_wave = nt == kThreads ? wave_rows(group, width) : 0;
     const int32_t rows_per_block = rows_per_wave > 0 ? kKeepWaves * rows_per_wave : (nt / group) * group;
     const size_t tile_bytes = size_t(rows_per_block) * width * sizeof(int32_t);
     const int64_t nb = ceil_div(num_walks, rows_per_block);

@@ -164,3 +164,23 @@ def test_unique_walks_wave_groups(n, group, width, offset):
     got_t, got_l = rd.rdf2v_unique_walks(t, to_dev(ln), group, status=new_status())
     ref_t, ref_l = oracle.unique_walks(tok, ln, group)
     assert np.array_equal(got_l.cpu().numpy(), ref_l) and np.array_equal(got_t.cpu().numpy(), ref_t)
+
+
+@pytest.mark.parametrize("width", [2, 9, 10, 17])
+@pytest.mark.parametrize("group", [21, 22, 32, 33, 42, 43, 50])
+def test_unique_walks_of_waves_and_blocks(group, width):
+    # on both sides of the group sizes and row widths at which blocks take over from waves; tokens
+    # as small as the lengths, whole walks repeated
+    say(f"[unique] waves and blocks group={group} width={width}")
+    n = 9 * 4 * group + 5
+    rng = np.random.default_rng(100 * group + width)
+    ln = rng.integers(1, width + 1, n).astype(np.int32)
+    tok = np.where(np.arange(width) < ln[:, None], rng.integers(0, 4, (n, width)), -1).astype(np.int32)
+    again = rng.random(n) < 0.4
+    again[0] = False
+    src = np.maximum(np.arange(n) - rng.integers(1, group + 1, n), 0)
+    for r in np.flatnonzero(again):
+        tok[r], ln[r] = tok[src[r]], ln[src[r]]
+    ref_t, ref_l = oracle.unique_walks(tok, ln, group)
+    got_t, got_l = _gpu_unique(tok, ln, group)
+    assert_rows_equal(got_t, got_l, ref_t, ref_l, f"group {group} width {width}")
