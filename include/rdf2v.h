@@ -96,7 +96,8 @@ size_t rdf2v_build_csr_workspace_size(int64_t num_triples, int32_t num_entities)
  * Sec. 3.1 loads the tokenised triples into device memory as a graph).
  *
  *   subj, pred, obj   [num_triples] int32 ids (device).
- *   row_ptr_out       [num_entities + 1] int32 (device), written.
+ *   row_ptr_out       [num_entities + 1] int32 (device), written; may overlap
+ *                     the inputs, which are then lost.
  *   edges_out         [num_triples][2] int32 (predicate, object) (device),
  *                     written; 8-byte aligned; must not alias the inputs.
  *   workspace         device scratch of at least

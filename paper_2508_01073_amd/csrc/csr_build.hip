@@ -391,8 +391,8 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(8)
 
 // ---------------------------------------------------------------------------
 // One workgroup, one launch: at most kMostTile triples. The passes exchange keys
-// and payloads through LDS. With at most kSmallEntities entities row_ptr is
-// the scan of a histogram of the subjects; with more, the sorted subjects go
+// and payloads through LDS. With row_ptr (at most kSmallEntities entities) it
+// becomes the scan of a histogram of the subjects; else the sorted subjects go
 // to keys_out for the row_ptr kernels. What bounds it is the chain of LDS
 // round trips and barriers; the passes as kernels of their own would be bound
 // by the gaps between thirteen launches (5,000 triples over 1,000
@@ -408,7 +408,7 @@ __global__ __launch_bounds__(kSortThreads) void csr_small_kernel(
   __shared__ __align__(16) char stage[kStageBytes<kRounds>];
   __shared__ int digit_start[kMaxBins];
   __shared__ int2 scan_scratch[kSortThreads / kWave];
-  const bool with_row_ptr = num_entities <= kSmallEntities;
+  const bool with_row_ptr = row_ptr != nullptr;
   const int lane = lane_id();
   const int wave = threadIdx.x / kWave;
   uint32_t key[kRounds];
@@ -747,7 +747,8 @@ SortPlan plan_csr_build(int64_t num_triples, int32_t num_entities) {
   // the bits below it to 16, so that it can write 2-byte keys. Every pass needs
   // room for its table: the reserved one; else, for the first pass, the idle
   // key buffer, for the last one the part of its key buffer that narrow keys
-  // leave, for any that leaves no bases behind the row_ptr output. Where that
+  // leave, for any later one that leaves no bases behind the row_ptr output (the
+  // inputs, which that may overlap, have been read by then). Where that
   // is not to be had (some tens of thousands of triples), narrower digits are.
   // Rounds of a tile: as long as the tiles are fewer than about two per CU,
   // smaller tiles use more of the chip (1M triples, scatter of 8 bits: 13.9 us
@@ -776,7 +777,7 @@ SortPlan plan_csr_build(int64_t num_triples, int32_t num_entities) {
       if (need <= space.counts + space.partials) p.off_tables[k] = off_tables;
       else if (k == 0 && last > 0 && need <= align_up(T * 4, 256)) p.off_tables[k] = p.off_keys_b;
       else if (k == last && need + own_keys <= align_up(T * 4, 256)) p.off_tables[k] = out + own_keys;
-      else if ((k < last || p.key_out == 4) && need + 256 <= in_row_ptr) p.table_in_row_ptr[k] = true;
+      else if (k > 0 && (k < last || p.key_out == 4) && need + 256 <= in_row_ptr) p.table_in_row_ptr[k] = true;
       else fits = false;
     }
     if (fits) return p;
@@ -869,19 +870,28 @@ rdf2v_status launch_csr_build(const int32_t *subj, const int32_t *pred, const in
   int2 *edges2 = reinterpret_cast<int2 *>(edges_out);
   char *ws = static_cast<char *>(workspace);
   if (plan.passes < 0) return RDF2V_ERR_WORKSPACE;
+  // row_ptr_out may overlap the inputs (only edges_out may not): it is then left
+  // alone until they have been read.
+  auto overlaps = [&](const int32_t *in) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(in), b = reinterpret_cast<uintptr_t>(row_ptr_out);
+    return a < b + (size_t(num_entities) + 1) * 4 && b < a + size_t(T) * 4;
+  };
+  bool fill_later = overlaps(subj) || overlaps(pred) || overlaps(obj);
   if (plan.passes == 0) {
     uint32_t *keys = reinterpret_cast<uint32_t *>(ws + plan.off_keys_a);
+    const bool with_row_ptr = num_entities <= kSmallEntities && !fill_later;
     csr_small_kernel<<<dim3(1), dim3(kSortThreads), 0, stream>>>(keys_in, pred, obj, int(T), num_entities,
-                                                                num_predicates, plan.total_bits, row_ptr_out, edges2,
-                                                                keys, status_dev);
+                                                                num_predicates, plan.total_bits,
+                                                                with_row_ptr ? row_ptr_out : nullptr, edges2, keys,
+                                                                status_dev);
     RDF2V_LAUNCH_CHECK();
-    if (num_entities <= kSmallEntities) return RDF2V_OK;
+    if (with_row_ptr) return RDF2V_OK;
     const rdf2v_status st = launch_row_ptr_fill(row_ptr_out, num_entities, stream);
     if (st != RDF2V_OK) return st;
     return launch_row_ptr<4>({keys, nullptr, 0, 0}, T, num_entities, row_ptr_out, stream);
   }
   int2 *pay_tmp = reinterpret_cast<int2 *>(ws + plan.off_payload);
-  bool fill_later = false;  // row_ptr_out holds a table until the sort is done
+  // a later pass's table may lie in row_ptr_out until the sort is done
   for (int pass = 0; pass < plan.passes; ++pass) fill_later = fill_later || plan.table_in_row_ptr[pass];
   PassArgs p{};
   p.keys_in = keys_in;

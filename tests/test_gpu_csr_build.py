@@ -116,3 +116,22 @@ def test_tile_and_digit_plans(T, V):
     np.cumsum(degree, out=row_ptr[1:])
     assert np.array_equal(csr.row_ptr.cpu().numpy(), row_ptr)
     assert np.array_equal(starts.cpu().numpy(), np.flatnonzero(degree))
+
+
+@pytest.mark.parametrize("T,V", [(5_000, 1_000), (8_192, 8_000), (9_000, 500), (20_000, 3_000), (60_000, 50_000),
+                                 (400_000, 300_000), (1_200_000, 100_000)])
+@pytest.mark.parametrize("column", [0, 1, 2])
+def test_row_ptr_in_place_of_an_input(T, V, column):
+    # row_ptr written over a column of the triples, from its first element and from somewhere inside
+    say(f"[csr] row_ptr over column {column}, T={T} V={V}")
+    P = 7
+    rng = np.random.default_rng(T + V + column)
+    s, p, o = (rng.integers(0, n, T).astype(np.int32) for n in (V, P, V))
+    rp, ed = oracle.build_csr(s, p, o, V, P)
+    for first in (0, (T - V - 1) // 2):
+        cols = [to_dev(x) for x in (s, p, o)]
+        st = new_status()
+        csr = rd.rdf2v_build_csr(*cols, V, P, status=st, row_ptr=cols[column][first:first + V + 1])
+        torch.cuda.synchronize()
+        assert int(st.item()) == 0
+        assert_csr_equal(csr, rp, ed)
