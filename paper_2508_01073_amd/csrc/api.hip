@@ -226,7 +226,7 @@ RDF2V_API rdf2v_status rdf2v_unique_walks(const int32_t *tokens, const int32_t *
 }
 
 RDF2V_API size_t rdf2v_bfs_walks_workspace_size(int32_t num_entities, int64_t num_roots) {
-  // rdf2v_bfs_walks takes fewer than 2^31 roots (its per-level stamps are int32)
+  // rdf2v_bfs_walks takes fewer than 2^31 roots (its queues hold them as int32)
   if (num_entities < 0 || num_roots < 0 || num_roots >= kInt32Limit) return 0;
   return rdf2v::bfs_walks_workspace_bytes(num_entities, num_roots);
 }
@@ -241,9 +241,7 @@ RDF2V_API rdf2v_status rdf2v_bfs_walks(const rdf2v_csr *csr, const int32_t *root
   if (num_roots < 0 || depth < 0 || depth > RDF2V_MAX_DEPTH || max_walks < 1) return RDF2V_ERR_INVALID_ARGUMENT;
   if (csr->num_edges >= kInt32Limit || id_space_too_large(csr->num_entities, csr->num_predicates))
     return RDF2V_ERR_TOO_LARGE;
-  // the per-level stamps of one workgroup (int32) must not run out
-  if (num_roots >= kInt32Limit || (num_roots > 0 && (num_roots + 1) * int64_t(depth + 1) >= kInt32Limit))
-    return RDF2V_ERR_TOO_LARGE;
+  if (num_roots >= kInt32Limit) return RDF2V_ERR_TOO_LARGE;  // the queues hold roots as int32
   if (num_roots > INT64_MAX / max_walks / (2 * int64_t(depth) + 1)) return RDF2V_ERR_TOO_LARGE;
   if (num_roots == 0) return RDF2V_OK;
   if (roots == nullptr || tokens_out == nullptr || len_out == nullptr || counts_out == nullptr)

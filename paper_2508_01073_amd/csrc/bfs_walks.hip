@@ -289,7 +289,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kWpe))) void
     if (in_queue != nullptr) {  // uniform
       if (t == 0) next_s = atomicAdd(taken, 1);
       __syncthreads();
-      k_in = next_s;
+      k_in = uint32_t(next_s);  // past the queue's end by the grid at most
       __syncthreads();
     }
     if (k_in >= n_in) break;
@@ -701,9 +701,9 @@ __global__ __launch_bounds__(kWideThreads) void bfs_wide_kernel(const BfsArgs a,
   for (;;) {
     if (t == 0) next_s = atomicAdd(p.taken, 1);
     __syncthreads();
-    const int32_t k_in = next_s;
+    const uint32_t k_in = uint32_t(next_s);  // past the queue's end by the grid at most
     __syncthreads();
-    if (k_in >= n_in) break;
+    if (k_in >= uint32_t(n_in)) break;
     const int64_t r = p.in_queue[k_in];
     const int32_t root = a.roots[r];  // in range: the tiers queue no other
     if constexpr (kLdsBits) {

@@ -306,6 +306,10 @@ def test_bfs_walks_validation(lib):
     assert f(ctypes.byref(c), FAKE, 5, 3, 4, FAKE, FAKE, FAKE, None, need, None, None) == pkg.RDF2V_ERR_WORKSPACE
     assert f(ctypes.byref(c), FAKE, 5, 3, 4, FAKE, FAKE, FAKE, WS, need - 1, None, None) == pkg.RDF2V_ERR_WORKSPACE
     assert f(ctypes.byref(c), FAKE, 2**40, 64, 4, FAKE, FAKE, FAKE, WS, need, None, None) == pkg.RDF2V_ERR_TOO_LARGE
+    assert f(ctypes.byref(c), FAKE, 2**31, 3, 4, FAKE, FAKE, FAKE, WS, need, None, None) == pkg.RDF2V_ERR_TOO_LARGE
+    # fewer than 2^31 roots are taken at any depth (here: as far as the workspace check)
+    for roots in (34_000_000, 2**31 - 1):
+        assert f(ctypes.byref(c), FAKE, roots, 64, 4, FAKE, FAKE, FAKE, None, 0, None, None) == pkg.RDF2V_ERR_WORKSPACE
     assert f(ctypes.byref(c), FAKE, 0, 3, 4, None, None, None, None, 0, None, None) == pkg.RDF2V_OK
     # the workspace is bounded (about 4 GiB) however many roots there are
     assert pkg.rdf2v_bfs_walks_workspace_size(50_000_000, 10**7) <= (1 << 32) + 3 * 10**9
