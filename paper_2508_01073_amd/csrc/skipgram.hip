@@ -33,7 +33,7 @@ typedef int32_t v2i32 __attribute__((ext_vector_type(2)));
 typedef int32_t v4i32 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
-constexpr int kCountThreads = 1024;  // emit blocks counted per workgroup
+constexpr int kCountThreads = 1024;  // of a workgroup that counts emit blocks
 
 // All arithmetic inside a block is 32-bit: a walk has at most 129 tokens, a
 // block at most 32,768 items, and the window is clamped to the row (a wider
@@ -69,17 +69,18 @@ __device__ __forceinline__ int32_t clamped(int32_t L, int32_t width, int &bad) {
 }
 
 // Where the emit blocks' outputs begin: the items of `walks` consecutive walks
-// (one emit block) per thread, their exclusive prefix inside the workgroup to
-// firsts, the workgroup's total to partials. A lone workgroup also writes what
+// (one emit block) per kLanes threads, their exclusive prefix inside the workgroup
+// to firsts, the workgroup's total to partials. A lone workgroup also writes what
 // partials_scan_kernel would.
-template <bool kCbow>
+template <bool kCbow, int kLanes>
 __global__ __launch_bounds__(kCountThreads) void item_count_kernel(const int32_t *__restrict__ len, int64_t n,
                                                                    int32_t width, int32_t window, int32_t walks,
                                                                    int64_t emit_blocks, int32_t *__restrict__ firsts,
                                                                    int64_t *__restrict__ partials, int64_t *total_out,
                                                                    int32_t *status) {
   __shared__ int32_t scratch[kCountThreads / kWave];
-  const int64_t b = int64_t(blockIdx.x) * kCountThreads + threadIdx.x;
+  const int64_t b = int64_t(blockIdx.x) * (kCountThreads / kLanes) + threadIdx.x / kLanes;
+  const int32_t lane = threadIdx.x % kLanes;
   const int32_t w = clamp_window(window, width);
   constexpr int32_t kAhead = 8;  // lengths of a thread in flight together
   int32_t s = 0;
@@ -87,17 +88,19 @@ __global__ __launch_bounds__(kCountThreads) void item_count_kernel(const int32_t
   if (b < emit_blocks) {
     const int64_t r0 = b * walks;
     const int32_t rows = int32_t(min(int64_t(walks), n - r0));
-    for (int32_t i0 = 0; i0 < rows; i0 += kAhead) {
+    for (int32_t i0 = lane; i0 < rows; i0 += kAhead * kLanes) {
       int32_t L[kAhead];
 #pragma unroll
-      for (int32_t k = 0; k < kAhead; ++k) L[k] = i0 + k < rows ? len[r0 + i0 + k] : 0;
+      for (int32_t k = 0; k < kAhead; ++k) L[k] = i0 + k * kLanes < rows ? len[r0 + i0 + k * kLanes] : 0;
 #pragma unroll
       for (int32_t k = 0; k < kAhead; ++k) s += walk_items<kCbow>(clamped(L[k], width, bad), w);
     }
   }
+#pragma unroll
+  for (int32_t off = 1; off < kLanes; off <<= 1) s += __shfl_xor(s, off, kWave);
   int32_t total;
-  const int32_t ex = block_exclusive_scan<kCountThreads>(s, scratch, total);
-  if (b < emit_blocks) firsts[b] = ex;
+  const int32_t ex = block_exclusive_scan<kCountThreads>(lane == 0 ? s : 0, scratch, total);
+  if (b < emit_blocks && lane == 0) firsts[b] = ex;
   if (threadIdx.x == 0) {
     partials[blockIdx.x] = gridDim.x == 1 ? 0 : total;
     if (gridDim.x == 1) *total_out = total;
@@ -139,7 +142,8 @@ struct EmitArgs {
   int32_t walks;              // per emit block: kBlock / width
   uint32_t width_inverse;     // ceil(2^32 / width); 0 for width 1
   const int32_t *firsts;
-  const int64_t *partials;
+  const int64_t *partials;    // per 2^group_bits emit blocks
+  int32_t group_bits;
   int64_t capacity;
   int32_t *status;
 };
@@ -157,7 +161,7 @@ __device__ __forceinline__ int32_t load_walks(const EmitArgs &a, BlockWalks<kBlo
   const int32_t t = threadIdx.x;
   const int64_t r0 = int64_t(blockIdx.x) * a.walks;
   const int32_t walks = int32_t(min(int64_t(a.walks), a.n - r0));
-  first = a.partials[blockIdx.x / kCountThreads] + a.firsts[blockIdx.x];
+  first = a.partials[blockIdx.x >> a.group_bits] + a.firsts[blockIdx.x];
   int bad = 0;  // reported by the count
   const int32_t token = t < walks * a.width ? a.tokens[r0 * a.width + t] : 0;
   const int32_t L = t < walks ? clamped(a.len[r0 + t], a.width, bad) : 0;
@@ -395,7 +399,11 @@ rdf2v_status count_items(const int32_t *tokens, const int32_t *len, int64_t num_
                          hipStream_t stream, EmitArgs &a, int64_t &emit_blocks) {
   emit_blocks = ceil_div(num_walks, walks);
   if (emit_blocks >= (int64_t(1) << 31)) return RDF2V_ERR_TOO_LARGE;
-  const int64_t nb = ceil_div(emit_blocks, kCountThreads);
+  // One thread counts an emit block's walks, eight do where there are more than
+  // 64 of them (rows of up to three tokens), which leave few emit blocks: 6M rows
+  // of 3 tokens, window 2, 172 -> 114 us a call.
+  const int32_t lanes = walks > kWave ? 8 : 1, group = kCountThreads / lanes;
+  const int64_t nb = ceil_div(emit_blocks, group);
   int32_t *firsts = static_cast<int32_t *>(workspace);
   int64_t *partials = reinterpret_cast<int64_t *>(firsts + (emit_blocks + 1) / 2 * 2);
   a.tokens = tokens;
@@ -407,11 +415,13 @@ rdf2v_status count_items(const int32_t *tokens, const int32_t *len, int64_t num_
   a.width_inverse = uint32_t(((uint64_t(1) << 32) + uint64_t(width) - 1) / uint64_t(width));
   a.firsts = firsts;
   a.partials = partials;
+  a.group_bits = lanes == 1 ? 10 : 7;
   a.capacity = capacity;
   a.status = status_dev;
   if (nb > 0) {
-    item_count_kernel<kCbow><<<dim3(unsigned(nb)), dim3(kCountThreads), 0, stream>>>(
-        len, num_walks, width, window, walks, emit_blocks, firsts, partials, count_out, status_dev);
+    auto kernel = lanes == 1 ? item_count_kernel<kCbow, 1> : item_count_kernel<kCbow, 8>;
+    kernel<<<dim3(unsigned(nb)), dim3(kCountThreads), 0, stream>>>(len, num_walks, width, window, walks, emit_blocks,
+                                                                  firsts, partials, count_out, status_dev);
     RDF2V_LAUNCH_CHECK();
   }
   if (nb != 1) {
@@ -432,7 +442,7 @@ rdf2v_status launch_emit(const EmitArgs &a, int64_t blocks, int threads, Emit em
     part.len += r0;
     part.n -= r0;
     part.firsts += first;
-    part.partials += first / kCountThreads;
+    part.partials += first >> a.group_bits;
     emit(part, dim3(unsigned(count)));
     RDF2V_LAUNCH_CHECK();
     return RDF2V_OK;

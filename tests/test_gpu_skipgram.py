@@ -137,3 +137,20 @@ def test_outputs_at_any_offset_and_cut(n, width, window, offset):
         assert (c[:offset] == -7).all() and (c[offset + cap:] == -7).all()
         assert (x[:offset] == -7).all() and (x[offset + wide:] == -7).all()
         assert int(st.item()) == (rd.RDF2V_STATUS_CAPACITY if cap < len(centers) else 0)
+
+
+@pytest.mark.parametrize("width,walks", [(1, 256), (2, 128), (3, 85)])
+@pytest.mark.parametrize("blocks", [127, 128, 129, 1025])
+def test_narrow_rows_in_many_blocks(width, walks, blocks):
+    # more walks to an emit block than a wave has lanes: eight threads count a block, 128 blocks a
+    # workgroup; numbers of blocks around one workgroup and several
+    for n in (walks * blocks, walks * blocks - 1, walks * (blocks - 1) + 1):
+        say(f"[pairs] narrow rows width={width} n={n}")
+        rng = np.random.default_rng(n + width)
+        ln = rng.integers(0, width + 1, n).astype(np.int32)
+        tok = np.where(np.arange(width) < ln[:, None], rng.integers(0, 10**6, (n, width)), -1).astype(np.int32)
+        t, l = to_dev(tok), to_dev(ln)
+        assert np.array_equal(_gpu_pairs(t, l, 2), oracle.skipgram_pairs(tok, ln, 2))
+        centers, contexts = rd.rdf2v_cbow_examples(t, l, 2)
+        ref_c, ref_x = oracle.cbow_examples(tok, ln, 2)
+        assert np.array_equal(centers.cpu().numpy(), ref_c) and np.array_equal(contexts.cpu().numpy(), ref_x)
