@@ -459,7 +459,9 @@ rdf2v_status launch_skipgram_pairs(const int32_t *tokens, const int32_t *len, in
   // smallest that fits one of kMaxStageBytes: several small blocks per CU keep
   // the write stream going while others load rows and place pairs, down to
   // about 8 KB of output each (8M walks of 17 tokens, window 5: 1.55 ms with
-  // 128 threads and 7.8 KB, 1.69 with 256 and 16.8, 1.68 with 64 and 3.4).
+  // 128 threads and 7.8 KB, 1.69 with 256 and 16.8, 1.68 with 64 and 3.4). Limits
+  // of 7, 8, 10, 12 and 14 KB, over widths 1 to 129 and windows 1 to 64, differ by
+  // no more than their runs do.
   const int64_t per_walk = max_walk_pairs(width, window);
   auto stage_bytes = [&](int block) { return size_t(per_walk * (block / width)) * sizeof(int2) + 4 * kLineInts; };
   int block = 0;  // 0: no stage
@@ -482,20 +484,24 @@ rdf2v_status launch_skipgram_pairs(const int32_t *tokens, const int32_t *len, in
 rdf2v_status launch_cbow_examples(const int32_t *tokens, const int32_t *len, int64_t num_walks, int32_t width,
                                   int32_t window, int32_t *centers_out, int32_t *contexts_out, int64_t capacity,
                                   int64_t *count_out, void *workspace, int32_t *status_dev, hipStream_t stream) {
-  // The staged kernel holds a block's context rows in LDS: B rows of
-  // 2 * window ints for B threads, 256-thread blocks up to 32 KB, else 128.
-  // The output-order kernel needs no stage. Measured on 8M walks of 17 tokens
-  // (ms, staged / output order): windows 1: 0.95 / 0.93, 2: 1.12 / 1.00,
-  // 5: 1.55 / 1.55, 10: 2.62 / 2.68, 20 (128 threads): 4.88 / 5.09, 40 (then
-  // 64-thread staged blocks): 14.2 / 9.1; so the staged kernel serves windows
-  // of 5 and more while a block of at least 128 threads holds its stage.
-  // (Earlier, at window 5 on 48.9M walks: 512-thread blocks, or two or four
-  // positions per thread, were 2-50 % slower.)
+  // The staged kernel holds a block's context rows in LDS, at most B rows of
+  // 2 * window ints for B threads: 256 threads up to 14 KB, 128 up to 32 KB. The
+  // output-order kernel needs no stage. us, staged / output order, for as many
+  // rows of 17 tokens (9 tokens) as give about 1.2 GB, 6M at most:
+  //   window 1: 481 / 533 (231 / 258)   2: 282 / 289 (256 / 264)   3: 239 / 273 (241 / 282)
+  //          4: 248 / 228 (261 / 241)   5: 266 / 282 (273 / 289)   6: 255 / 279 (263 / 289)
+  //          7: 281 / 294 (263 / 304)   8: 273 / 250 (274 / 259)  10: 259 / 283 (260 / 289)
+  //         12: 257 / 273 (259 / 280)  16: 487 / 241 (492 / 248)  20: 247 / 280
+  //         24: 296 / 246              32: 533 / 241
+  // Threads place their context rows side by side, 2 * window banks apart, so
+  // windows of a multiple of 8 queue at four banks or fewer and take the output
+  // order, like window 4 and those whose stage does not fit.
+  const bool staged = window % 8 != 0 && window != 4;
   const size_t row_bytes = size_t(2) * size_t(window) * sizeof(int32_t);
   auto stage_bytes = [&](int block) { return size_t(block / width * width) * row_bytes + 4 * kLineInts; };
   int block = 0;  // 0: output order
   for (int b : {128, 256})
-    if (window >= 5 && width <= b && stage_bytes(b) <= (block == 0 ? kMaxStageBytes : kBestStageBytes)) block = b;
+    if (staged && width <= b && stage_bytes(b) <= (block == 0 ? kMaxStageBytes : kBestStageBytes)) block = b;
   EmitArgs a;
   int64_t blocks;
   const rdf2v_status st = count_items<true>(tokens, len, num_walks, width, window, (block ? block : kThreads) / width,

@@ -35,7 +35,7 @@ def _random_rows(width, n, seed):
 @pytest.mark.parametrize("width", [1, 2, 9, 17, 33, 129])
 @pytest.mark.parametrize("window", [1, 2, 5, 20, 128])
 def test_random_rows(width, window):
-    # windows 20 and 128 take the 128-thread, 64-thread and unstaged launches
+    # windows 1, 2, 5 and 20 take staged launches where a block's context rows fit, 128 the output order
     say(f"[cbow] random rows width={width} window={window}")
     tok, ln = _random_rows(width, 2000, width * 1000 + window)
     c, x = _gpu_cbow(to_dev(tok), to_dev(ln), window)
@@ -115,3 +115,18 @@ def test_powerlaw_corpus_slices_and_pairs():
         rows, cols = np.nonzero(x != -1)
         pairs = rd.rdf2v_skipgram_pairs(sl_t, sl_l, 5).cpu().numpy()
         assert np.array_equal(np.stack([c[rows], x[rows, cols]], axis=1), pairs)
+
+
+@pytest.mark.parametrize("width", [1, 8, 17, 65, 129])
+@pytest.mark.parametrize("window", [2, 3, 4, 7, 8, 9, 16, 24, 31])
+def test_windows_of_both_forms(width, window):
+    # windows on both sides of the rule that picks the staged or the output-order kernel
+    say(f"[cbow] both forms width={width} window={window}")
+    rng = np.random.default_rng(1000 * width + window)
+    n = 700
+    ln = rng.integers(0, width + 1, n).astype(np.int32)
+    ln[::3] = width
+    tok = np.where(np.arange(width) < ln[:, None], rng.integers(0, 10**6, (n, width)), -1).astype(np.int32)
+    centers, contexts = rd.rdf2v_cbow_examples(to_dev(tok), to_dev(ln), window)
+    ref_c, ref_x = oracle.cbow_examples(tok, ln, window)
+    assert np.array_equal(centers.cpu().numpy(), ref_c) and np.array_equal(contexts.cpu().numpy(), ref_x)
