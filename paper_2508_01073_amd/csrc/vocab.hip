@@ -490,14 +490,16 @@ __device__ __forceinline__ bool same_string_global(const StrCol *ca, int64_t sa,
 // their block's stage, strings too long for an inline copy, compares left
 // undecided): the same hash and table, with strings read from global memory
 // and equal tags settled against the representative's bytes whenever the
-// inline copy does not decide. A chain of dependent reads per occurrence, so
-// those of one step are in flight together. (Table loads at agent scope, which
-// go past L2, queue at the lines of frequent strings: 148 + 111 us on 20M
-// triples.)
+// inline copy does not decide. A chain of dependent reads per occurrence.
+// kAhead: a string's first words are read together and kept, and the slot's
+// with its key, for launches whose waves are all on the chip at once; else one
+// word after the other, in registers that let nearly twice the waves hide each
+// other's reads. (Table loads at agent scope, which go past L2, queue at the
+// lines of frequent strings: 148 + 111 us on 20M triples.)
 // Returns the slot (-1: the table is full), also left in the id output.
-template <bool kPaired>
+template <bool kPaired, bool kAhead>
 __device__ __forceinline__ int32_t insert_general(const Seq &seq, int64_t q, Slot *__restrict__ table, int64_t mask,
-                                               int32_t *status) {
+                                                  int32_t *status) {
   const int col = seq_col<kPaired>(q);
   int32_t *out = ((kPaired && col == 1) ? seq.out[1] : seq.out[0]) + seq_row<kPaired>(q);
   const StrCol cv = (kPaired && col == 1) ? seq.col[1] : seq.col[0];
@@ -506,14 +508,16 @@ __device__ __forceinline__ int32_t insert_general(const Seq &seq, int64_t q, Slo
   int64_t start, len;
   string_range(*c, seq_row<kPaired>(q), start, len, bad);
   const int64_t words = (len + 6) / 7;
-  uint64_t wr[kRegWords];
+  constexpr int kKept = kAhead ? kRegWords : 0;  // words in registers
+  uint64_t wr[kKept + 1];
 #pragma unroll
-  for (int i = 0; i < kRegWords; ++i) wr[i] = i < words ? word7_global(c, start, len, i) : 0;
+  for (int i = 0; i < kKept; ++i) wr[i] = i < words ? word7_global(c, start, len, i) : 0;
   uint64_t h = hash_seed(len);
 #pragma unroll
-  for (int i = 0; i < kRegWords; ++i)
+  for (int i = 0; i < kKept; ++i)
     if (i < words) h = hash_step(h, wr[i]);
-  for (int64_t i = kRegWords; i < words; ++i) h = hash_step(h, word7_global(c, start, len, i));
+#pragma unroll 2
+  for (int64_t i = kKept; i < words; ++i) h = hash_step(h, word7_global(c, start, len, i));
   h = fmix64(h);
   const uint64_t ident = ((h >> 44) << 12) | uint64_t(min(len, kLenField));
   const uint64_t mine = (ident << 32) | uint32_t(q);
@@ -525,9 +529,9 @@ __device__ __forceinline__ int32_t insert_general(const Seq &seq, int64_t q, Slo
     // Through the caches, as in the fast pass: what that pass wrote is visible
     // here, and what this one adds is at worst seen as empty or unwritten.
     const uint4 k4 = load16(&sl->key);
-    uint4 pr[kRegWords / 2];
+    uint4 pr[kKept / 2 + 1];
 #pragma unroll
-    for (int j = 0; j < kRegWords / 2; ++j) pr[j] = 2 * j < nw ? load16(&sl->words[2 * j]) : make_uint4(0, 0, 0, 0);
+    for (int j = 0; j < kKept / 2; ++j) pr[j] = 2 * j < nw ? load16(&sl->words[2 * j]) : make_uint4(0, 0, 0, 0);
     uint64_t k = u64_of(k4.x, k4.y);
     if (k4.x == 0xffffffffu || k4.y == 0xffffffffu) {  // empty, or seen while it changed
       const uint64_t prev = atomicCAS(reinterpret_cast<unsigned long long *>(&sl->key),
@@ -547,19 +551,22 @@ __device__ __forceinline__ int32_t insert_general(const Seq &seq, int64_t q, Slo
     if (nw >= 0) {
       int seen = 0;  // bit k set: some word had state k
 #pragma unroll
-      for (int j = 0; j < kRegWords / 2; ++j) {
+      for (int j = 0; j < kKept / 2; ++j) {
         if (2 * j < nw) seen |= 1 << word_state(u64_of(pr[j].x, pr[j].y), wr[2 * j]);
         if (2 * j + 1 < nw) seen |= 1 << word_state(u64_of(pr[j].z, pr[j].w), wr[2 * j + 1]);
       }
-      for (int i = kRegWords; i < nw && !(seen & 2); ++i) {
-        const uint4 v = load16(&sl->words[i & ~1]);
-        seen |= 1 << word_state((i & 1) ? u64_of(v.z, v.w) : u64_of(v.x, v.y), word7_global(c, start, len, i));
+#pragma unroll 1
+      for (int i = kKept; i < nw && !(seen & 2); i += 2) {
+        const uint4 v = load16(&sl->words[i]);
+        seen |= 1 << word_state(u64_of(v.x, v.y), word7_global(c, start, len, i));
+        if (i + 1 < nw) seen |= 1 << word_state(u64_of(v.z, v.w), word7_global(c, start, len, i + 1));
       }
       same = (seen & 2) ? 0 : ((seen & 4) ? -1 : 1);
     }
     if (same < 0) {
       const int64_t rep = int64_t(uint32_t(k));
-      const StrCol *rc = &seq.col[seq_col<kPaired>(rep)];
+      const StrCol rcv = (kPaired && seq_col<kPaired>(rep) == 1) ? seq.col[1] : seq.col[0];
+      const StrCol *rc = &rcv;
       int rbad = 0;
       int64_t rstart, rlen;
       string_range(*rc, seq_row<kPaired>(rep), rstart, rlen, rbad);
@@ -590,10 +597,23 @@ __device__ __forceinline__ int32_t insert_general(const Seq &seq, int64_t q, Slo
 // took 285 + 408 us. Lookups from a thread per occurrence, each lowering
 // minpos itself: 131 + 84 us, and 25 + 12 us on 5,000 triples.
 constexpr int kMasksPerWave = 8;
-constexpr int64_t kGeneralWaves = 16384;  // below this many masks a wave takes one: the chip holds them all
+constexpr int64_t kGeneralWaves = 16384;  // below this many masks a wave takes one
 
-template <bool kPaired>
-__global__ __launch_bounds__(kThreads) void insert_general_kernel(Seq seq, uint64_t *__restrict__ deferred,
+// The lookups of few masks read ahead (122 registers, 4 waves per SIMD), those
+// of many hold less (72 registers, 7 waves; one left of it spills two). The
+// line is what the chip holds of the former, 256 CUs of 16 waves: below it
+// every wave is there from the start and only the length of its chain of reads
+// counts. Vocabulary calls, triples and share of literals beyond an inline
+// copy, reading ahead / not: 5,000, 0: 87 / 94 us; 60,000, 0: 170 / 176;
+// 300,000, 0.5: 455 / 428; 3M, 0.1: 1,478 / 1,221; 3M, 0.5: 2,243 / 1,757;
+// 10M, 0.5: 8,397 / 6,163; 20M, 0: 2,412 / 2,382. With literals only it is
+// 3M: 2,028 / 2,127, as each takes the long way once and few share a slot.
+// (8 waves, 64 registers with 8 spills: 3M 0.5 1,699, literals only 2,195.)
+constexpr int64_t kAheadMasks = 4096;
+constexpr int kManyWaves = 7;
+
+template <bool kPaired, bool kAhead>
+__global__ __launch_bounds__(kThreads, kAhead ? 1 : kManyWaves) void insert_general_kernel(Seq seq, uint64_t *__restrict__ deferred,
                                                                   int64_t words, Slot *__restrict__ table,
                                                                   int64_t mask, int32_t *status) {
   const int lane = lane_id();
@@ -610,7 +630,7 @@ __global__ __launch_bounds__(kThreads) void insert_general_kernel(Seq seq, uint6
                        uint32_t(__builtin_amdgcn_readlane(int(own), k));
     const int64_t q = (wave + k * stride) * 64 + lane;
     int32_t slot = -1;
-    if ((m >> lane) & 1u) slot = insert_general<kPaired>(seq, q, table, mask, status);
+    if ((m >> lane) & 1u) slot = insert_general<kPaired, kAhead>(seq, q, table, mask, status);
     // Of the lanes with one slot the first has the smallest occurrence: it alone
     // lowers minpos (one update per occurrence queues at the frequent strings).
     bool first = false;
@@ -846,8 +866,13 @@ rdf2v_status insert_seq(const Seq &seq, const RankSeq &r, int32_t *status, hipSt
         seq, r.n, r.table, r.capacity - 1, r.bits, status);
   RDF2V_LAUNCH_CHECK();
   const int64_t waves = std::max(ceil_div(r.words, kMasksPerWave), std::min(r.words, kGeneralWaves));
-  insert_general_kernel<kPaired><<<dim3(unsigned(ceil_div(waves, kThreads / kWave))), dim3(kThreads), 0, stream>>>(
-      seq, r.bits, r.words, r.table, r.capacity - 1, status);
+  const dim3 general(unsigned(ceil_div(waves, kThreads / kWave)));
+  if (r.words <= kAheadMasks)
+    insert_general_kernel<kPaired, true><<<general, dim3(kThreads), 0, stream>>>(seq, r.bits, r.words, r.table,
+                                                                                 r.capacity - 1, status);
+  else
+    insert_general_kernel<kPaired, false><<<general, dim3(kThreads), 0, stream>>>(seq, r.bits, r.words, r.table,
+                                                                                  r.capacity - 1, status);
   RDF2V_LAUNCH_CHECK();
   return RDF2V_OK;
 }

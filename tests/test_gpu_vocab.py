@@ -134,6 +134,23 @@ def test_long_strings_at_scale():
     assert ref[3] == len(ents) and ref[4] == len(preds)
 
 
+@pytest.mark.parametrize("T", [131_072, 131_073, 262_145])
+def test_literals_read_ahead_or_not(T):
+    # The general pass holds a string's first words for up to 4,096 groups of 64
+    # occurrences (131,072 triples for entities, twice that for predicates) and
+    # reads word by word beyond. Strings on both sides of the 98-byte inline
+    # copy and of the 56 bytes held, so that the long ones push short ones of
+    # their block out of its stage and those compare with inline copies.
+    say(f"[vocab] literals, {T} triples")
+    rng = np.random.default_rng(29)
+    stem = bytes(rng.integers(0, 256, 400, dtype=np.uint8))
+    lens = np.concatenate([np.arange(0, 120), rng.integers(120, 400, 60)])
+    pool = [stem[:int(k)] + b"%03d" % j for j in range(6) for k in lens]
+    cols = [_column([pool[i] for i in rng.integers(0, len(pool), T)], lead=int(rng.integers(0, 8)))
+            for _ in range(3)]
+    _compare(cols, f"literals, {T} triples", max_e=len(pool), max_p=len(pool))
+
+
 def test_inline_copy_length_boundary():
     # Strings of 96..100 bytes differing only in their last byte: up to 98 bytes
     # they are compared against the slot's inline copy, beyond it against the
