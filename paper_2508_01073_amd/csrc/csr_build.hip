@@ -489,11 +489,20 @@ __global__ __launch_bounds__(kSortThreads) void csr_small_kernel(
 // row_ptr[v] = number of sorted subjects < v, for v in [0, V], from the sorted
 // subjects in one pass: where the subject changes from a (at position i-1) to
 // b (at i), every v in (a, b] has row_ptr[v] = i; the subjects v above the
-// last one get n. A thread writes at most kGapRun of those entries; longer
+// last one get n. A thread writes at most gap_run of those entries; longer
 // runs of entities without out-edges keep the -1 that the first count pass put
 // there, and row_ptr_fixup_kernel finds each of them by binary search.
 // ---------------------------------------------------------------------------
+// Writing a gap is cheaper than a search per entry while the gaps are short
+// or there are threads enough: 1M triples over 10M entities 144 us with runs
+// of 64, 195 us with 1; 3M over 10M is slower with 1 as well. With four
+// entities per triple and few triples, the threads that write the gaps, 16 of
+// them each, are few and the searching ones many: 20,000 triples over 1M
+// entities 175 us with runs of 64, 106 us with 1; 8,193 over 1M 161 / 63;
+// 200,000 over 10M 214 / 148; 400,000 over 10M 181 / 165.
 constexpr int kGapRun = 64;
+constexpr int64_t kSparse = 4;                   // entities per triple ...
+constexpr int64_t kSparseMax = int64_t(1) << 19;  // ... and fewer triples than this: runs of 1
 
 // The sorted subjects as the last pass left them: the low bits of each, and
 // where each top digit begins. kKey: bytes of a stored key (4: the whole
@@ -524,6 +533,7 @@ constexpr int kBoundItems = kKey == 4 ? 8 : 16;
 template <int kKey>
 __global__ __launch_bounds__(kBoundThreads) void row_ptr_bounds_kernel(const SortedKeys sorted,
                                                                        int64_t n_triples, int32_t num_entities,
+                                                                       uint32_t gap_run,
                                                                        int32_t *__restrict__ row_ptr) {
   // Positions and ids are below 2^31: unsigned 32-bit arithmetic throughout.
   constexpr uint32_t kItems = kBoundItems<kKey>;
@@ -587,7 +597,7 @@ __global__ __launch_bounds__(kBoundThreads) void row_ptr_bounds_kernel(const Sor
     const uint32_t b = i == n ? V : whole(k[j]);
     if (b >= first) {
       const uint32_t hi = min(b, V);  // ids >= V cannot occur after validation
-      const uint32_t lo = max(first, hi >= uint32_t(kGapRun) ? hi - (kGapRun - 1) : 0u);
+      const uint32_t lo = max(first, hi >= gap_run ? hi - (gap_run - 1) : 0u);
       for (uint32_t v = lo; v <= hi; ++v) row_ptr[v] = int32_t(i);
     }
     first = b + 1;
@@ -844,8 +854,9 @@ rdf2v_status launch_row_ptr_fill(int32_t *row_ptr, int32_t num_entities, hipStre
 template <int kKey>
 rdf2v_status launch_row_ptr(const SortedKeys &sorted, int64_t T, int32_t num_entities, int32_t *row_ptr,
                             hipStream_t stream) {
+  const int gap_run = T < kSparseMax && num_entities >= kSparse * T ? 1 : kGapRun;
   row_ptr_bounds_kernel<kKey><<<dim3(unsigned(ceil_div(T + 1, kBoundThreads * kBoundItems<kKey>))), dim3(kBoundThreads), 0,
-                                stream>>>(sorted, T, num_entities, row_ptr);
+                                stream>>>(sorted, T, num_entities, uint32_t(gap_run), row_ptr);
   RDF2V_LAUNCH_CHECK();
   row_ptr_fixup_kernel<kKey><<<dim3(unsigned(ceil_div(int64_t(num_entities) + 1, 256))), dim3(256), 0, stream>>>(
       sorted, T, num_entities, row_ptr);

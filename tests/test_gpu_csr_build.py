@@ -2,7 +2,7 @@
 made to reach the edge cases of its kernels, bit-exact (row_ptr and edges whole):
 
 * row_ptr comes from one pass over the sorted subjects that fills at most 64 entities per
-  change of subject, the rest by binary search: runs of 62 to 66 and 127 to 129 entities
+  change of subject (one on sparse graphs), the rest by binary search: runs of 62 to 66 and 127 to 129 entities
   without out-edges between subjects, before the first subject and after the last;
 * the digit counts add a wave's equal digits with one atomic: tiles that hold one hub's
   triples only, tiles half hub and half others, and tiles mixing many hubs;
@@ -135,3 +135,17 @@ def test_row_ptr_in_place_of_an_input(T, V, column):
         torch.cuda.synchronize()
         assert int(st.item()) == 0
         assert_csr_equal(csr, rp, ed)
+
+
+@pytest.mark.parametrize("T,V", [(9_000, 35_999), (9_000, 36_000), (20_000, 1_000_000), (8_193, 5_000_000),
+                                 ((1 << 19) - 1, 1 << 21), (1 << 19, 1 << 21)])
+@pytest.mark.parametrize("clustered", [False, True])
+def test_gaps_of_sparse_graphs(T, V, clustered):
+    # Four entities per triple or more, below 2^19 triples: a subject writes its own row_ptr entry
+    # only and the gap before it is searched. Either side of both limits, with subjects spread over
+    # the ids and with a few runs of them (long gaps beside rows without one).
+    rng = np.random.default_rng(T + V)
+    s = rng.integers(0, V, T)
+    if clustered:
+        s = (rng.choice([0, 1, V // 2, V - 300], T) + rng.integers(0, 300, T)) % V
+    _check(s, rng.integers(0, 7, T), rng.integers(0, V, T), V, 7, f"sparse, clustered={clustered}")
