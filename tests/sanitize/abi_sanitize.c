@@ -88,6 +88,12 @@ int main(void) {
   EXPECT(rdf2v_bfs_walks(&csr, FI, INT64_MAX, 64, INT32_MAX, FI, FI, FI, F, 1 << 20, NULL, NULL) ==
          RDF2V_ERR_TOO_LARGE);
   EXPECT(rdf2v_bfs_walks(&csr, FI, 10, 2, 0, FI, FI, FI, F, 1 << 20, NULL, NULL) == RDF2V_ERR_INVALID_ARGUMENT);
+  EXPECT(rdf2v_bfs_fill_unused(FI, INT64_MAX, INT32_MAX, 129, FI, FI, NULL) == RDF2V_ERR_TOO_LARGE);
+  EXPECT(rdf2v_bfs_fill_unused(FI, INT64_MIN, 4, 9, FI, FI, NULL) == RDF2V_ERR_INVALID_ARGUMENT);
+  EXPECT(rdf2v_bfs_fill_unused(FI, 10, INT32_MIN, 9, FI, FI, NULL) == RDF2V_ERR_INVALID_ARGUMENT);
+  EXPECT(rdf2v_bfs_fill_unused(FI, 10, 4, INT32_MAX, FI, FI, NULL) == RDF2V_ERR_INVALID_ARGUMENT);
+  EXPECT(rdf2v_bfs_fill_unused(FI, 10, 4, 9, NULL, FI, NULL) == RDF2V_ERR_INVALID_ARGUMENT);
+  EXPECT(rdf2v_bfs_fill_unused(NULL, 0, 4, 9, NULL, NULL, NULL) == RDF2V_OK);
 
   /* vocabulary */
   const uint8_t *C = (const uint8_t *)F;

@@ -315,6 +315,30 @@ def test_bfs_walks_validation(lib):
     assert pkg.rdf2v_bfs_walks_workspace_size(50_000_000, 10**7) <= (1 << 32) + 3 * 10**9
 
 
+def test_bfs_fill_unused_validation(lib):
+    so, pkg = lib
+    assert "rdf2v_bfs_fill_unused" in _declared_functions()
+    fake = ctypes.c_void_p(1 << 40)
+
+    def call(roots, max_walks, width, counts=fake, tokens=fake, lens=fake):
+        return so.rdf2v_bfs_fill_unused(counts, roots, max_walks, width, tokens, lens, None)
+
+    ok, invalid, too_large = pkg.RDF2V_OK, pkg.RDF2V_ERR_INVALID_ARGUMENT, pkg.RDF2V_ERR_TOO_LARGE
+    assert call(-1, 4, 9) == invalid
+    for max_walks in (0, -1, -(1 << 31)):
+        assert call(10, max_walks, 9) == invalid
+    for width in (0, -1, 130, (1 << 31) - 1):
+        assert call(10, 4, width) == invalid
+        assert call(0, 4, width) == invalid
+    assert call(10, 4, 9, counts=None) == invalid
+    assert call(10, 4, 9, tokens=None) == invalid
+    assert call(10, 4, 9, lens=None) == invalid
+    assert call(1 << 31, 4, 9) == too_large
+    assert call((1 << 63) - 1, (1 << 31) - 1, 129) == too_large
+    assert call(0, 4, 9) == ok
+    assert call(0, 1, 129, counts=None, tokens=None, lens=None) == ok
+
+
 def test_vocabulary_validation(lib):
     so, pkg = lib
     f = so.rdf2v_build_vocabulary
