@@ -246,8 +246,8 @@ rdf2v_status rdf2v_skipgram_pairs(const int32_t *tokens, const int32_t *len, int
  * rdf2v_skipgram_pairs for callers that cannot allocate device memory (code
  * being captured into a graph, tight serving loops, harnesses that forbid
  * hipMalloc): the same pairs, count and status, with the same arguments
- * except that there is no workspace. The scratch (per-walk output offsets and
- * block sums) lives instead in a device array of RDF2V_NOALLOC_SCRATCH_BYTES
+ * except that there is no workspace. The scratch (an output offset per block
+ * of walks, and their sums) lives instead in a device array of RDF2V_NOALLOC_SCRATCH_BYTES
  * that the library holds on every device it runs on until the process ends;
  * the first call on a device looks its address up (making that device current
  * for the lookup and restoring the caller's current device). The call itself

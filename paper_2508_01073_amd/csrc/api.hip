@@ -180,7 +180,7 @@ RDF2V_API rdf2v_status rdf2v_skipgram_pairs(const int32_t *tokens, const int32_t
 
 RDF2V_API size_t rdf2v_cbow_examples_workspace_size(int64_t num_walks) {
   if (num_walks < 0 || num_walks > kMaxRows) return 0;
-  return rdf2v::skipgram_workspace_bytes(num_walks);  // the same per-walk offsets and block sums
+  return rdf2v::skipgram_workspace_bytes(num_walks);  // the same offsets per block and their sums
 }
 
 RDF2V_API rdf2v_status rdf2v_cbow_examples(const int32_t *tokens, const int32_t *len, int64_t num_walks,

@@ -3,7 +3,7 @@
 // The CSR's rows must keep the triples' input order (a stable sort by subject),
 // so that walk parity is exact and independent of scheduling. Atomics cannot
 // give that order; an LSD radix sort on the subject id can, because every pass
-// is a stable counting sort on one digit. A pass is two or three launches:
+// is a stable counting sort on one digit. A pass is three launches:
 //   1. radix_count:   per tile of up to 8,192 triples, a histogram of the pass's digit
 //                     (LDS atomics), written digit-major to a count table;
 //   2. row_scan:      exclusive scan of each digit's row of that table (one

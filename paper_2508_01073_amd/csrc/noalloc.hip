@@ -2,8 +2,8 @@
 // device memory (code under stream capture, tight serving loops, harnesses that
 // forbid hipMalloc).
 //
-// rdf2v_skipgram_pairs takes its scratch (per-walk output offsets and the scan's
-// block sums) from a caller workspace. This variant keeps that scratch in one
+// rdf2v_skipgram_pairs takes its scratch (an output offset per block of walks and
+// the scan's sums) from a caller workspace. This variant keeps that scratch in one
 // fixed file-scope device array instead. HIP gives every device that loads
 // this code object its own copy of the array, at its own address; the host
 // name `scratch` is only a stand-in for it, so the device address is looked up

@@ -196,8 +196,10 @@ constexpr int kBatchPairs = 3;     // further pairs of inline words read togethe
 // compare-and-swap), each inline word from 0 to its final value once, and
 // minpos only decreases. So a stale key reads as empty and the
 // compare-and-swap then returns the real one; a stale word reads as not
-// written and the occurrence is left to the general pass, which reads at agent
-// scope; a stale minpos is larger than the real one and at worst costs an
+// written and the occurrence is left to the general pass, which reads the same
+// way but settles an unwritten word, stale or not, against the bytes of the
+// representative the key names, and an empty key by the compare-and-swap as
+// here; a stale minpos is larger than the real one and at worst costs an
 // atomicMin that changes nothing. The checks also hold if a load were to see
 // one 4-byte half of a key or word updated and the other not: a key with
 // either half all ones goes through the compare-and-swap, and a word counts as
