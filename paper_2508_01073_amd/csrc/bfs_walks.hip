@@ -586,9 +586,10 @@ __global__ void bfs_queue_reset_kernel(int32_t *queue_counts) {
 // entities; the random bit tests and updates then never leave the CU) and in
 // the workgroup's slice otherwise, and a chunk is as wide as registers allow.
 // Measured on the 20M-triple power-law graph (1M entities, depth 2, 1,000
-// roots of 290K pairs on average and 5M at most): 2.4 ms, the time of the root
-// with most pairs, against 165 ms with 64-bit offers per entity in the
-// workspace (two random accesses at agent scope per pair, 119 workgroups).
+// roots of 290K pairs on average and 5M at most): 2.4 ms, calls of 2.4 to 3.4 ms
+// by the roots drawn: the time of the root with most pairs, against 165 ms with
+// 64-bit offers per entity in the workspace (two random accesses at agent scope
+// per pair, 119 workgroups).
 // A slice holds 25 bytes per tree node: entity, parent, predicate, a
 // has-a-child byte, and for the nodes of the level being expanded that have
 // records their position, row start and degree prefix.

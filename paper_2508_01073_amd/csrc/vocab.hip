@@ -601,16 +601,16 @@ __device__ __forceinline__ int32_t insert_general(const Seq &seq, int64_t q, Slo
 constexpr int kMasksPerWave = 8;
 constexpr int64_t kGeneralWaves = 16384;  // below this many masks a wave takes one
 
-// The lookups of few masks read ahead (122 registers, 4 waves per SIMD), those
-// of many hold less (72 registers, 7 waves; one left of it spills two). The
-// line is what the chip holds of the former, 256 CUs of 16 waves: below it
-// every wave is there from the start and only the length of its chain of reads
-// counts. Vocabulary calls, triples and share of literals beyond an inline
-// copy, reading ahead / not: 5,000, 0: 87 / 94 us; 60,000, 0: 170 / 176;
-// 300,000, 0.5: 455 / 428; 3M, 0.1: 1,478 / 1,221; 3M, 0.5: 2,243 / 1,757;
-// 10M, 0.5: 8,397 / 6,163; 20M, 0: 2,412 / 2,382. With literals only it is
-// 3M: 2,028 / 2,127, as each takes the long way once and few share a slot.
-// (8 waves, 64 registers with 8 spills: 3M 0.5 1,699, literals only 2,195.)
+// The lookups of few masks read ahead (116 registers, 4 waves per SIMD), those
+// of many hold less (72 registers with 2 spills, 7 waves). The line is what the
+// chip holds of the former, 256 CUs of 16 waves: below it every wave is there
+// from the start and only the length of its chain of reads counts. Vocabulary
+// calls, triples and the share of entities that are text of 11 to 158 bytes in
+// place of an IRI, us reading ahead / not: 5,000, 0: 87 / 94; 60,000, 0:
+// 170 / 176; 300,000, 0.5: 455 / 428; 3M, 0.1: 1,478 / 1,221; 3M, 0.5:
+// 2,243 / 1,757; 10M, 0.5: 8,397 / 6,163; 20M, 0: 2,412 / 2,382. Only 3M
+// triples of text alone take longer, 2,028 / 2,127. (8 waves, 64 registers with
+// 8 spills: 3M, 0.5 1,699; text alone 2,195.)
 constexpr int64_t kAheadMasks = 4096;
 constexpr int kManyWaves = 7;
 
