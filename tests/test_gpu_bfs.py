@@ -249,7 +249,7 @@ def test_trees_beyond_the_lds_tiers(V, fan, depth, max_walks):
 
 
 @pytest.mark.parametrize("depth,max_walks", [(0, 1), (1, 3), (2, 7), (3, 64), (4, 1000)])
-def test_unused_rows_are_filled(depth, max_walks):
+def test_unused_rows_are_filled(depth, max_walks, monkeypatch):
     # outputs allocated by the binding: -1 and 0 past every root's walks, whatever the memory held
     say(f"[bfs] unused rows depth={depth} max_walks={max_walks}")
     rng = np.random.default_rng(depth)
@@ -257,9 +257,17 @@ def test_unused_rows_are_filled(depth, max_walks):
     s, p, o = rng.integers(0, V // 2, T), rng.integers(0, P, T), rng.integers(0, V, T)
     csr = gpu_csr(*(x.astype(np.int32) for x in (s, p, o)), V, P)
     roots = np.concatenate([rng.integers(0, V, 300), [V + 5, 0, -1]]).astype(np.int32)
-    junk = torch.full((len(roots) * max_walks * (2 * depth + 2) + 64,), 77, dtype=torch.int32, device=device())
-    del junk  # the caching allocator hands this memory to the call
-    tok, ln, cnt = rd.rdf2v_bfs_walks(csr, to_dev(roots), depth, max_walks, status=new_status())
+    empty, filled = torch.empty, []
+
+    def junk(*args, **kw):  # every buffer that the call allocates starts as junk
+        filled.append(empty(*args, **kw).fill_(77))
+        return filled[-1]
+
+    d_roots, st = to_dev(roots), new_status()
+    with monkeypatch.context() as m:
+        m.setattr(torch, "empty", junk)
+        tok, ln, cnt = rd.rdf2v_bfs_walks(csr, d_roots, depth, max_walks, status=st)
+    assert any(x is tok for x in filled) and any(x is ln for x in filled)
     tok, ln, cnt = tok.cpu().numpy(), ln.cpu().numpy(), cnt.cpu().numpy()
     unused = np.arange(max_walks)[None, :] >= cnt[:, None]
     assert (tok[unused] == -1).all() and (ln[unused] == 0).all()
